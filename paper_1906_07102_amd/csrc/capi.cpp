@@ -38,7 +38,8 @@ struct lmg_plan {
     int max_items = 0;
     int cap = 0;
     int M = 0;                  // retained image size 2 x0 N
-    int waves = 0;              // waves (private LDS patches) per gridding workgroup
+    int npatch = 1;             // LDS patches per gridding workgroup
+    int waves = 0;              // waves per gridding workgroup
     int nchan = 1;              // channels (grids), each with its own run of visibilities
     int nblocks = 0;            // plan blocks (runs of <= kPlanBlockVis visibilities of one channel)
     mutable bool bad_data = false;
@@ -116,36 +117,40 @@ int choose_tile(int N, int W) {
     return T;
 }
 
-// Largest tile <= T whose table and four private patches fit one
-// workgroup's LDS; where the tile cannot shrink (at most 128 x 128 tiles),
-// fewer waves per workgroup (fit_waves).
+// Largest tile <= T of which the table and four patches fit a compute unit's LDS, so that several workgroups share
+// it (and the patches of a sparse plan stay small enough for the allocation-free call's fixed scratch); where the
+// tile cannot shrink (at most 128 x 128 tiles), fewer.
 int fit_tile(int T, int N, lmg_precision prec, int W, int Ms) {
-    while (T / 2 >= min_tile(W) && grid_lds_bytes(prec, W, T, Ms, kMaxGridWaves) > kMaxDynLds && N / (T / 2) <= 128)
-        T /= 2;
+    while (T / 2 >= min_tile(W) && grid_lds_bytes(prec, W, T, Ms, 4) > kMaxDynLds && N / (T / 2) <= 128) T /= 2;
     return T;
 }
-// Waves (private patches) per gridding workgroup: the count that lets a
-// compute unit hold the most waves by LDS (160 KB per unit), capped at what
-// the kernel's registers allow (env LMG_GRID_WAVES overrides, 1..4).
-int fit_waves(int T, lmg_precision prec, int W, int Ms) {
+// LDS patches of a gridding workgroup: two where two workgroups of two patches share a compute unit (tiles of 32
+// cells), else one (64-cell tiles: 4.2M visibilities on 8192^2 in FP32 154 us with one, 207 with two). With one patch
+// the flushes of a workgroup's waves wait for each other: four waves on one / two patches, W = 7 kernel times, 16.8M
+// visibilities FP32 206 / 187 us, compensated 293 / 274, FP64 474 / 450; 3.0M of one density on 2048^2 FP32 114 / 84,
+// compensated 176 / 122, FP64 188 / 147. (256 sparse channels at W = 5, compensated, are the exception: 458 with one
+// patch and three waves, 510 with two and four.) A function of the mode, support and tile alone: the number of
+// patches fixes the order of the sums, which a batch and a single channel share.
+int fit_patches(int T, lmg_precision prec, int W, int Ms) {
+    return 2 * (grid_lds_bytes(prec, W, T, Ms, 2) + 256) <= kMaxLds ? 2 : 1;
+}
+// Waves per gridding workgroup, a multiple of its patches: four, as an item has about four turns (16.8M visibilities:
+// 4.1) and the waves beyond an item's turns only wait (4.2M, W = 10, compensated: 234 us with four, 344 with six).
+// A launch of few items gets six, since it does not fill the chip and an item's latency is what counts: 202K
+// visibilities on 1024^2 58 us with four, 45 with six; 1.0M on 2048^2, W = 5, 54 and 47; but 3.0M of one density on
+// 2048^2, 84 and 129. The estimate takes a quarter of the tiles as occupied, as an image's data are. (env
+// LMG_GRID_WAVES overrides, 1 .. kMaxGridWaves)
+int fit_waves(int T, int N, int nchan, int64_t nvis, int cap, lmg_precision prec, int W, int* npatch) {
+    const int most = max_grid_waves(prec, W);
     const int forced = env_int("LMG_GRID_WAVES", 0);
-    if (forced >= 1 && forced <= kMaxGridWaves && grid_lds_bytes(prec, W, T, Ms, forced) <= kMaxDynLds) return forced;
-    // Waves per compute unit the kernel's registers allow: about 3 per SIMD for plain and compensated
-    // FP32 (W x W complex FP32 accumulators), 1 for FP64 (twice the accumulator registers).
-    const int by_registers = prec == LMG_F64 ? 4 : 12;
-    // The compensated form's (hi, lo) patch cells make LDS the limit, and 1, 2 or 3 waves per workgroup often
-    // give a compute unit the same number of waves; there, more waves per workgroup measured faster up to 3
-    // at W >= 7 (0.456 / 0.380 / 0.318 ms on 16.8M visibilities at W = 7) and up to 2 below (0.269 / 0.211 /
-    // 0.228 ms at W = 5).
-    const int prefer = prec == LMG_F32_KAHAN ? (W >= 7 ? 3 : 2) : 1;
-    int best = 1, best_total = 0;
-    for (int w = 1; w <= kMaxGridWaves; ++w) {
-        const size_t b = grid_lds_bytes(prec, W, T, Ms, w) + 256;
-        if (b > kMaxLds) break;
-        const int total = std::min(static_cast<int>(kMaxLds / b) * w, by_registers);
-        if (total > best_total || (total == best_total && w <= prefer)) { best = w; best_total = total; }
+    if (forced >= 1 && forced <= kMaxGridWaves) {
+        const int w = std::min(forced, most);
+        if (w % *npatch) *npatch = 1;
+        return w;
     }
-    return best;
+    const int64_t tiles = static_cast<int64_t>(N / T) * (N / T) * nchan;
+    if (nvis <= (int64_t{1} << 20) && std::min((tiles + 3) / 4, nvis) + nvis / cap <= 2048) return std::min(6, most);
+    return 4;
 }
 
 int choose_cap() { return std::min(env_int("LMG_CAP", 8192), kMaxCap); }
@@ -470,7 +475,7 @@ lmg_status run_grid_entries(const lmg_plan* p, const void* vs, void* grid, void*
     GridArgs a{};
     a.N = p->g.N; a.W = p->g.W; a.T = p->g.T; a.ntx = p->g.ntx; a.Ms = table_ms(t); a.degree = kernel_degree(t);
     a.tab_global = table_global(t, p->prec) ? 1 : 0;
-    a.n_items = p->flags + 1; a.max_items = p->max_items; a.waves = p->waves; a.Ft = p->Ft; a.kb = p->kb;
+    a.n_items = p->flags + 1; a.max_items = p->max_items; a.npatch = p->npatch; a.waves = p->waves; a.Ft = p->Ft; a.kb = p->kb;
     a.items = p->items; a.pieces = p->pieces; a.off = p->off; a.coef = p->coef;
     a.vis = vs; a.patches = patches; a.counter = counters;
     {
@@ -570,9 +575,11 @@ lmg_status create_plan(const lmg_table* table, int N, lmg_precision prec, int nc
     if (table_global(table, prec) && !table->dev_coef[prec == LMG_F64 ? 1 : 0]) return LMG_ENOTSUP;
     const int T = tile ? tile : fit_tile(choose_tile(N, table->W), N, prec, table->W, staged_ms(table, prec));
     if (T < table->W || N / T > 128) return LMG_ENOTSUP;      // cannot happen for N >= 2W, N <= 8192
-    const int waves = fit_waves(T, prec, table->W, staged_ms(table, prec));
-    if (grid_lds_bytes(prec, table->W, T, staged_ms(table, prec), waves) > kMaxDynLds) return LMG_ENOTSUP;
     const int cap = choose_cap();
+    const int Ms = staged_ms(table, prec);
+    int npatch = fit_patches(T, prec, table->W, Ms);
+    const int waves = fit_waves(T, N, nchan, nvis, cap, prec, table->W, &npatch);
+    if (grid_lds_bytes(prec, table->W, T, Ms, npatch) > kMaxDynLds) return LMG_ENOTSUP;
     const Layout L = plan_layout(N, nvis, prec, cap, nchan);
     if (!workspace || ws_bytes < L.total) return LMG_EWORKSPACE;
     if (ensure_attributes() != hipSuccess) return LMG_EHIP;
@@ -586,6 +593,7 @@ lmg_status create_plan(const lmg_table* table, int N, lmg_precision prec, int nc
     p->g.nchan = nchan;
     p->g.ref = tap_reference(table->W);
     p->waves = waves;
+    p->npatch = npatch;
     p->nchan = nchan;
     p->nvis = nvis;
     p->cap = cap;

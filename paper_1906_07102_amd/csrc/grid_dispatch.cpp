@@ -55,12 +55,12 @@ hipError_t launch_assemble(lmg_precision prec, const AssembleArgs& args, hipStre
     return hipErrorInvalidValue;
 }
 
-size_t grid_lds_bytes(lmg_precision prec, int W, int T, int Ms, int waves) {
+size_t grid_lds_bytes(lmg_precision prec, int W, int T, int Ms, int npatch) {
     const size_t rs = prec == LMG_F64 ? 8 : 4;
     const size_t cell = prec == LMG_F32 ? 8 : 16;
     const size_t tab = ((static_cast<size_t>(Ms + 1) * W * 4 * rs) + 15) & ~size_t(15);
     const size_t P = static_cast<size_t>(T + W - 1);
-    return tab + P * P * (cell + 1) * static_cast<size_t>(waves);
+    return tab + P * P * (cell + 1) * static_cast<size_t>(npatch);
 }
 
 }  // namespace lmg

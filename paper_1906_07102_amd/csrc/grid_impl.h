@@ -13,9 +13,9 @@ namespace dev {
 
 // ------------------------------------------------------------ gridding
 // Accumulation policies. `Reg` accumulates one footprint cell over a piece
-// in registers; `Cell` is the LDS patch element. Patches are private to a
-// wave, so a flush is a plain read-modify-write. Lanes of one wave may flush
-// overlapping footprints, so one tap's store must reach LDS before another
+// in registers; `Cell` is the LDS patch element. One wave at a time
+// flushes into a patch, so a flush is a plain read-modify-write. Lanes of one wave
+// may flush overlapping footprints, so one tap's store must reach LDS before another
 // tap's load: the patch is accessed with 64-bit atomic loads and stores of
 // wavefront scope and sequential consistency, which the compiler neither
 // merges nor reorders (LDS executes one wave's operations in order, so they
@@ -165,18 +165,27 @@ struct AccF64 {
 // RG footprint rows (RG x W accumulators) and then adds them to the patch;
 // footprints wider than the mode's register budget (Acc::kAccRegBudget) take
 // several such passes over the piece. The FP32 forms keep the accumulators
-// near 112 registers, so that three waves fit a SIMD; FP64, whose patch cells
-// and table hold a compute unit to four waves by LDS anyway, takes 224 (one
-// pass at W = 7: 0.59 -> 0.48 ms on 16.8M visibilities).
+// near 112 registers, so that three waves fit a SIMD; FP64 takes 224, one pass
+// at W = 7, where two waves fit (16.8M visibilities, 0.59 -> 0.48 ms with one
+// pass instead of two), but two passes of four rows at W = 8, which leave room
+// for two waves as well (4.2M: 555 -> 445 us with one pass of seven and one of
+// a single row before); wider FP64 footprints keep one wave per SIMD.
 template <typename Acc, int W>
 struct RowGroup {
+    static constexpr bool kF64 = sizeof(typename Acc::Reg) == 16;
     static constexpr int kRegsPerTap = static_cast<int>(sizeof(typename Acc::Reg) / 4);
-    static constexpr int kRG0 = Acc::kAccRegBudget / (kRegsPerTap * W);
-    static constexpr int RG = kRG0 < 1 ? 1 : (kRG0 > W ? W : kRG0);
-    static constexpr int kPasses = (W + RG - 1) / RG;
+    static constexpr int kRG0 = (kF64 && W == 8 ? 144 : Acc::kAccRegBudget) / (kRegsPerTap * W);
+    static constexpr int kRG1 = kRG0 < 1 ? 1 : (kRG0 > W ? W : kRG0);
+    static constexpr int kPasses = (W + kRG1 - 1) / kRG1;
+    static constexpr int RG = (W + kPasses - 1) / kPasses;     // the passes' rows as even as they go
+    static constexpr int kMaxWaves = max_grid_waves(kF64 ? LMG_F64 : LMG_F32, W);
 };
-
-constexpr int kGridWaves = 4;      // most waves per gridding workgroup (one private patch each; a.waves at run time)
+// Waves per SIMD the compiler keeps room for.
+template <typename Acc, int W, int kTab>
+constexpr int waves_per_simd() {
+    using G = RowGroup<Acc, W>;
+    return G::kMaxWaves == 4 ? 1 : (!G::kF64 && W <= 7 && kTab != kTabDirect) ? 3 : 2;
+}
 
 // Add the piece's accumulated rows r0 .. r0 + RG - 1 (those below W) to the
 // patch. Lanes holding the same cell take turns: each round one of them wins
@@ -210,10 +219,20 @@ __device__ __forceinline__ void flush_rows(typename Acc::Cell* patch, unsigned c
 // (a.counter, zero at launch) until none are left, so the table is staged
 // once per workgroup and uneven items (many channels of very different
 // sizes) balance dynamically.
+//
+// Pieces are taken 64 at a time (a "turn"; neighbouring full pieces, often of
+// one cell, go to different turns). A workgroup has S = a.npatch patches and
+// `waves` waves, a multiple of S; turn j is accumulated in registers by wave
+// j mod waves and flushed into patch j mod S, after the turns before it on
+// that patch (s_turn counts them). So the order of every sum is that of the
+// plan's pieces, whatever the number of waves. With as many waves as patches
+// nothing waits; more waves hide more latency where LDS holds few patches or
+// the launch has few items.
 template <typename R, typename Acc, int W, int kTab>
-__global__ __launch_bounds__(64 * kGridWaves) void k_grid_items(GridArgs a) {
+__global__ __launch_bounds__((64 * RowGroup<Acc, W>::kMaxWaves))
+__attribute__((amdgpu_waves_per_eu(waves_per_simd<Acc, W, kTab>()))) void k_grid_items(GridArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ int s_item;
+    __shared__ int s_item, s_turn[kMaxGridWaves];
     using VT = typename C2<R>::T;
     using PT2 = typename Pack<R>::T2;
     using Cell = typename Acc::Cell;
@@ -224,11 +243,12 @@ __global__ __launch_bounds__(64 * kGridWaves) void k_grid_items(GridArgs a) {
     R* tab = reinterpret_cast<R*>(smem);
     const int ntab = kTab == kTabLds ? (a.Ms + 1) * W * 4 : 0;
     Cell* patches = reinterpret_cast<Cell*>(smem + ((ntab * sizeof(R) + 15) & ~size_t(15)));
-    const int nw = a.waves;
-    unsigned char* owners = reinterpret_cast<unsigned char*>(patches + nw * P2);   // a lane id per cell
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    Cell* patch = patches + wave * P2;
-    unsigned char* owner = owners + wave * P2;
+    const int S = a.npatch;
+    unsigned char* owners = reinterpret_cast<unsigned char*>(patches + S * P2);   // a lane id per cell
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+    Cell* patch = patches + (wave % S) * P2;
+    unsigned char* owner = owners + (wave % S) * P2;
+    int* turn_of = &s_turn[wave % S];
     const R* gtab = reinterpret_cast<const R*>(a.coef);
     for (int i = threadIdx.x; i < ntab; i += blockDim.x) tab[i] = gtab[i];
     const VT* vis = reinterpret_cast<const VT*>(a.vis);     // entry order, weights applied
@@ -236,29 +256,31 @@ __global__ __launch_bounds__(64 * kGridWaves) void k_grid_items(GridArgs a) {
     const int nitems = *a.n_items;
     for (;;) {
         if (threadIdx.x == 0) s_item = atomicAdd(a.counter, 1);
-        for (int i = threadIdx.x; i < nw * P2; i += blockDim.x) Acc::zero_cell(&patches[i]);
+        if (threadIdx.x < S) s_turn[threadIdx.x] = 0;
+        for (int i = threadIdx.x; i < S * P2; i += blockDim.x) Acc::zero_cell(&patches[i]);
         __syncthreads();
         const int item = s_item;
         if (item >= nitems) break;                       // uniform across the workgroup
         const int4 it = a.items[item];
-        constexpr int kB = 4;                               // entries whose loads are issued together
-        const int rounds = (it.w + blockDim.x - 1) / blockDim.x;
-        // consecutive pieces go to different waves (a dense cell's full pieces are neighbours, and lanes of
-        // one wave sharing a cell flush in turns); a lane's piece of the next round is loaded a round ahead
-        const int p0 = (threadIdx.x & 63) * (blockDim.x >> 6) + (threadIdx.x >> 6);
-        int2 pc_next = make_int2(0, 0);
-        if (p0 < it.w) pc_next = a.pieces[it.y + p0];
-        for (int rd = 0; rd < rounds; ++rd) {               // uniform across the workgroup
-            const int p = rd * blockDim.x + p0;
-            const bool have = p < it.w;
-            const int2 pc = pc_next;
-            pc_next = make_int2(0, 0);
-            if (p + static_cast<int>(blockDim.x) < it.w) pc_next = a.pieces[it.y + p + blockDim.x];
-            const int len = pc.y & 0xffff;
-            const int l = static_cast<int>(static_cast<unsigned>(pc.y) >> 16);
+        // entries whose loads are issued together (FP64 at W = 7 with 1 / 2: 16.8M visibilities 453 / 460 us, 3.0M of
+        // one density 138 / 145; with 4 it spills at two waves per SIMD)
+        constexpr int kB = sizeof(R) == 8 && W <= 8 ? 1 : 4;
+        const int np = it.w & 0xffff, fturns = it.w >> 16;  // pieces; turns of full pieces only
+        const int turns = (np + 63) >> 6;
+        auto piece_of = [&](int j) { return j < fturns ? lane * fturns + j : j * 64 + lane; };
 #pragma unroll
-            for (int pass = 0; pass < NPASS; ++pass) {
-                const int r0 = pass * RG;
+        for (int pass = 0; pass < NPASS; ++pass) {
+            const int r0 = pass * RG;
+            int2 pc_next = make_int2(0, 0);                 // a lane's piece of the next turn is loaded a turn ahead
+            if (piece_of(wave) < np) pc_next = a.pieces[it.y + piece_of(wave)];
+            for (int j = wave; j < turns; j += nw) {        // uniform across the wave
+                const bool have = piece_of(j) < np;
+                const int2 pc = pc_next;
+                pc_next = make_int2(0, 0);
+                const int pn = piece_of(j + nw);
+                if (pn < np) pc_next = a.pieces[it.y + pn];
+                const int len = pc.y & 0xffff;
+                const int l = static_cast<int>(static_cast<unsigned>(pc.y) >> 16);
                 typename Acc::Reg acc[RG * W];
                 // One batch of kB entries from entry j0 of the piece. The first batch sets the accumulators
                 // from its first entry instead of adding to zeros; every lane runs that entry (a lane without
@@ -299,17 +321,25 @@ __global__ __launch_bounds__(64 * kGridWaves) void k_grid_items(GridArgs a) {
                 };
                 batch(0, std::true_type{});
                 for (int j0 = kB; j0 < len; j0 += kB) batch(j0, std::false_type{});
+                // The patch's turns are numbered in the order (pass, j); each is flushed by a wave that waits for
+                // none after it.
+                const int turn = pass * ((turns - wave % S + S - 1) / S) + j / S;
+                if (nw > S)
+                    while (__hip_atomic_load(turn_of, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) != turn)
+                        __builtin_amdgcn_s_sleep(1);
                 flush_rows<Acc, W, RG>(patch, owner, P, lane, have && len > 0, l, r0, acc);
+                if (nw > S && lane == 0)
+                    __hip_atomic_store(turn_of, turn + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
             }
         }
         __syncthreads();
         Cell* out = reinterpret_cast<Cell*>(a.patches) + static_cast<size_t>(item) * P2;
         for (int i = threadIdx.x; i < P2; i += blockDim.x) {
             typename Acc::Sum sum;
-            for (int w = 0; w < nw; ++w) sum.add(patches[w * P2 + i]);
+            for (int w = 0; w < S; ++w) sum.add(patches[w * P2 + i]);
             out[i] = sum.cell();
         }
-        __syncthreads();                                    // patches and s_item are reused
+        __syncthreads();                                    // the patches, s_item and s_turn are reused
     }
 }
 
@@ -459,7 +489,7 @@ template <typename R, typename Acc, int W, int kTab>
 hipError_t launch_grid_w(const GridArgs& a, hipStream_t s) {
     const int P = a.T + W - 1;
     const size_t tab = kTab == kTabLds ? ((static_cast<size_t>(a.Ms + 1) * W * 4 * sizeof(R)) + 15) & ~size_t(15) : 0;
-    const size_t shm = tab + static_cast<size_t>(P) * P * (sizeof(typename Acc::Cell) + 1) * a.waves;
+    const size_t shm = tab + static_cast<size_t>(P) * P * (sizeof(typename Acc::Cell) + 1) * a.npatch;
     const void* fn = reinterpret_cast<const void*>(&dev::k_grid_items<R, Acc, W, kTab>);
     static const hipError_t attr = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxDynLds);
     if (attr != hipSuccess) return attr;

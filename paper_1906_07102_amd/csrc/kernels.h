@@ -45,7 +45,7 @@ struct GridArgs {
     int tab_global;        // 1: read the coefficient table from device memory, not LDS
     const int* n_items;    // device: number of work items (written by the plan)
     int max_items;         // most work items the plan can have (sizes the launch)
-    int waves;             // waves per workgroup, 1..4, each with its own LDS patch
+    int npatch, waves;     // LDS patches per workgroup; waves per workgroup, a multiple of it up to kMaxGridWaves
     int Ft, kb;            // packed offsets: bits of the in-interval fraction t and of the interval k
     const int4* items;     // (tile, first position, count, pieces)
     const int2* pieces;    // (first entry, length | cell << 16)
@@ -136,10 +136,12 @@ hipError_t set_kernel_attributes();
 // Read (and, if set, clear) the device-wide flag the plans raise on non-finite coordinates, on the
 // current device. Synchronous.
 hipError_t take_data_error(int* flag);
-// LDS bytes of the gridding kernel with `waves` private patches (the
-// degridding kernel needs no more than one patch).
-size_t grid_lds_bytes(lmg_precision prec, int W, int T, int Ms, int waves);
-constexpr int kMaxGridWaves = 4;
+// LDS bytes of the gridding kernel with `npatch` patches (the degridding
+// kernel needs no more than one patch).
+size_t grid_lds_bytes(lmg_precision prec, int W, int T, int Ms, int npatch);
+constexpr int kMaxGridWaves = 8;
+// Most waves of a gridding workgroup: four where the accumulators need a SIMD's whole register file.
+constexpr int max_grid_waves(lmg_precision prec, int W) { return prec == LMG_F64 && W >= 9 ? 4 : kMaxGridWaves; }
 constexpr size_t kMaxLds = 160 * 1024;
 // Dynamic LDS the item kernels may request: they also hold a few bytes of
 // static LDS (the current work item), and both must fit the 160 KB.

@@ -370,14 +370,14 @@ __global__ __launch_bounds__(kPermThreads) void k_plan_place(const int* __restri
 
 // Pass 4 (workgroups loop over items): order the item's visibilities into
 // pieces (at most kPiece visibilities of one footprint cell) and lay the
-// entries out in piece order, so that a round of the gridding kernel, which
-// takes consecutive pieces, reads one contiguous range. Piece order: the full
+// entries out in piece order, so that a turn of the gridding kernel, which
+// takes 64 of them, reads one contiguous range. Piece order: the full
 // pieces, cell by cell (cell c's f = n / kPiece pieces at F(c) .. F(c)+f-1,
 // F an exclusive prefix of f), then the tails, longest first (a wave's lanes
 // run loops of similar length). Outputs: packed offsets `off` by entry,
 // pos2 (tile-order position -> entry), pieces[] (first entry, length |
-// cell << 16) and items[i].w = number of pieces. Dropped visibilities
-// (tile-order positions n_valid .. nvis) get pos2 = -1.
+// cell << 16) and items[i].w = number of pieces | (full pieces / 64) << 16.
+// Dropped visibilities (tile-order positions n_valid .. nvis) get pos2 = -1.
 // Ranks within a cell follow the item's tile order in a fixed way: the item
 // is cut into `groups` contiguous chunks, one per group of waves, each with
 // its own LDS cell counters whose bases are the counts of the chunks before
@@ -461,7 +461,7 @@ __global__ __launch_bounds__(kSortThreads) void k_plan_sort_items(PlanGeom g, in
                 lcnt[t] = nf + inc_n - n;
                 lbase[t] = nf * kPiece + inc_e - n * t;
             }
-            if (ln == 63) items[item].w = nf + inc_n;
+            if (ln == 63) items[item].w = (nf + inc_n) | ((nf >> 6) << 16);
         }
         __syncthreads();
         // Tail slots come from LDS cursors; the waves take them in a fixed turn (a barrier between turns), so
