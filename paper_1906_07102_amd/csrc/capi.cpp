@@ -41,7 +41,7 @@ struct lmg_plan {
     int npatch = 1;             // LDS patches per gridding workgroup
     int waves = 0;              // waves per gridding workgroup
     int nchan = 1;              // channels (grids), each with its own run of visibilities
-    int nblocks = 0;            // plan blocks (runs of <= kPlanBlockVis visibilities of one channel)
+    int nblocks = 0;            // plan blocks (runs of <= plan_block_vis() visibilities of one channel)
     mutable bool bad_data = false;
     // Occupied band of the grid (storage rows / columns [lo, hi)) and the
     // window of tiles that covers it (first tile, number of tiles).
@@ -169,7 +169,10 @@ struct Layout {
 };
 
 // Most plan blocks for nvis visibilities over nchan channels.
-int64_t max_plan_blocks(int64_t nvis, int nchan) { return plan_blocks(nvis) + nchan; }
+int64_t max_plan_blocks(int N, int64_t nvis, int nchan) {
+    const int v = plan_block_vis(N, nvis);
+    return (nvis + v - 1) / v + nchan;
+}
 
 // Tile arrays are sized for the smallest tile any plan may pick (N / T <= 128,
 // T >= 8), so the size query need not know the table.
@@ -178,7 +181,7 @@ Layout plan_layout(int N, int64_t nvis, lmg_precision prec, int cap, int nchan =
     const int64_t ntiles = std::min<int64_t>(16384, static_cast<int64_t>(N / 8) * (N / 8));
     const int64_t tot = ntiles * nchan;
     L.max_items = static_cast<int>(std::min<int64_t>(tot, nvis) + (nvis + cap - 1) / cap + 1);
-    L.max_blocks = static_cast<int>(max_plan_blocks(nvis, nchan));
+    L.max_blocks = static_cast<int>(max_plan_blocks(N, nvis, nchan));
     size_t o = 0;
     auto take = [&o](size_t bytes) { const size_t at = o; o = align_up(o + bytes); return at; };
     L.flags = take(16 * sizeof(int));
@@ -625,14 +628,15 @@ lmg_status create_plan(const lmg_table* table, int N, lmg_precision prec, int nc
     p->twiddle = base + L.twiddle;
     p->hpix = base + L.hpix;
 
-    // Plan blocks: runs of at most kPlanBlockVis visibilities of one channel.
+    // Plan blocks: runs of at most plan_block_vis() visibilities of one channel.
+    const int block_vis = plan_block_vis(N, nvis);
     std::vector<int4> blocks;
     std::vector<int> chan_blocks(static_cast<size_t>(nchan) + 1);
     for (int c = 0; c < nchan; ++c) {
         chan_blocks[c] = static_cast<int>(blocks.size());
-        for (int64_t a = offsets[c]; a < offsets[c + 1]; a += kPlanBlockVis)
+        for (int64_t a = offsets[c]; a < offsets[c + 1]; a += block_vis)
             blocks.push_back(make_int4(c, static_cast<int>(a),
-                                       static_cast<int>(std::min<int64_t>(kPlanBlockVis, offsets[c + 1] - a)), 0));
+                                       static_cast<int>(std::min<int64_t>(block_vis, offsets[c + 1] - a)), 0));
     }
     chan_blocks[nchan] = static_cast<int>(blocks.size());
     p->nblocks = static_cast<int>(blocks.size());

@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 
 #include "lmg_internal.h"
@@ -10,11 +11,18 @@
 namespace lmg {
 
 // The plan's streaming passes over the visibilities: blocks of kPlanThreads
-// threads, each handling a run of at most kPlanBlockVis consecutive
+// threads, each handling a run of at most plan_block_vis() consecutive
 // visibilities of one channel.
 constexpr int kPlanThreads = 1024;
 constexpr int kPlanBlockVis = 65536;
-inline int plan_blocks(int64_t nvis) { return static_cast<int>((nvis + kPlanBlockVis - 1) / kPlanBlockVis); }
+// A block per compute unit while blocks hold at least 1,024 visibilities (2,048 where a block's tile histogram may
+// have 16,384 entries, which it zeroes and writes), at most kPlanBlockVis: the passes take a block's time as long as
+// the blocks fit the chip at once.
+inline int plan_block_vis(int N, int64_t nvis) {
+    const int64_t least = N >= 4096 ? 2048 : 1024;
+    const int64_t v = (std::max(least, (nvis + 255) / 256) + 1023) / 1024 * 1024;
+    return static_cast<int>(std::min<int64_t>(v, kPlanBlockVis));
+}
 // Longest run of one footprint cell handled by one lane (a "piece").
 constexpr int kPiece = 32;
 // Elements of padding after the entry-order arrays the item kernels read in runs.

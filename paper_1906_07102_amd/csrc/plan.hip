@@ -11,7 +11,7 @@ namespace dev {
 __device__ int g_data_error;
 
 // Pass 1: count visibilities per tile, per plan block (a run of at most
-// kPlanBlockVis visibilities of one channel, kept per block so that pass 3
+// plan_block_vis() visibilities of one channel, kept per block so that pass 3
 // can place each block's visibilities of a tile in one contiguous run). The
 // slot after the tiles counts visibilities whose coordinates are not finite
 // (they are dropped). blocks[b] = (channel, first visibility, count, 0).
@@ -285,9 +285,10 @@ __global__ __launch_bounds__(1024) void k_plan_scan(PlanGeom g, const int* __res
 // its own (k_plan_place): here each XCD runs 32 plan blocks, that is 32
 // time windows, at once, and their partly written lines would overflow L2.
 // Positions are ranks taken from the block's LDS cursors. The waves of the
-// workgroup take them in a fixed turn (wave 0 first, a barrier between
-// turns), so that the order within a tile's run, and with it every later
-// summation order, is the same on every run.
+// workgroup hold consecutive runs of the caller order and take their ranks in
+// a fixed turn (wave 0 first, a barrier between turns), so that a tile's
+// visibilities stay in the caller's order: every later summation order is the
+// same on every run and for every size of block.
 template <typename R>
 __global__ __launch_bounds__(kPlanThreads) void k_plan_scatter(const double2* __restrict__ uv,
                                                                const int4* __restrict__ blocks, int nb, PlanGeom g,
@@ -306,20 +307,23 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_scatter(const double2* __
     __syncthreads();
     const int wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
     const int64_t base = bd.y, end = static_cast<int64_t>(bd.y) + bd.z;
-    constexpr int kB = 8;                                    // coordinates loaded together per thread
-    for (int i0 = 0; i0 < bd.z; i0 += kB * kPlanThreads) {  // uniform across the workgroup
+    constexpr int kB = 8;                                    // most coordinates loaded together per thread
+    const int kb_run = min(kB, (bd.z + kPlanThreads - 1) / kPlanThreads);     // coordinates per thread and step
+    const int first = wave * 64 * kb_run + (threadIdx.x & 63);
+    for (int i0 = 0; i0 < bd.z; i0 += kb_run * kPlanThreads) {  // uniform across the workgroup
         double2 c[kB];
+        const int64_t k0 = base + i0 + first;                // this thread's coordinates: k0 + 64 u, u < kb_run
 #pragma unroll
         for (int u = 0; u < kB; ++u) {
-            const int64_t k = base + i0 + u * kPlanThreads + threadIdx.x;
-            if (k < end) c[u] = nt_load(uv + k);     // the coordinates' last read
+            const int64_t k = k0 + u * 64;
+            if (u < kb_run && k < end) c[u] = nt_load(uv + k);     // the coordinates' last read
         }
-        int key[kB];                                         // tile slot (ntiles: dropped), -1 past the block
+        int key[kB];                                         // tile slot (ntiles: dropped), -1 past the run
 #pragma unroll
         for (int u = 0; u < kB; ++u) {
-            const int64_t k = base + i0 + u * kPlanThreads + threadIdx.x;
+            const int64_t k = k0 + u * 64;
             key[u] = -1;
-            if (k >= end) continue;
+            if (u >= kb_run || k >= end) continue;
             int cu, cv;
             double du, dv;
             if (tap_geometry(c[u].x, g.W, g.ref, g.N, &cu, &du) && tap_geometry(c[u].y, g.W, g.ref, g.N, &cv, &dv)) {
@@ -342,10 +346,8 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_scatter(const double2* __
             __syncthreads();
         }
 #pragma unroll
-        for (int u = 0; u < kB; ++u) {
-            const int64_t k = base + i0 + u * kPlanThreads + threadIdx.x;
-            if (key[u] >= 0) inv0[k] = dst[u];
-        }
+        for (int u = 0; u < kB; ++u)
+            if (key[u] >= 0) inv0[k0 + u * 64] = dst[u];
     }
 }
 
