@@ -53,8 +53,8 @@ def algorithmic_bytes(name: str, nvis: int, N: int, M: int, cs: int) -> float:
         "grid_items": (16.0 + cs + 4.0) * nvis,
         "assemble": float(N) * N * cs,
         "degrid_items": (16.0 + cs) * nvis + float(N) * N * cs,
-        "fft_rows_inverse": float(N) * N * cs + float(M) * N * cs,
-        "fft_cols_inverse_correct_crop": float(M) * N * cs + float(M) * M * cs + 0 * rs,
+        "fft_cols_inverse": float(N) * N * cs + float(M) * N * cs,
+        "fft_rows_inverse_correct_crop": float(M) * N * cs + float(M) * M * cs + 0 * rs,
         "fft_rows_forward_correct_pad": float(M) * M * cs + float(N) * M * cs,
         "fft_cols_forward": float(N) * M * cs + float(N) * N * cs,
     }.get(name, 0.0)

@@ -215,7 +215,7 @@ Scratch scratch_layout(int N, int W, int T, int M, int items, int64_t nvis, lmg_
     const size_t P = static_cast<size_t>(T + W - 1);
     const size_t patches = align_up(static_cast<size_t>(items) * P * P * patch_cell_size(prec));
     const size_t grid = align_up(static_cast<size_t>(N) * N * cplx_size(prec));
-    const size_t tmp = align_up(static_cast<size_t>(M) * N * cplx_size(prec));
+    const size_t tmp = align_up(static_cast<size_t>((M + 3) / 4 * 4) * N * cplx_size(prec));     // blocks of four rows
     const size_t vs = align_up(static_cast<size_t>(nvis + kRunPad) * cplx_size(prec));
     Scratch s{};
     size_t o = align_up(kCounters * sizeof(int));
@@ -247,16 +247,24 @@ std::map<int, std::vector<double>>& twiddle_cache() {
     static std::map<int, std::vector<double>> c;
     return c;
 }
+// N complex values (cos, -sin): the twiddles of the transform's stages after the first, in the order the stages read
+// them. A stage of radix RAD after Ns = 8, 64, ... combined points holds e^{-2 pi i r k / (RAD Ns)} at Ns - 8 +
+// (r - 1) Ns + k for r = 1 .. RAD - 1, k < Ns.
 const std::vector<double>& twiddles_f64(int N) {
     std::lock_guard<std::mutex> lk(g_cache_mu);
     auto& c = twiddle_cache();
     auto it = c.find(N);
     if (it != c.end()) return it->second;
-    std::vector<double> tw(2 * static_cast<size_t>(N));
-    for (int t = 0; t < N; ++t) {
-        const double a = 2.0 * 3.14159265358979323846 * (static_cast<double>(t) / N);
-        tw[2 * t] = std::cos(a);
-        tw[2 * t + 1] = -std::sin(a);
+    std::vector<double> tw(2 * static_cast<size_t>(N), 0.0);
+    for (int Ns = 8; Ns < N; Ns *= 8) {
+        const int rad = std::min(8, N / Ns);
+        for (int r = 1; r < rad; ++r)
+            for (int k = 0; k < Ns; ++k) {
+                const double a = 2.0 * 3.14159265358979323846 * (static_cast<double>(r * k) / (rad * Ns));
+                const size_t at = static_cast<size_t>(Ns) - 8 + static_cast<size_t>(r - 1) * Ns + k;
+                tw[2 * at] = std::cos(a);
+                tw[2 * at + 1] = -std::sin(a);
+            }
     }
     return c.emplace(N, std::move(tw)).first->second;
 }
@@ -481,17 +489,19 @@ lmg_status run_grid_entries(const lmg_plan* p, const void* vs, void* grid, void*
     a.n_items = p->flags + 1; a.max_items = p->max_items; a.npatch = p->npatch; a.waves = p->waves; a.Ft = p->Ft; a.kb = p->kb;
     a.items = p->items; a.pieces = p->pieces; a.off = p->off; a.coef = p->coef;
     a.vis = vs; a.patches = patches; a.counter = counters;
+    a.transpose = band_only ? 1 : 0;
     {
         TraceScope ts("grid_items", s);
         LMG_HIP(launch_grid(p->prec, a, s));
     }
     AssembleArgs b{};
+    b.transpose = a.transpose;
     b.N = p->g.N; b.W = p->g.W; b.T = p->g.T; b.ntx = p->g.ntx; b.nchan = p->nchan;
     b.accumulate = accumulate ? 1 : 0;
-    if (band_only) {                  // an internal grid: only the occupied window is ever read
+    if (band_only) {                  // an internal grid, stored transposed: only the occupied window is ever read
         const lmg_status st = ensure_flags(p);     // the grid kernels are already queued
         if (st != LMG_OK) return st;
-        b.tr0 = p->win_r0; b.trows = p->win_rn; b.tc0 = p->win_c0; b.tcols = p->win_cn;
+        b.tr0 = p->win_c0; b.trows = p->win_cn; b.tc0 = p->win_r0; b.tcols = p->win_rn;    // rows along u
     } else {
         b.tr0 = 0; b.trows = p->g.ntx; b.tc0 = 0; b.tcols = p->g.ntx;
     }
@@ -513,7 +523,8 @@ lmg_status run_grid(const lmg_plan* p, const void* vis, const float* w, void* gr
 }
 
 // Degridding into entry order.
-lmg_status run_degrid_entries(const lmg_plan* p, const void* grid, void* vs, int* counters, hipStream_t s) {
+lmg_status run_degrid_entries(const lmg_plan* p, const void* grid, bool transposed, void* vs, int* counters,
+                              hipStream_t s) {
     const lmg_table* t = p->table;
     if (wait_plan(p, s) != LMG_OK) return LMG_EHIP;
     LMG_HIP(launch_zero_ints(counters + 1, 1, s));
@@ -522,15 +533,16 @@ lmg_status run_degrid_entries(const lmg_plan* p, const void* grid, void* vs, int
     a.tab_global = table_global(t, p->prec) ? 1 : 0;
     a.n_items = p->flags + 1; a.max_items = p->max_items; a.Ft = p->Ft; a.kb = p->kb;
     a.items = p->items; a.pieces = p->pieces; a.off = p->off; a.coef = p->coef;
-    a.grid = grid; a.vis_out = vs; a.counter = counters + 1;
+    a.grid = grid; a.transpose = transposed ? 1 : 0; a.vis_out = vs; a.counter = counters + 1;
     TraceScope ts("degrid_items", s);
     LMG_HIP(launch_degrid(p->prec, a, s));
     return LMG_OK;
 }
 
 // Degridding, then entry order -> caller order.
-lmg_status run_degrid(const lmg_plan* p, const void* grid, void* vis_out, void* vs, int* counters, hipStream_t s) {
-    const lmg_status st = run_degrid_entries(p, grid, vs, counters, s);
+lmg_status run_degrid(const lmg_plan* p, const void* grid, bool transposed, void* vis_out, void* vs, int* counters,
+                      hipStream_t s) {
+    const lmg_status st = run_degrid_entries(p, grid, transposed, vs, counters, s);
     if (st != LMG_OK) return st;
     TraceScope ts("permute_out", s);
     LMG_HIP(launch_permute_out(p->prec == LMG_F64, vs, p->inv, p->nvis, vis_out, s));
@@ -822,7 +834,7 @@ lmg_status lmg_degrid_planned(const lmg_plan* p, const void* grid, void* vis_out
     if (!scratch_ok(p, LMG_OP_DEGRID, scratch, scratch_bytes)) return LMG_EWORKSPACE;
     const Scratch L = plan_scratch(p, LMG_OP_DEGRID);
     char* sc = static_cast<char*>(scratch);
-    return run_degrid(p, grid, vis_out, sc + L.vs, reinterpret_cast<int*>(sc + L.counters),
+    return run_degrid(p, grid, false, vis_out, sc + L.vs, reinterpret_cast<int*>(sc + L.counters),
                       static_cast<hipStream_t>(stream));
 }
 
@@ -866,7 +878,7 @@ lmg_status lmg_degrid_planned_ordered(const lmg_plan* p, const void* grid, void*
     if (!scratch_ok(p, LMG_OP_DEGRID, scratch, scratch_bytes)) return LMG_EWORKSPACE;
     const Scratch L = plan_scratch(p, LMG_OP_DEGRID);
     char* sc = static_cast<char*>(scratch);
-    return run_degrid_entries(p, grid, vis_plan_out, reinterpret_cast<int*>(sc + L.counters),
+    return run_degrid_entries(p, grid, false, vis_plan_out, reinterpret_cast<int*>(sc + L.counters),
                               static_cast<hipStream_t>(stream));
 }
 
@@ -891,25 +903,24 @@ lmg_status lmg_make_dirty_image_planned(const lmg_plan* p, const void* vis, cons
         LMG_HIP(launch_zero_ints(static_cast<int*>(image), static_cast<int>(static_cast<size_t>(M) * M * cs / 4), s));
         return LMG_OK;
     }
-    // Rows m of the occupied band: transform over n (only the occupied columns are non-zero), keep the
-    // central M outputs, write transposed (tmp is M x N; only columns r0 .. r0 + nr are written).
+    // The grid is stored transposed (rows n). Rows n of the occupied band: transform over m (only the occupied rows m
+    // are non-zero), keep the central M outputs, write transposed (tmp is M x N, blocked; only columns c0 .. c0 + nc
+    // are written).
     FftArgs a = fft_args(N, +1, p->twiddle);
-    a.nrows = nr; a.src = static_cast<char*>(grid) + (static_cast<size_t>(r0) * N + c0) * cs; a.src_pitch = N;
-    a.in_count = nc; a.in_pos = c0;
-    a.dst = static_cast<char*>(tmp) + static_cast<size_t>(r0) * cs; a.dst_pitch = N; a.out_count = M;
-    a.out_pos = N / 2 - M / 2;
+    a.nrows = nc; a.src = static_cast<char*>(grid) + (static_cast<size_t>(c0) * N + r0) * cs; a.src_pitch = N;
+    a.in_count = nr; a.in_pos = r0;
+    a.dst = tmp; a.dst_pitch = N; a.dst_blocked = 1; a.dst_col = c0; a.out_count = M; a.out_pos = N / 2 - M / 2;
     {
-        TraceScope ts("fft_rows_inverse", s);
+        TraceScope ts("fft_cols_inverse", s);
         LMG_HIP(launch_fft_pass(f64, a, s));
     }
-    // Rows p of tmp: transform over m (zero outside the band), keep the central M outputs, apply
+    // Rows q of tmp: transform over n (zero outside the band), keep the central M outputs, apply
     // h(x_p) h(y_q), write image[q][p].
     FftArgs b = fft_args(N, +1, p->twiddle);
-    b.nrows = M; b.src = static_cast<char*>(tmp) + static_cast<size_t>(r0) * cs; b.src_pitch = N;
-    b.in_count = nr; b.in_pos = r0;
-    b.dst = image; b.dst_pitch = M; b.out_count = M; b.out_pos = N / 2 - M / 2;
+    b.nrows = M; b.src = tmp; b.src_pitch = N; b.src_blocked = 1; b.src_col = c0; b.in_count = nc; b.in_pos = c0;
+    b.dst = image; b.dst_pitch = M; b.out_count = M; b.out_pos = N / 2 - M / 2; b.straight = 1;
     b.h_out = p->hpix; b.h_row = p->hpix; b.row_off = N / 2 - M / 2;
-    TraceScope ts("fft_cols_inverse_correct_crop", s);
+    TraceScope ts("fft_rows_inverse_correct_crop", s);
     LMG_HIP(launch_fft_pass(f64, b, s));
     return LMG_OK;
 }
@@ -938,23 +949,24 @@ lmg_status lmg_predict_visibilities_planned(const lmg_plan* p, const void* image
         // the occupied column band, write transposed (tmp: nc rows n, M columns q).
         FftArgs a = fft_args(N, -1, p->twiddle);
         a.nrows = M; a.src = image; a.src_pitch = M; a.in_count = M; a.in_pos = N / 2 - M / 2;
-        a.dst = tmp; a.dst_pitch = M; a.out_count = nc; a.out_pos = c0;
+        a.dst = tmp; a.dst_pitch = M; a.dst_blocked = 1; a.out_count = nc; a.out_pos = c0;
         a.h_in = p->hpix; a.h_row = p->hpix; a.row_off = N / 2 - M / 2;
         {
             TraceScope ts("fft_rows_forward_correct_pad", s);
             LMG_HIP(launch_fft_pass(f64, a, s));
         }
-        // Rows n of tmp: zero-pad to N, transform over q, write the occupied band of grid rows m.
+        // Rows n of tmp: zero-pad to N, transform over q, write the occupied band of the grid, stored transposed
+        // (rows n).
         FftArgs b = fft_args(N, -1, p->twiddle);
-        b.nrows = nc; b.src = tmp; b.src_pitch = M; b.in_count = M; b.in_pos = N / 2 - M / 2;
-        b.dst = static_cast<char*>(grid) + (static_cast<size_t>(r0) * N + c0) * cs; b.dst_pitch = N;
+        b.nrows = nc; b.src = tmp; b.src_pitch = M; b.src_blocked = 1; b.in_count = M; b.in_pos = N / 2 - M / 2;
+        b.dst = static_cast<char*>(grid) + (static_cast<size_t>(c0) * N + r0) * cs; b.dst_pitch = N; b.straight = 1;
         b.out_count = nr; b.out_pos = r0;
         {
             TraceScope ts("fft_cols_forward", s);
             LMG_HIP(launch_fft_pass(f64, b, s));
         }
     }
-    return run_degrid(p, grid, vis_out, sc + L.vs, reinterpret_cast<int*>(sc + L.counters), s);
+    return run_degrid(p, grid, true, vis_out, sc + L.vs, reinterpret_cast<int*>(sc + L.counters), s);
 }
 
 lmg_status lmg_workspace_size(int N, int W, double x0, int64_t nvis, lmg_precision prec, int op, size_t* bytes) {
@@ -1089,10 +1101,10 @@ lmg_status lmg_fft2_centred(int N, lmg_precision prec, int sign, void* data, voi
     }
     FftArgs a = fft_args(N, sign, tw);
     a.nrows = N; a.src = data; a.src_pitch = N; a.in_count = N; a.in_pos = 0;
-    a.dst = scratch; a.dst_pitch = N; a.out_count = N; a.out_pos = 0;
+    a.dst = scratch; a.dst_pitch = N; a.dst_blocked = 1; a.out_count = N; a.out_pos = 0;
     LMG_HIP(launch_fft_pass(f64, a, s));
     FftArgs b = a;
-    b.src = scratch; b.dst = data;
+    b.src = scratch; b.src_blocked = 1; b.dst = data; b.dst_blocked = 0;
     LMG_HIP(launch_fft_pass(f64, b, s));
     return LMG_OK;
 }

@@ -47,8 +47,9 @@ __global__ __launch_bounds__(kDegridThreads) void k_degrid_items(DegridArgs a) {
         const VT* grid = reinterpret_cast<const VT*>(a.grid) + static_cast<size_t>(chan) * a.N * a.N;
         for (int i = threadIdx.x; i < P * P; i += blockDim.x) {
             const int r = i / P, c = i - (i / P) * P;
-            const int gr = (tm * a.T + r) & (a.N - 1), gc = (tn * a.T + c) & (a.N - 1);
-            patch[i] = grid[static_cast<size_t>(gr) * a.N + gc];
+            // r, c: the grid's storage order; the patch's rows follow v
+            const int gr = ((a.transpose ? tn : tm) * a.T + r) & (a.N - 1), gc = ((a.transpose ? tm : tn) * a.T + c) & (a.N - 1);
+            patch[a.transpose ? c * P + r : i] = grid[static_cast<size_t>(gr) * a.N + gc];
         }
         __syncthreads();
         for (int e = it.y + threadIdx.x; e < it.y + it.z; e += blockDim.x) {

@@ -335,8 +335,9 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<Acc, W, kTab>()))) void k_grid
         __syncthreads();
         Cell* out = reinterpret_cast<Cell*>(a.patches) + static_cast<size_t>(item) * P2;
         for (int i = threadIdx.x; i < P2; i += blockDim.x) {
+            const int from = a.transpose ? (i % P) * P + i / P : i;
             typename Acc::Sum sum;
-            for (int w = 0; w < S; ++w) sum.add(patches[w * P2 + i]);
+            for (int w = 0; w < S; ++w) sum.add(patches[w * P2 + from]);
             out[i] = sum.cell();
         }
         __syncthreads();                                    // the patches, s_item and s_turn are reused
@@ -364,18 +365,18 @@ __global__ __launch_bounds__(kAssembleThreads) void k_assemble(AssembleArgs a) {
     const int tm = (a.tr0 + wt / a.tcols) % a.ntx, tn = (a.tc0 + wt % a.tcols) % a.ntx;
     const int ntiles = a.ntx * a.ntx;
     const int cbase = chan * ntiles;                        // global tiles of this channel
-    const int t = cbase + tm * a.ntx + tn;
+    // a transposed grid's tile rows run along u, while tiles are numbered along v
+    auto tile = [&](int r, int c) { return cbase + (a.transpose ? c * a.ntx + r : r * a.ntx + c); };
+    const int tmu = (tm + a.ntx - 1) % a.ntx, tnl = (tn + a.ntx - 1) % a.ntx;
     const int P = a.T + a.W - 1;
     const int halo = a.W - 1;
     const Cell* patches = reinterpret_cast<const Cell*>(a.patches);
     VT* grid = reinterpret_cast<VT*>(a.grid) + static_cast<size_t>(chan) * a.N * a.N;
     int src_t[4], src_dr[4], src_dc[4];
-    src_t[0] = t;                                                                src_dr[0] = 0;   src_dc[0] = 0;
-    src_t[1] = cbase + tm * a.ntx + (tn + a.ntx - 1) % a.ntx;                    src_dr[1] = 0;   src_dc[1] = a.T;
-    src_t[2] = cbase + ((tm + a.ntx - 1) % a.ntx) * a.ntx + tn;                  src_dr[2] = a.T; src_dc[2] = 0;
-    src_t[3] = cbase + ((tm + a.ntx - 1) % a.ntx) * a.ntx + (tn + a.ntx - 1) % a.ntx;
-    src_dr[3] = a.T;
-    src_dc[3] = a.T;
+    src_t[0] = tile(tm, tn);   src_dr[0] = 0;   src_dc[0] = 0;
+    src_t[1] = tile(tm, tnl);  src_dr[1] = 0;   src_dc[1] = a.T;
+    src_t[2] = tile(tmu, tn);  src_dr[2] = a.T; src_dc[2] = 0;
+    src_t[3] = tile(tmu, tnl); src_dr[3] = a.T; src_dc[3] = a.T;
     int i0[4], i1[4];
     bool any = false;
     for (int s = 0; s < 4; ++s) {

@@ -61,6 +61,7 @@ struct GridArgs {
     const void* coef;      // coefficient table, float or double; FP64 expansion for a direct table
     const void* vis;       // complex, entry order, weights applied
     void* patches;         // n_items patches of (T + W - 1)^2 cells
+    int transpose;         // 1: patches are written transposed (a grid stored with rows along u)
     int* counter;          // work-item counter, zero at launch
 };
 
@@ -73,6 +74,7 @@ struct AssembleArgs {
     int tr0, tc0, trows, tcols;   // window of tiles written (rows tr0.., columns tc0.., wrapping)
     int rows;                     // tile rows per workgroup (set by the launcher)
     int rows_kernel;              // 1: whole grids by runs of rows (k_assemble_rows; set by the launcher)
+    int transpose;                // 1: patches and grid are transposed (grid rows along u, tiles' rows along u)
     int accumulate;               // 1: add to the grid's values; 0: overwrite every cell of the window
     const int* item_start;   // per tile, ntiles + 1
     const void* patches;
@@ -90,6 +92,7 @@ struct DegridArgs {
     const void* off;
     const void* coef;
     const void* grid;      // nchan grids of N x N
+    int transpose;         // 1: the grid is stored transposed (rows along u)
     void* vis_out;         // entry order
     int* counter;          // work-item counter, zero at launch
 };
@@ -103,8 +106,12 @@ struct FftArgs {
     int in_count, in_pos;  // loaded values and their first FFT position
     void* dst;
     int dst_pitch;         // elements between destination rows
+    // The intermediate of two passes, written transposed by the first and read by rows by the second, may be blocked
+    // (see k_fft_pass): columns src_col / dst_col on of rows of src_pitch / dst_pitch elements, multiples of two.
+    int src_blocked, src_col, dst_blocked, dst_col;
+    int straight;          // 1: a source row's outputs go to one destination row; 0: transposed
     int out_count, out_pos;
-    const void* twiddle;   // N complex values e^{-2 pi i t / N}
+    const void* twiddle;   // N complex values: the stages' twiddles, in the order the stages read them
     const void* h_in;      // per input position, or nullptr
     const void* h_out;     // per output position, or nullptr
     const void* h_row;     // per source row (index row + row_off), or nullptr
