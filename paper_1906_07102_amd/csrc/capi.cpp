@@ -630,6 +630,8 @@ lmg_status create_plan(const lmg_table* table, int N, lmg_precision prec, int nc
     p->pieces = reinterpret_cast<int2*>(base + L.pieces);
     p->lb = 0;
     while ((1 << p->lb) < T) ++p->lb;
+    p->g.lb = p->lb;
+    while ((1 << p->g.lbx) < p->g.ntx) ++p->g.lbx;
     // Packed offsets hold the interval index in kb <= 24 bits over Ft >= 2 fraction bits.
     p->ms_enc = table->direct ? 1 : table->Ms;
     p->kb = 0;

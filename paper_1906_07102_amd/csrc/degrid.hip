@@ -29,24 +29,26 @@ __global__ __launch_bounds__(kDegridThreads) void k_degrid_items(DegridArgs a) {
     const int ntab = kTab == kTabLds ? (a.Ms + 1) * W * 4 : 0;
     VT* patch = reinterpret_cast<VT*>(smem + ((ntab * sizeof(R) + 15) & ~size_t(15)));
     const int P = a.T + W - 1;
-    const int ntiles = a.ntx * a.ntx;
+    const unsigned inv_p = 0xffffffffu / P + 1;      // i / P = umulhi(i, inv_p) for i < P P
+    const int lbx = __builtin_ctz(static_cast<unsigned>(a.ntx));     // tiles per axis are a power of two
     const R* gtab = reinterpret_cast<const R*>(a.coef);
     for (int i = threadIdx.x; i < ntab; i += blockDim.x) tab[i] = gtab[i];
     VT* out = reinterpret_cast<VT*>(a.vis_out);     // entry order
     const PT2* off = reinterpret_cast<const PT2*>(a.off);
     const int cshift = a.Ft + a.kb;
     const int nitems = *a.n_items;
-    for (;;) {
-        if (threadIdx.x == 0) s_item = atomicAdd(a.counter, 1);
+    for (bool first = true;; first = false) {
+        // the first items are dealt by workgroup, the others from the counter
+        if (threadIdx.x == 0) s_item = first ? blockIdx.x : gridDim.x + atomicAdd(a.counter, 1);
         __syncthreads();
         const int item = s_item;
         if (item >= nitems) break;                   // uniform across the workgroup
         const int4 it = a.items[item];
-        const int chan = it.x / ntiles, lt = it.x % ntiles;
-        const int tm = lt / a.ntx, tn = lt % a.ntx;
+        const int chan = it.x >> (2 * lbx), lt = it.x & (a.ntx * a.ntx - 1);
+        const int tm = lt >> lbx, tn = lt & (a.ntx - 1);
         const VT* grid = reinterpret_cast<const VT*>(a.grid) + static_cast<size_t>(chan) * a.N * a.N;
         for (int i = threadIdx.x; i < P * P; i += blockDim.x) {
-            const int r = i / P, c = i - (i / P) * P;
+            const int r = __umulhi(static_cast<unsigned>(i), inv_p), c = i - r * P;
             // r, c: the grid's storage order; the patch's rows follow v
             const int gr = ((a.transpose ? tn : tm) * a.T + r) & (a.N - 1), gc = ((a.transpose ? tm : tn) * a.T + c) & (a.N - 1);
             patch[a.transpose ? c * P + r : i] = grid[static_cast<size_t>(gr) * a.N + gc];

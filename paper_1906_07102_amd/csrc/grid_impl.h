@@ -240,6 +240,7 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<Acc, W, kTab>()))) void k_grid
     constexpr int NPASS = RowGroup<Acc, W>::kPasses;
     const int P = a.T + W - 1;
     const int P2 = P * P;
+    const unsigned inv_p = 0xffffffffu / P + 1;             // i / P = umulhi(i, inv_p) for i < P2
     R* tab = reinterpret_cast<R*>(smem);
     const int ntab = kTab == kTabLds ? (a.Ms + 1) * W * 4 : 0;
     Cell* patches = reinterpret_cast<Cell*>(smem + ((ntab * sizeof(R) + 15) & ~size_t(15)));
@@ -254,8 +255,9 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<Acc, W, kTab>()))) void k_grid
     const VT* vis = reinterpret_cast<const VT*>(a.vis);     // entry order, weights applied
     const PT2* off = reinterpret_cast<const PT2*>(a.off);   // packed offsets, entry order
     const int nitems = *a.n_items;
-    for (;;) {
-        if (threadIdx.x == 0) s_item = atomicAdd(a.counter, 1);
+    for (bool first = true;; first = false) {
+        // the first items are dealt by workgroup, the others from the counter
+        if (threadIdx.x == 0) s_item = first ? blockIdx.x : gridDim.x + atomicAdd(a.counter, 1);
         if (threadIdx.x < S) s_turn[threadIdx.x] = 0;
         for (int i = threadIdx.x; i < S * P2; i += blockDim.x) Acc::zero_cell(&patches[i]);
         __syncthreads();
@@ -335,7 +337,8 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<Acc, W, kTab>()))) void k_grid
         __syncthreads();
         Cell* out = reinterpret_cast<Cell*>(a.patches) + static_cast<size_t>(item) * P2;
         for (int i = threadIdx.x; i < P2; i += blockDim.x) {
-            const int from = a.transpose ? (i % P) * P + i / P : i;
+            const int row = __umulhi(static_cast<unsigned>(i), inv_p);
+            const int from = a.transpose ? (i - row * P) * P + row : i;
             typename Acc::Sum sum;
             for (int w = 0; w < S; ++w) sum.add(patches[w * P2 + from]);
             out[i] = sum.cell();
@@ -362,12 +365,13 @@ __global__ __launch_bounds__(kAssembleThreads) void k_assemble(AssembleArgs a) {
     const int chan = blockIdx.x / (nblk * per_chan);
     const int wt = (blockIdx.x / nblk) % per_chan;          // tile within the written window
     const int rb = (blockIdx.x % nblk) * ar;
-    const int tm = (a.tr0 + wt / a.tcols) % a.ntx, tn = (a.tc0 + wt % a.tcols) % a.ntx;
+    const int tm = (a.tr0 + wt / a.tcols) & (a.ntx - 1), tn = (a.tc0 + wt % a.tcols) & (a.ntx - 1);
     const int ntiles = a.ntx * a.ntx;
     const int cbase = chan * ntiles;                        // global tiles of this channel
     // a transposed grid's tile rows run along u, while tiles are numbered along v
     auto tile = [&](int r, int c) { return cbase + (a.transpose ? c * a.ntx + r : r * a.ntx + c); };
-    const int tmu = (tm + a.ntx - 1) % a.ntx, tnl = (tn + a.ntx - 1) % a.ntx;
+    const int tmu = (tm - 1) & (a.ntx - 1), tnl = (tn - 1) & (a.ntx - 1);     // ntx is a power of two, as T is
+    const int lbT = __builtin_ctz(static_cast<unsigned>(a.T));
     const int P = a.T + a.W - 1;
     const int halo = a.W - 1;
     const Cell* patches = reinterpret_cast<const Cell*>(a.patches);
@@ -387,7 +391,7 @@ __global__ __launch_bounds__(kAssembleThreads) void k_assemble(AssembleArgs a) {
     if (a.accumulate && !any) return;                       // uniform across the workgroup
     if (!any) {                                             // no patch: zeros, two cells per store
         for (int pair = threadIdx.x; pair < ar * a.T / 2; pair += blockDim.x) {
-            const int lr = rb + (2 * pair) / a.T, lc = (2 * pair) % a.T;
+            const int lr = rb + ((2 * pair) >> lbT), lc = (2 * pair) & (a.T - 1);
             VT* dst = grid + static_cast<size_t>(tm * a.T + lr) * a.N + tn * a.T + lc;
             VT z[2];
             z[0].x = 0; z[0].y = 0; z[1] = z[0];
@@ -396,7 +400,7 @@ __global__ __launch_bounds__(kAssembleThreads) void k_assemble(AssembleArgs a) {
         return;
     }
     for (int cell = threadIdx.x; cell < ar * a.T; cell += blockDim.x) {
-        const int lr = rb + cell / a.T, lc = cell % a.T;
+        const int lr = rb + (cell >> lbT), lc = cell & (a.T - 1);
         typename Acc::Sum sum;
         for (int s = 0; s < 4; ++s) {
             if ((s == 1 && lc >= halo) || (s == 2 && lr >= halo) || (s == 3 && (lr >= halo || lc >= halo))) continue;
@@ -433,7 +437,7 @@ __global__ __launch_bounds__(kAssembleThreads) void k_assemble_rows(AssembleArgs
     const int tm = r0 / a.T, rb = r0 % a.T;
     const int ntiles = a.ntx * a.ntx;
     const int cbase = chan * ntiles;
-    const int tmu = (tm + a.ntx - 1) % a.ntx;
+    const int tmu = (tm - 1) & (a.ntx - 1);
     for (int i = threadIdx.x; i <= a.ntx; i += blockDim.x) {
         rng[i] = a.item_start[cbase + tm * a.ntx + i];
         rng[a.ntx + 1 + i] = a.item_start[cbase + tmu * a.ntx + i];
@@ -448,7 +452,7 @@ __global__ __launch_bounds__(kAssembleThreads) void k_assemble_rows(AssembleArgs
     const Cell* patches = reinterpret_cast<const Cell*>(a.patches);
     VT* grid = reinterpret_cast<VT*>(a.grid) + static_cast<size_t>(chan) * a.N * a.N + static_cast<size_t>(r0) * a.N;
     for (int tn = 0; tn < a.ntx; ++tn) {                   // uniform across the workgroup
-        const int tl = (tn + a.ntx - 1) % a.ntx;
+        const int tl = (tn - 1) & (a.ntx - 1);
         int i0[4], i1[4];
         i0[0] = own[tn]; i1[0] = own[tn + 1];              // own tile, left, upper, upper-left
         i0[1] = own[tl]; i1[1] = own[tl + 1];

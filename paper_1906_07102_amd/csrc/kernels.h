@@ -36,6 +36,7 @@ struct PlanGeom {
     int T;        // tile edge (cells)
     int ntx;      // tiles per axis, N / T
     int ntiles;   // ntx * ntx, per channel
+    int lb, lbx;  // log2 of T and of ntx (both powers of two)
     int nchan;    // channels, each with its own grid; global tile = channel * ntiles + tile
     double ref;   // offset of the reference tap from the first tap
 };

@@ -41,7 +41,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_count(const double2* __re
             int cu, cv;
             double du, dv;
             if (tap_geometry(c[u].x, g.W, g.ref, g.N, &cu, &du) && tap_geometry(c[u].y, g.W, g.ref, g.N, &cv, &dv)) {
-                atomicAdd(&hist[(cv / g.T) * g.ntx + (cu / g.T)], 1);
+                atomicAdd(&hist[((cv >> g.lb) << g.lbx) + (cu >> g.lb)], 1);
             } else {
                 atomicAdd(&hist[g.ntiles], 1);
                 bad = 1;
@@ -79,10 +79,10 @@ __global__ __launch_bounds__(64 * kScanGroups) void k_plan_colscan(PlanGeom g, i
             b1 = chan_blocks[g.nchan];
             col = g.ntiles;
         } else {
-            const int c = static_cast<int>(slot / g.ntiles);
+            const int c = static_cast<int>(slot >> (2 * g.lbx));
             b0 = chan_blocks[c];
             b1 = chan_blocks[c + 1];
-            col = static_cast<int>(slot % g.ntiles);
+            col = static_cast<int>(slot) & (g.ntiles - 1);
         }
     }
     const int len = b1 - b0;
@@ -152,10 +152,8 @@ __device__ __forceinline__ void scan_place(const PlanGeom& g, int t, int c, int 
     const int ni = slot_items(c, cap);
     item_start[t] = a.si;
     if (c > 0) {
-        // tiles per row and tiles per channel are powers of two
-        const int lbx = __builtin_ctz(static_cast<unsigned>(g.ntx));
         const int lt = t & (g.ntiles - 1);
-        const int tr = lt >> lbx, tc = lt & (g.ntx - 1);
+        const int tr = lt >> g.lbx, tc = lt & (g.ntx - 1);
         a.rmin = min(a.rmin, tr);
         a.rmax = max(a.rmax, tr);
         a.cmin = min(a.cmin, tc);
@@ -327,10 +325,10 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_scatter(const double2* __
             int cu, cv;
             double du, dv;
             if (tap_geometry(c[u].x, g.W, g.ref, g.N, &cu, &du) && tap_geometry(c[u].y, g.W, g.ref, g.N, &cv, &dv)) {
-                key[u] = (cv / g.T) * g.ntx + (cu / g.T);
+                key[u] = ((cv >> g.lb) << g.lbx) + (cu >> g.lb);
                 typename Pack<R>::T2 o;
-                o.x = pack_axis<R>(cu % g.T, du, dlo, lb, ms, kb);
-                o.y = pack_axis<R>(cv % g.T, dv, dlo, lb, ms, kb);
+                o.x = pack_axis<R>(cu & (g.T - 1), du, dlo, lb, ms, kb);
+                o.y = pack_axis<R>(cv & (g.T - 1), dv, dlo, lb, ms, kb);
                 offk[k] = o;
             } else {
                 key[u] = g.ntiles;                           // dropped: a position after the valid ones
@@ -420,7 +418,7 @@ __global__ __launch_bounds__(kSortThreads) void k_plan_sort_items(PlanGeom g, in
         const int g0 = grp * chunk, g1 = min(it.z, g0 + chunk);
         for (int e = g0 + wig * 64 + lane; e < g1; e += 64 * wpg) {
             const typename Pack<R>::T2 r = off0[it.y + e];
-            atomicAdd(&gc[static_cast<int>(r.y >> sh) * g.T + static_cast<int>(r.x >> sh)], 1);
+            atomicAdd(&gc[(static_cast<int>(r.y >> sh) << lb) + static_cast<int>(r.x >> sh)], 1);
         }
         __syncthreads();
         if (groups > 1) {
@@ -475,7 +473,7 @@ __global__ __launch_bounds__(kSortThreads) void k_plan_sort_items(PlanGeom g, in
                     if (groups == 1) cnt[c] = 0;         // the group's ranks while placing
                     if (!n) continue;
                     const int f = n / kPiece, t = n % kPiece;
-                    const int lc = ((c / g.T) << 8) | (c % g.T);
+                    const int lc = ((c >> lb) << 8) | (c & (g.T - 1));
                     const int Fc = cinfo[c];
                     for (int q = 0; q < f; ++q)
                         pieces[it.y + Fc + q] = make_int2(it.y + (Fc + q) * kPiece, kPiece | (lc << 16));
@@ -498,7 +496,7 @@ __global__ __launch_bounds__(kSortThreads) void k_plan_sort_items(PlanGeom g, in
             int c = 0, rank = 0;
             if (live) {
                 r = off0[it.y + e];
-                c = static_cast<int>(r.y >> sh) * g.T + static_cast<int>(r.x >> sh);
+                c = (static_cast<int>(r.y >> sh) << lb) + static_cast<int>(r.x >> sh);
             }
             if (wpg == 1) {                              // the group's counters are the wave's own
                 if (live) rank = atomicAdd(&gc[c], 1);
