@@ -415,10 +415,10 @@ void give_flag_slot(int* s) {
 
 lmg_plan::~lmg_plan() {
     if (ready) {
-        (void)hipEventSynchronize(ready);          // the readback into the pinned slot has landed
+        (void)hipEventSynchronize(ready);          // the counts have reached the pinned slot
         (void)hipEventDestroy(ready);
+        if (host_flags) give_flag_slot(host_flags);    // (a plan that failed before its event keeps its slot)
     }
-    if (host_flags) give_flag_slot(host_flags);
 }
 
 namespace {
@@ -642,58 +642,81 @@ lmg_status create_plan(const lmg_table* table, int N, lmg_precision prec, int nc
     p->twiddle = base + L.twiddle;
     p->hpix = base + L.hpix;
 
-    // Plan blocks: runs of at most plan_block_vis() visibilities of one channel.
+    // Plan blocks: runs of at most plan_block_vis() visibilities of one channel. A single channel's tables are written
+    // by the setup kernel; a batch's are staged in pinned memory.
     const int block_vis = plan_block_vis(N, nvis);
     std::vector<int4> blocks;
-    std::vector<int> chan_blocks(static_cast<size_t>(nchan) + 1);
-    for (int c = 0; c < nchan; ++c) {
-        chan_blocks[c] = static_cast<int>(blocks.size());
-        for (int64_t a = offsets[c]; a < offsets[c + 1]; a += block_vis)
-            blocks.push_back(make_int4(c, static_cast<int>(a),
-                                       static_cast<int>(std::min<int64_t>(block_vis, offsets[c + 1] - a)), 0));
+    std::vector<int> chan_blocks;
+    if (nchan == 1) {
+        p->nblocks = static_cast<int>((nvis + block_vis - 1) / block_vis);
+    } else {
+        chan_blocks.resize(static_cast<size_t>(nchan) + 1);
+        for (int c = 0; c < nchan; ++c) {
+            chan_blocks[c] = static_cast<int>(blocks.size());
+            for (int64_t a = offsets[c]; a < offsets[c + 1]; a += block_vis)
+                blocks.push_back(make_int4(c, static_cast<int>(a),
+                                           static_cast<int>(std::min<int64_t>(block_vis, offsets[c + 1] - a)), 0));
+        }
+        chan_blocks[nchan] = static_cast<int>(blocks.size());
+        p->nblocks = static_cast<int>(blocks.size());
     }
-    chan_blocks[nchan] = static_cast<int>(blocks.size());
-    p->nblocks = static_cast<int>(blocks.size());
     if (p->nblocks > L.max_blocks) return LMG_EINVAL;       // cannot happen; guards the workspace bound
 
     // Constant tables: kernel coefficients, FFT twiddles, correction h(x_p); block tables.
     std::vector<double> h(N);
     if (lmg_correction(table, N, h.data()) != LMG_OK) return LMG_EINVAL;
-    std::vector<float> hf(h.begin(), h.end());
+    PlanSetup su{};
+    su.flags = p->flags;
+    su.blocks = p->blocks;
+    su.chan_blocks = p->chan_blocks;
+    su.gen_blocks = nchan == 1 ? p->nblocks : -1;
+    su.block_vis = block_vis;
+    su.nvis = static_cast<int>(nvis);
+    int copies = 0;
+    auto from_pinned = [&](void* dst, const void* src, size_t bytes) {
+        su.dst[copies] = dst;
+        su.src[copies] = src;
+        su.bytes[copies++] = static_cast<int>(bytes);
+    };
+    std::vector<float> hf;
     if (const lmg_table::Pinned* pc = pinned_constants(table, N, prec, h)) {
         const char* b = static_cast<const char*>(pc->host);
-        if (upload(p->coef, b + pc->coef, pc->coef_bytes, s) != LMG_OK) return LMG_EHIP;
-        if (upload(p->twiddle, b + pc->twiddle, pc->twiddle_bytes, s) != LMG_OK) return LMG_EHIP;
-        if (upload(p->hpix, b + pc->hpix, pc->hpix_bytes, s) != LMG_OK) return LMG_EHIP;
+        from_pinned(p->coef, b + pc->coef, pc->coef_bytes);
+        from_pinned(p->twiddle, b + pc->twiddle, pc->twiddle_bytes);
+        from_pinned(p->hpix, b + pc->hpix, pc->hpix_bytes);
     } else if (prec == LMG_F64) {
         if (upload(p->coef, coef_host(table, prec), tab_bytes, s) != LMG_OK) return LMG_EHIP;
         if (upload(p->twiddle, twiddles_f64(N).data(), 2 * sizeof(double) * N, s) != LMG_OK) return LMG_EHIP;
         if (upload(p->hpix, h.data(), sizeof(double) * N, s) != LMG_OK) return LMG_EHIP;
     } else {
+        hf.assign(h.begin(), h.end());
         if (upload(p->coef, coef_host(table, prec), tab_bytes, s) != LMG_OK) return LMG_EHIP;
         if (upload(p->twiddle, twiddles_f32(N).data(), 2 * sizeof(float) * N, s) != LMG_OK) return LMG_EHIP;
         if (upload(p->hpix, hf.data(), sizeof(float) * N, s) != LMG_OK) return LMG_EHIP;
     }
-    {
+    bool staged = false;
+    if (nchan > 1) {
         const size_t bb = blocks.size() * sizeof(int4), cb = chan_blocks.size() * sizeof(int);
-        char* st = static_cast<char*>(block_staging(align_up(bb) + cb));
-        const void* bsrc = blocks.data();
-        const void* csrc = chan_blocks.data();
-        if (st) {
+        if (char* st = static_cast<char*>(block_staging(align_up(bb) + cb))) {
             if (bb) std::memcpy(st, blocks.data(), bb);
             std::memcpy(st + align_up(bb), chan_blocks.data(), cb);
-            bsrc = st;
-            csrc = st + align_up(bb);
-        }
-        if (bb && upload(p->blocks, bsrc, bb, s) != LMG_OK) return LMG_EHIP;
-        if (upload(p->chan_blocks, csrc, cb, s) != LMG_OK) return LMG_EHIP;
-        if (st) {
-            if (!g_staging.done) LMG_HIP(hipEventCreateWithFlags(&g_staging.done, hipEventDisableTiming));
-            LMG_HIP(hipEventRecord(g_staging.done, s));
-            g_staging.pending = true;
+            from_pinned(p->blocks, st, bb);
+            from_pinned(p->chan_blocks, st + align_up(bb), cb);
+            staged = true;
+        } else {
+            if (upload(p->blocks, blocks.data(), bb, s) != LMG_OK) return LMG_EHIP;
+            if (upload(p->chan_blocks, chan_blocks.data(), cb, s) != LMG_OK) return LMG_EHIP;
         }
     }
-    LMG_HIP(launch_zero_ints(p->flags, 16, s));          // a kernel, not a memset node, if captured
+    {
+        TraceScope ts("plan_setup", s);
+        LMG_HIP(launch_plan_setup(su, s));
+    }
+    if (staged) {
+        if (!g_staging.done) LMG_HIP(hipEventCreateWithFlags(&g_staging.done, hipEventDisableTiming));
+        LMG_HIP(hipEventRecord(g_staging.done, s));
+        g_staging.pending = true;
+    }
     {
         TraceScope ts("plan_count", s);
         LMG_HIP(launch_plan_count(uv, p->blocks, p->nblocks, p->g, p->blockhist, p->flags, s));
@@ -704,38 +727,43 @@ lmg_status create_plan(const lmg_table* table, int N, lmg_precision prec, int nc
     }
     {
         TraceScope ts("plan_scan", s);
-        LMG_HIP(launch_plan_scan(p->g, p->tile_count, p->tile_start, p->item_start, p->items, p->flags, cap, s));
+        p->host_flags = take_flag_slot();
+        LMG_HIP(launch_plan_scan(p->g, p->tile_count, p->tile_start, p->item_start, p->items, p->flags, cap,
+                                 p->host_flags, s));
     }
+    const bool direct = nvis <= kDirectPlanVis;
     {
         TraceScope ts("plan_scatter", s);
         // packed offsets by caller index go to `off` for now (the item sort overwrites it)
-        LMG_HIP(launch_plan_scatter(prec == LMG_F64, uv, p->blocks, p->nblocks, p->g, p->tile_start, p->blockhist,
-                                    delta_low(table->W), p->lb, p->ms_enc, p->kb, p->inv0, p->off, s));
+        LMG_HIP(launch_plan_scatter(prec == LMG_F64, direct, uv, p->blocks, p->nblocks, p->g, p->tile_start,
+                                    p->blockhist, delta_low(table->W), p->lb, p->ms_enc, p->kb, p->inv0,
+                                    direct ? p->off0 : p->off, s));
     }
-    {
+    if (!direct) {
         TraceScope ts("plan_place", s);
         LMG_HIP(launch_plan_place(prec == LMG_F64, p->inv0, p->off, p->flags, nvis, p->off0, s));
     }
     {
         TraceScope ts("plan_sort_items", s);
         LMG_HIP(launch_plan_sort(prec == LMG_F64, p->g, p->items, L.max_items, p->flags, static_cast<int>(nvis),
-                                 p->lb, p->off0, p->off, p->pos2, p->pieces, s));
+                                 p->lb, p->off0, direct ? p->inv0 : nullptr, p->off, direct ? p->inv : p->pos2,
+                                 p->pieces, s));
     }
-    {
+    if (!direct) {
         TraceScope ts("plan_compose", s);
         LMG_HIP(launch_plan_compose(p->inv0, p->pos2, nvis, p->inv, s));
     }
-    // Counts come back asynchronously; the host reads them when it first needs them.
-    LMG_HIP(hipEventCreateWithFlags(&p->ready, hipEventDisableTiming));
-    p->host_flags = take_flag_slot();
-    if (p->host_flags) {
-        LMG_HIP(hipMemcpyAsync(p->host_flags, p->flags, 8 * sizeof(int), hipMemcpyDeviceToHost, s));
-        LMG_HIP(hipEventRecord(p->ready, s));
-    } else {                                  // no pinned memory: read back synchronously
+    // The counts came back with the scan; the host reads them when it first needs them.
+    hipEvent_t ready = nullptr;
+    LMG_HIP(hipEventCreateWithFlags(&ready, hipEventDisableTiming));
+    const hipError_t rec = hipEventRecord(ready, s);
+    if (rec != hipSuccess) (void)hipEventDestroy(ready);
+    LMG_HIP(rec);
+    p->ready = ready;
+    if (!p->host_flags) {                                  // no pinned memory: read back synchronously
         static thread_local int fallback[8];
         LMG_HIP(hipMemcpyAsync(fallback, p->flags, sizeof(fallback), hipMemcpyDeviceToHost, s));
-        LMG_HIP(hipEventRecord(p->ready, s));
-        LMG_HIP(hipEventSynchronize(p->ready));
+        LMG_HIP(hipStreamSynchronize(s));
         p->host_flags = fallback;
         const lmg_status st = ensure_flags(p.get());
         p->host_flags = nullptr;

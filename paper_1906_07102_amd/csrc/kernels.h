@@ -23,6 +23,8 @@ inline int plan_block_vis(int N, int64_t nvis) {
     const int64_t v = (std::max(least, (nvis + 255) / 256) + 1023) / 1024 * 1024;
     return static_cast<int>(std::min<int64_t>(v, kPlanBlockVis));
 }
+// Plans of at most this many visibilities scatter directly (k_plan_scatter).
+constexpr int64_t kDirectPlanVis = 1 << 18;
 // Longest run of one footprint cell handled by one lane (a "piece").
 constexpr int kPiece = 32;
 // Elements of padding after the entry-order arrays the item kernels read in runs.
@@ -119,22 +121,37 @@ struct FftArgs {
     int row_off;
 };
 
+// What a plan's workspace starts from: up to five arrays copied from pinned host memory (16-byte aligned on both
+// sides, sizes multiples of four), 16 zeroed flags, and for a single channel (gen_blocks >= 0) the block tables.
+struct PlanSetup {
+    static constexpr int kCopies = 5;
+    const void* src[kCopies];
+    void* dst[kCopies];
+    int bytes[kCopies];
+    int* flags;
+    int4* blocks;
+    int* chan_blocks;
+    int gen_blocks, block_vis, nvis;
+};
+hipError_t launch_plan_setup(const PlanSetup& a, hipStream_t s);
 hipError_t launch_plan_count(const double* uv, const int4* blocks, int nb, const PlanGeom& g, int* blockhist,
                              int* flags, hipStream_t s);
 hipError_t launch_plan_colscan(const PlanGeom& g, int* blockhist, const int* chan_blocks, int* tile_count,
                                hipStream_t s);
+// host_flags (or nullptr): pinned host copy of flags[0 .. 7].
 hipError_t launch_plan_scan(const PlanGeom& g, const int* tile_count, int* tile_start, int* item_start, int4* items,
-                            int* flags, int cap, hipStream_t s);
-// inv0[k] = tile-order position, offk[k] = packed offsets (both by caller index), packed for a table of
-// ms intervals (1 for a direct table), kb = bits of ms.
-hipError_t launch_plan_scatter(bool f64, const double* uv, const int4* blocks, int nb, const PlanGeom& g,
+                            int* flags, int cap, int* host_flags, hipStream_t s);
+// By caller index: index[k] = tile-order position, offs[k] = packed offsets, packed for a table of ms intervals (1 for
+// a direct table), kb = bits of ms. With `direct`, by tile-order position: index[p] = caller index, offs[p].
+hipError_t launch_plan_scatter(bool f64, bool direct, const double* uv, const int4* blocks, int nb, const PlanGeom& g,
                                const int* tile_start, const int* blockhist, double dlo, int lb, int ms, int kb,
-                               int* inv0, void* offk, hipStream_t s);
+                               int* index, void* offs, hipStream_t s);
 // off0[inv0[k]] = offk[k] for the valid visibilities (flags[2] of them).
 hipError_t launch_plan_place(bool f64, const int* inv0, const void* offk, const int* flags, int64_t nvis, void* off0,
                              hipStream_t s);
 hipError_t launch_plan_sort(bool f64, const PlanGeom& g, int4* items, int max_items, const int* flags, int nvis,
-                            int lb, const void* off0, void* off, int* pos2, int2* pieces, hipStream_t s);
+                            int lb, const void* off0, const int* perm0, void* off, int* map, int2* pieces,
+                            hipStream_t s);
 hipError_t launch_plan_compose(const int* inv0, const int* pos2, int64_t nvis, int* inv, hipStream_t s);
 // Bytes of one visibility's packed offsets (both axes).
 size_t packed_offset_bytes(bool f64);

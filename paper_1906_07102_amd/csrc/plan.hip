@@ -10,6 +10,36 @@ namespace dev {
 // read and cleared by lmg_sync_status through the runtime's symbol copies.
 __device__ int g_data_error;
 
+// Before pass 1: the constants a plan keeps (coefficients, twiddles,
+// correction) and, for a batch, the block tables, read from pinned host memory
+// in 16-byte pieces (one per thread, all in flight at once); the block tables
+// of a single channel, which follow from its size; the flags, zeroed. One
+// launch instead of five copies and a fill, which took 30 to 40 us of host and
+// queue time per plan.
+__global__ __launch_bounds__(256) void k_plan_setup(PlanSetup a) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < 16) a.flags[i] = 0;
+    for (int b = i; b < a.gen_blocks; b += gridDim.x * 256)
+        a.blocks[b] = make_int4(0, b * a.block_vis, min(a.block_vis, a.nvis - b * a.block_vis), 0);
+    if (a.gen_blocks >= 0 && i < 2) a.chan_blocks[i] = i ? a.gen_blocks : 0;
+    int at = i;
+#pragma unroll
+    for (int q = 0; q < PlanSetup::kCopies; ++q) {
+        const int n = (a.bytes[q] + 15) / 16;
+        if (at >= 0 && at < n) {
+            const char* src = static_cast<const char*>(a.src[q]) + static_cast<size_t>(at) * 16;
+            char* dst = static_cast<char*>(a.dst[q]) + static_cast<size_t>(at) * 16;
+            const int left = a.bytes[q] - at * 16;
+            if (left >= 16) {
+                *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(src);
+            } else {
+                for (int w = 0; w < left; w += 4) *reinterpret_cast<int*>(dst + w) = *reinterpret_cast<const int*>(src + w);
+            }
+        }
+        at -= n;
+    }
+}
+
 // Pass 1: count visibilities per tile, per plan block (a run of at most
 // plan_block_vis() visibilities of one channel, kept per block so that pass 3
 // can place each block's visibilities of a tile in one contiguous run). The
@@ -208,7 +238,7 @@ __device__ __forceinline__ void scan_slots(const PlanGeom& g, const int* cnt, in
 __global__ __launch_bounds__(1024) void k_plan_scan(PlanGeom g, const int* __restrict__ tile_count,
                                                     int* __restrict__ tile_start, int* __restrict__ item_start,
                                                     int4* __restrict__ items, int* __restrict__ flags, int cap,
-                                                    int staged) {
+                                                    int staged, int* __restrict__ host_flags) {
     extern __shared__ int lds[];
     int* sh = lds;                               // 17 ints for the block reductions
     const int tot = g.ntiles * g.nchan;          // tile slots, channel-major; slot tot = dropped
@@ -274,11 +304,22 @@ __global__ __launch_bounds__(1024) void k_plan_scan(PlanGeom g, const int* __res
         flags[5] = rmax;
         flags[6] = cmin;
         flags[7] = cmax;
+        if (host_flags) {                        // the host's copy, in pinned memory
+            host_flags[0] = flags[0];
+            host_flags[1] = nitems;
+            host_flags[2] = flags[2];
+            host_flags[3] = busy;
+            host_flags[4] = rmin;
+            host_flags[5] = rmax;
+            host_flags[6] = cmin;
+            host_flags[7] = cmax;
+            __threadfence_system();
+        }
     }
 }
 
-// Pass 3: give each visibility its tile-order position (inv0, by caller
-// index) and its packed offsets (offk, by caller index): both writes are
+// Pass 3: give each visibility its tile-order position (index = inv0, by
+// caller index) and its packed offsets (offs, by caller index): both writes are
 // coalesced. The scattered store of the offsets into tile order is a pass of
 // its own (k_plan_place): here each XCD runs 32 plan blocks, that is 32
 // time windows, at once, and their partly written lines would overflow L2.
@@ -287,13 +328,19 @@ __global__ __launch_bounds__(1024) void k_plan_scan(PlanGeom g, const int* __res
 // a fixed turn (wave 0 first, a barrier between turns), so that a tile's
 // visibilities stay in the caller's order: every later summation order is the
 // same on every run and for every size of block.
-template <typename R>
+//
+// kDirect (plans of at most kDirectPlanVis visibilities, whose arrays stay in
+// L2, so that scattered stores need no order of their own): the offsets go
+// straight to tile order (off0) with the caller index beside them (perm0), and
+// the item sort writes caller index -> entry itself; the place and compose
+// passes are not run.
+template <typename R, bool kDirect>
 __global__ __launch_bounds__(kPlanThreads) void k_plan_scatter(const double2* __restrict__ uv,
                                                                const int4* __restrict__ blocks, int nb, PlanGeom g,
                                                                const int* __restrict__ tile_start,
                                                                const int* __restrict__ blockhist, double dlo, int lb,
-                                                               int ms, int kb, int* __restrict__ inv0,
-                                                               typename Pack<R>::T2* __restrict__ offk) {
+                                                               int ms, int kb, int* __restrict__ index,
+                                                               typename Pack<R>::T2* __restrict__ offs) {
     extern __shared__ int cur[];
     const int hs = g.ntiles + 1;
     const int chunk = xcd_chunk(blockIdx.x, nb);
@@ -317,6 +364,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_scatter(const double2* __
             if (u < kb_run && k < end) c[u] = nt_load(uv + k);     // the coordinates' last read
         }
         int key[kB];                                         // tile slot (ntiles: dropped), -1 past the run
+        typename Pack<R>::T2 packed[kB];
 #pragma unroll
         for (int u = 0; u < kB; ++u) {
             const int64_t k = k0 + u * 64;
@@ -329,7 +377,8 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_scatter(const double2* __
                 typename Pack<R>::T2 o;
                 o.x = pack_axis<R>(cu & (g.T - 1), du, dlo, lb, ms, kb);
                 o.y = pack_axis<R>(cv & (g.T - 1), dv, dlo, lb, ms, kb);
-                offk[k] = o;
+                packed[u] = o;
+                if (!kDirect) offs[k] = o;
             } else {
                 key[u] = g.ntiles;                           // dropped: a position after the valid ones
             }
@@ -344,8 +393,15 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_scatter(const double2* __
             __syncthreads();
         }
 #pragma unroll
-        for (int u = 0; u < kB; ++u)
-            if (key[u] >= 0) inv0[k0 + u * 64] = dst[u];
+        for (int u = 0; u < kB; ++u) {
+            if (key[u] < 0) continue;
+            if constexpr (kDirect) {
+                if (key[u] != g.ntiles) offs[dst[u]] = packed[u];
+                index[dst[u]] = static_cast<int>(k0 + u * 64);
+            } else {
+                index[k0 + u * 64] = dst[u];
+            }
+        }
     }
 }
 
@@ -375,9 +431,10 @@ __global__ __launch_bounds__(kPermThreads) void k_plan_place(const int* __restri
 // pieces, cell by cell (cell c's f = n / kPiece pieces at F(c) .. F(c)+f-1,
 // F an exclusive prefix of f), then the tails, longest first (a wave's lanes
 // run loops of similar length). Outputs: packed offsets `off` by entry,
-// pos2 (tile-order position -> entry), pieces[] (first entry, length |
+// map (pos2, tile-order position -> entry; with perm0, tile-order position ->
+// caller index, it is inv, caller index -> entry), pieces[] (first entry, length |
 // cell << 16) and items[i].w = number of pieces | (full pieces / 64) << 16.
-// Dropped visibilities (tile-order positions n_valid .. nvis) get pos2 = -1.
+// Dropped visibilities (tile-order positions n_valid .. nvis) get -1.
 // Ranks within a cell follow the item's tile order in a fixed way: the item
 // is cut into `groups` contiguous chunks, one per group of waves, each with
 // its own LDS cell counters whose bases are the counts of the chunks before
@@ -388,8 +445,9 @@ template <typename R>
 __global__ __launch_bounds__(kSortThreads) void k_plan_sort_items(PlanGeom g, int4* __restrict__ items,
                                                          const int* __restrict__ flags, int nvis, int lb, int groups,
                                                          const typename Pack<R>::T2* __restrict__ off0,
+                                                         const int* __restrict__ perm0,
                                                          typename Pack<R>::T2* __restrict__ off,
-                                                         int* __restrict__ pos2, int2* __restrict__ pieces) {
+                                                         int* __restrict__ map, int2* __restrict__ pieces) {
     extern __shared__ int sm[];
     __shared__ int scan_sh[17];         // block scan
     __shared__ int lcnt[kPiece];        // tails per length, then slot cursors
@@ -407,7 +465,7 @@ __global__ __launch_bounds__(kSortThreads) void k_plan_sort_items(PlanGeom g, in
     int* gc = gcnt + grp * TT;
     const int n_items = flags[1];
     for (int e = flags[2] + blockIdx.x * blockDim.x + threadIdx.x; e < nvis; e += gridDim.x * blockDim.x)
-        pos2[e] = -1;
+        map[perm0 ? perm0[e] : e] = -1;
     for (int item = blockIdx.x; item < n_items; item += gridDim.x) {     // uniform across the workgroup
         const int4 it = items[item];
         for (int c = threadIdx.x; c < groups * TT; c += blockDim.x) gcnt[c] = 0;
@@ -513,7 +571,7 @@ __global__ __launch_bounds__(kSortThreads) void k_plan_sort_items(PlanGeom g, in
                 const int pos = rank < f * kPiece ? Fc * kPiece + rank : (ci >> 16) + rank - f * kPiece;
                 const int dst = it.y + pos;
                 off[dst] = r;
-                pos2[it.y + e] = dst;
+                map[perm0 ? perm0[it.y + e] : it.y + e] = dst;
             }
         }
         __syncthreads();                                 // LDS counters are reused by the next item
@@ -601,6 +659,13 @@ __global__ void k_zero_ints(int* __restrict__ p, int n) {
 
 }  // namespace dev
 
+hipError_t launch_plan_setup(const PlanSetup& a, hipStream_t s) {
+    int n = 16;
+    for (int q = 0; q < PlanSetup::kCopies; ++q) n += (a.bytes[q] + 15) / 16;
+    hipLaunchKernelGGL(dev::k_plan_setup, dim3((n + 255) / 256), dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+
 hipError_t launch_plan_count(const double* uv, const int4* blocks, int nb, const PlanGeom& g, int* blockhist,
                              int* flags, hipStream_t s) {
     if (nb == 0) return hipSuccess;
@@ -618,7 +683,7 @@ hipError_t launch_plan_colscan(const PlanGeom& g, int* blockhist, const int* cha
 }
 
 hipError_t launch_plan_scan(const PlanGeom& g, const int* tile_count, int* tile_start, int* item_start, int4* items,
-                            int* flags, int cap, hipStream_t s) {
+                            int* flags, int cap, int* host_flags, hipStream_t s) {
     // Staged through LDS when the counts and two offset arrays fit (and the
     // per-thread run fits the kernel's registers: ns <= 1024 * 24).
     const size_t ns = static_cast<size_t>(g.ntiles) * g.nchan + 1;
@@ -626,7 +691,7 @@ hipError_t launch_plan_scan(const PlanGeom& g, const int* tile_count, int* tile_
     const int staged = (staged_bytes <= kMaxDynLds && ns <= 1024 * 24) ? 1 : 0;
     const size_t shm = staged ? staged_bytes : 32 * sizeof(int);
     hipLaunchKernelGGL(dev::k_plan_scan, dim3(1), dim3(1024), shm, s, g, tile_count, tile_start, item_start, items,
-                       flags, cap, staged);
+                       flags, cap, staged, host_flags);
     return hipGetLastError();
 }
 
@@ -635,19 +700,24 @@ int packed_cell_shift(bool f64, int lb) {
     return f64 ? dev::pack_cell_shift<double>(lb) : dev::pack_cell_shift<float>(lb);
 }
 
-hipError_t launch_plan_scatter(bool f64, const double* uv, const int4* blocks, int nb, const PlanGeom& g,
+namespace {
+template <typename R, bool kDirect>
+void scatter(const double* uv, const int4* blocks, int nb, const PlanGeom& g, const int* tile_start,
+             const int* blockhist, double dlo, int lb, int ms, int kb, int* index, void* offs, hipStream_t s) {
+    hipLaunchKernelGGL((dev::k_plan_scatter<R, kDirect>), dim3(nb), dim3(kPlanThreads), (g.ntiles + 1) * sizeof(int), s,
+                       reinterpret_cast<const double2*>(uv), blocks, nb, g, tile_start, blockhist, dlo, lb, ms, kb,
+                       index, reinterpret_cast<typename dev::Pack<R>::T2*>(offs));
+}
+}  // namespace
+
+hipError_t launch_plan_scatter(bool f64, bool direct, const double* uv, const int4* blocks, int nb, const PlanGeom& g,
                                const int* tile_start, const int* blockhist, double dlo, int lb, int ms, int kb,
-                               int* inv0, void* offk, hipStream_t s) {
+                               int* index, void* offs, hipStream_t s) {
     if (nb == 0) return hipSuccess;
-    const size_t shm = (g.ntiles + 1) * sizeof(int);
-    if (f64)
-        hipLaunchKernelGGL(dev::k_plan_scatter<double>, dim3(nb), dim3(kPlanThreads), shm, s,
-                           reinterpret_cast<const double2*>(uv), blocks, nb, g, tile_start, blockhist, dlo, lb, ms, kb,
-                           inv0, reinterpret_cast<ulonglong2*>(offk));
-    else
-        hipLaunchKernelGGL(dev::k_plan_scatter<float>, dim3(nb), dim3(kPlanThreads), shm, s,
-                           reinterpret_cast<const double2*>(uv), blocks, nb, g, tile_start, blockhist, dlo, lb, ms, kb,
-                           inv0, reinterpret_cast<uint2*>(offk));
+    if (f64 && direct) scatter<double, true>(uv, blocks, nb, g, tile_start, blockhist, dlo, lb, ms, kb, index, offs, s);
+    else if (f64) scatter<double, false>(uv, blocks, nb, g, tile_start, blockhist, dlo, lb, ms, kb, index, offs, s);
+    else if (direct) scatter<float, true>(uv, blocks, nb, g, tile_start, blockhist, dlo, lb, ms, kb, index, offs, s);
+    else scatter<float, false>(uv, blocks, nb, g, tile_start, blockhist, dlo, lb, ms, kb, index, offs, s);
     return hipGetLastError();
 }
 
@@ -665,7 +735,8 @@ hipError_t launch_plan_place(bool f64, const int* inv0, const void* offk, const 
 }
 
 hipError_t launch_plan_sort(bool f64, const PlanGeom& g, int4* items, int max_items, const int* flags, int nvis,
-                            int lb, const void* off0, void* off, int* pos2, int2* pieces, hipStream_t s) {
+                            int lb, const void* off0, const int* perm0, void* off, int* map, int2* pieces,
+                            hipStream_t s) {
     // One counter group per wave while the counters fit in 40 KB with the per-cell arrays (T <= 32),
     // else one group whose waves take turns.
     const size_t TT = static_cast<size_t>(g.T) * g.T;
@@ -675,11 +746,11 @@ hipError_t launch_plan_sort(bool f64, const PlanGeom& g, int4* items, int max_it
     const unsigned nb = static_cast<unsigned>(std::max(1, std::min(max_items, 8192)));
     if (f64)
         hipLaunchKernelGGL(dev::k_plan_sort_items<double>, dim3(nb), dim3(dev::kSortThreads), shm, s, g, items, flags, nvis, lb, groups,
-                           reinterpret_cast<const ulonglong2*>(off0), reinterpret_cast<ulonglong2*>(off), pos2,
+                           reinterpret_cast<const ulonglong2*>(off0), perm0, reinterpret_cast<ulonglong2*>(off), map,
                            pieces);
     else
         hipLaunchKernelGGL(dev::k_plan_sort_items<float>, dim3(nb), dim3(dev::kSortThreads), shm, s, g, items, flags, nvis, lb, groups,
-                           reinterpret_cast<const uint2*>(off0), reinterpret_cast<uint2*>(off), pos2,
+                           reinterpret_cast<const uint2*>(off0), perm0, reinterpret_cast<uint2*>(off), map,
                            pieces);
     return hipGetLastError();
 }
@@ -731,8 +802,10 @@ hipError_t set_kernel_attributes() {
     // Per-tile histograms of up to 128 x 128 ints; the item sort keeps two per-cell arrays of up to 128 x 128.
     LMG_ATTR(72 * 1024, &dev::k_plan_count);
     LMG_ATTR(kMaxDynLds, &dev::k_plan_scan);
-    LMG_ATTR(72 * 1024, &dev::k_plan_scatter<float>);
-    LMG_ATTR(72 * 1024, &dev::k_plan_scatter<double>);
+    LMG_ATTR(72 * 1024, &dev::k_plan_scatter<float, false>);
+    LMG_ATTR(72 * 1024, &dev::k_plan_scatter<float, true>);
+    LMG_ATTR(72 * 1024, &dev::k_plan_scatter<double, false>);
+    LMG_ATTR(72 * 1024, &dev::k_plan_scatter<double, true>);
     LMG_ATTR(128 * 1024, &dev::k_plan_sort_items<float>);
     LMG_ATTR(128 * 1024, &dev::k_plan_sort_items<double>);
 #undef LMG_ATTR
