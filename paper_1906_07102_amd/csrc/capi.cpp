@@ -54,7 +54,8 @@ struct lmg_plan {
     int* blockhist = nullptr;      // per plan block and tile: counts, then offsets
     int4* blocks = nullptr;        // per plan block: (channel, first visibility, count, 0)
     int* chan_blocks = nullptr;    // per channel, its first plan block; nchan + 1 entries
-    int4* items = nullptr;
+    int4* items = nullptr;         // per tile: runs of at most cap visibilities
+    int4* sub = nullptr;           // work items: items, or four quadrants of each
     int* inv0 = nullptr;           // caller index -> tile-order position
     void* off0 = nullptr;          // packed offsets, by tile-order position
     void* off = nullptr;           // packed offsets, by entry (piece order within items)
@@ -162,7 +163,7 @@ size_t cplx_size(lmg_precision p) { return 2 * real_size(p); }
 size_t patch_cell_size(lmg_precision p) { return p == LMG_F32 ? 8 : 16; }
 
 struct Layout {
-    size_t flags, tile_count, tile_start, item_start, blockhist, blocks, chan_blocks, items, inv0, off0, off, pos2, inv, pieces, coef,
+    size_t flags, tile_count, tile_start, item_start, blockhist, blocks, chan_blocks, items, sub, inv0, off0, off, pos2, inv, pieces, coef,
         twiddle, hpix, total;
     int max_items;
     int max_blocks;
@@ -192,6 +193,7 @@ Layout plan_layout(int N, int64_t nvis, lmg_precision prec, int cap, int nchan =
     L.blocks = take(static_cast<size_t>(L.max_blocks) * sizeof(int4));
     L.chan_blocks = take((static_cast<size_t>(nchan) + 1) * sizeof(int));
     L.items = take(static_cast<size_t>(L.max_items) * sizeof(int4));
+    L.sub = take(N == 8192 ? static_cast<size_t>(L.max_items) * 4 * sizeof(int4) : 0);
     L.inv0 = take(static_cast<size_t>(nvis) * sizeof(int));
     L.off0 = take(static_cast<size_t>(nvis) * packed_offset_bytes(prec == LMG_F64));
     L.off = take(static_cast<size_t>(nvis + kRunPad) * packed_offset_bytes(prec == LMG_F64));
@@ -211,9 +213,9 @@ struct Scratch {
 };
 constexpr int kCounters = 2;    // work-item counters of the gridding and degridding kernels
 
-Scratch scratch_layout(int N, int W, int T, int M, int items, int64_t nvis, lmg_precision prec, int op) {
-    const size_t P = static_cast<size_t>(T + W - 1);
-    const size_t patches = align_up(static_cast<size_t>(items) * P * P * patch_cell_size(prec));
+Scratch scratch_layout(int N, int W, int T, int lsub, int M, int items, int64_t nvis, lmg_precision prec, int op) {
+    const size_t P = static_cast<size_t>((T >> lsub) + W - 1);
+    const size_t patches = align_up((static_cast<size_t>(items) << (2 * lsub)) * P * P * patch_cell_size(prec));
     const size_t grid = align_up(static_cast<size_t>(N) * N * cplx_size(prec));
     const size_t tmp = align_up(static_cast<size_t>((M + 3) / 4 * 4) * N * cplx_size(prec));     // blocks of four rows
     const size_t vs = align_up(static_cast<size_t>(nvis + kRunPad) * cplx_size(prec));
@@ -229,8 +231,17 @@ Scratch scratch_layout(int N, int W, int T, int M, int items, int64_t nvis, lmg_
     return s;
 }
 
+// Gridding work items are the quadrants of 64-cell tiles (1 = log2 2) on 8192^2 grids, where 128 x 128 tiles cannot be
+// smaller, in the modes with 16-byte patch cells: a 64-cell patch leaves a compute unit one workgroup (gridding 16.8M
+// visibilities, compensated, W = 7: 694 us whole, 578 as quadrants; 4.2M, FP64, W = 6: 283 and 229; FP32's 8-byte cells
+// leave three, 154 and 156).
+int tile_lsub(int N, int T, lmg_precision prec) { return N == 8192 && T == 64 && prec != LMG_F32 ? 1 : 0; }
+
 size_t scratch_for(int N, int W, int T, int M, int items, int64_t nvis, lmg_precision prec, int op) {
-    return scratch_layout(N, W, T, M, items, nvis, prec, op).total;
+    size_t b = 0;
+    for (int lsub = 0; lsub <= tile_lsub(N, T, prec); ++lsub)
+        b = std::max(b, scratch_layout(N, W, T, lsub, M, items, nvis, prec, op).total);
+    return b;
 }
 
 bool valid_grid(int N, int W, double x0, int* M) {
@@ -484,10 +495,11 @@ lmg_status run_grid_entries(const lmg_plan* p, const void* vs, void* grid, void*
     if (wait_plan(p, s) != LMG_OK) return LMG_EHIP;
     LMG_HIP(launch_zero_ints(counters, 1, s));
     GridArgs a{};
-    a.N = p->g.N; a.W = p->g.W; a.T = p->g.T; a.ntx = p->g.ntx; a.Ms = table_ms(t); a.degree = kernel_degree(t);
+    a.N = p->g.N; a.W = p->g.W; a.T = p->g.T >> p->g.lsub; a.ntx = p->g.ntx << p->g.lsub; a.lsub = p->g.lsub;
+    a.Ms = table_ms(t); a.degree = kernel_degree(t);
     a.tab_global = table_global(t, p->prec) ? 1 : 0;
-    a.n_items = p->flags + 1; a.max_items = p->max_items; a.npatch = p->npatch; a.waves = p->waves; a.Ft = p->Ft; a.kb = p->kb;
-    a.items = p->items; a.pieces = p->pieces; a.off = p->off; a.coef = p->coef;
+    a.n_items = p->flags + 1; a.max_items = p->max_items << (2 * p->g.lsub); a.npatch = p->npatch; a.waves = p->waves; a.Ft = p->Ft; a.kb = p->kb;
+    a.items = p->sub; a.pieces = p->pieces; a.off = p->off; a.coef = p->coef;
     a.vis = vs; a.patches = patches; a.counter = counters;
     a.transpose = band_only ? 1 : 0;
     {
@@ -496,14 +508,15 @@ lmg_status run_grid_entries(const lmg_plan* p, const void* vs, void* grid, void*
     }
     AssembleArgs b{};
     b.transpose = a.transpose;
-    b.N = p->g.N; b.W = p->g.W; b.T = p->g.T; b.ntx = p->g.ntx; b.nchan = p->nchan;
+    b.N = p->g.N; b.W = p->g.W; b.T = a.T; b.ntx = a.ntx; b.lsub = p->g.lsub; b.nchan = p->nchan;
     b.accumulate = accumulate ? 1 : 0;
     if (band_only) {                  // an internal grid, stored transposed: only the occupied window is ever read
         const lmg_status st = ensure_flags(p);     // the grid kernels are already queued
         if (st != LMG_OK) return st;
-        b.tr0 = p->win_c0; b.trows = p->win_cn; b.tc0 = p->win_r0; b.tcols = p->win_rn;    // rows along u
+        const int l = p->g.lsub;                    // the window is in plan tiles; rows along u
+        b.tr0 = p->win_c0 << l; b.trows = p->win_cn << l; b.tc0 = p->win_r0 << l; b.tcols = p->win_rn << l;
     } else {
-        b.tr0 = 0; b.trows = p->g.ntx; b.tc0 = 0; b.tcols = p->g.ntx;
+        b.tr0 = 0; b.trows = a.ntx; b.tc0 = 0; b.tcols = a.ntx;
     }
     b.item_start = p->item_start; b.patches = patches; b.grid = grid;
     TraceScope ts("assemble", s);
@@ -529,10 +542,13 @@ lmg_status run_degrid_entries(const lmg_plan* p, const void* grid, bool transpos
     if (wait_plan(p, s) != LMG_OK) return LMG_EHIP;
     LMG_HIP(launch_zero_ints(counters + 1, 1, s));
     DegridArgs a{};
-    a.N = p->g.N; a.W = p->g.W; a.T = p->g.T; a.ntx = p->g.ntx; a.Ms = table_ms(t); a.degree = kernel_degree(t);
+    // FP32 grids by whole tiles also where gridding takes quadrants (16.8M visibilities on 8192^2: 195 us against 223)
+    const int lsub = p->prec == LMG_F64 ? p->g.lsub : 0;
+    a.N = p->g.N; a.W = p->g.W; a.T = p->g.T >> lsub; a.ntx = p->g.ntx << lsub; a.lsub = lsub;
+    a.Ms = table_ms(t); a.degree = kernel_degree(t);
     a.tab_global = table_global(t, p->prec) ? 1 : 0;
-    a.n_items = p->flags + 1; a.max_items = p->max_items; a.Ft = p->Ft; a.kb = p->kb;
-    a.items = p->items; a.pieces = p->pieces; a.off = p->off; a.coef = p->coef;
+    a.n_items = p->flags + 1; a.max_items = p->max_items << (2 * lsub); a.Ft = p->Ft; a.kb = p->kb;
+    a.items = lsub ? p->sub : p->items; a.pieces = p->pieces; a.off = p->off; a.coef = p->coef;
     a.grid = grid; a.transpose = transposed ? 1 : 0; a.vis_out = vs; a.counter = counters + 1;
     TraceScope ts("degrid_items", s);
     LMG_HIP(launch_degrid(p->prec, a, s));
@@ -562,7 +578,7 @@ Scratch plan_scratch(const lmg_plan* p, int op) {
     // that no query waits for its counts.
     const int64_t bound = std::min<int64_t>(static_cast<int64_t>(p->g.ntiles) * p->nchan, p->nvis) +
                           (p->nvis + p->cap - 1) / p->cap + 1;
-    return scratch_layout(p->g.N, p->g.W, p->g.T, p->M, static_cast<int>(std::min<int64_t>(bound, p->max_items)),
+    return scratch_layout(p->g.N, p->g.W, p->g.T, p->g.lsub, p->M, static_cast<int>(std::min<int64_t>(bound, p->max_items)),
                           p->nvis, p->prec, op);
 }
 
@@ -592,9 +608,20 @@ lmg_status create_plan(const lmg_table* table, int N, lmg_precision prec, int nc
     if (T < table->W || N / T > 128) return LMG_ENOTSUP;      // cannot happen for N >= 2W, N <= 8192
     const int cap = choose_cap();
     const int Ms = staged_ms(table, prec);
-    int npatch = fit_patches(T, prec, table->W, Ms);
-    const int waves = fit_waves(T, N, nchan, nvis, cap, prec, table->W, &npatch);
-    if (grid_lds_bytes(prec, table->W, T, Ms, npatch) > kMaxDynLds) return LMG_ENOTSUP;
+    // Quadrants, unless their patches alone would take the plan out of reach of the allocation-free call.
+    int lsub = tile_lsub(N, T, prec);
+    if (lsub) {
+        const int64_t bound = std::min<int64_t>(static_cast<int64_t>(N / T) * (N / T) * nchan, nvis) + (nvis + cap - 1) / cap + 1;
+        const int items = static_cast<int>(std::min<int64_t>(bound, INT32_MAX / 4));
+        auto fits = [&](int l) {
+            return scratch_layout(N, table->W, T, l, M, items, nvis, prec, LMG_OP_GRID).total <= LMG_STATIC_SCRATCH_BYTES;
+        };
+        if (bound > INT32_MAX / 4 || (fits(0) && !fits(1))) lsub = 0;
+    }
+    const int Tq = T >> lsub;
+    int npatch = fit_patches(Tq, prec, table->W, Ms);
+    const int waves = fit_waves(Tq, N, nchan, nvis, cap, prec, table->W, &npatch);
+    if (grid_lds_bytes(prec, table->W, Tq, Ms, npatch) > kMaxDynLds) return LMG_ENOTSUP;
     const Layout L = plan_layout(N, nvis, prec, cap, nchan);
     if (!workspace || ws_bytes < L.total) return LMG_EWORKSPACE;
     if (ensure_attributes() != hipSuccess) return LMG_EHIP;
@@ -606,6 +633,7 @@ lmg_status create_plan(const lmg_table* table, int N, lmg_precision prec, int nc
     p->prec = prec;
     p->g.N = N; p->g.W = table->W; p->g.T = T; p->g.ntx = N / T; p->g.ntiles = (N / T) * (N / T);
     p->g.nchan = nchan;
+    p->g.lsub = lsub;
     p->g.ref = tap_reference(table->W);
     p->waves = waves;
     p->npatch = npatch;
@@ -622,6 +650,7 @@ lmg_status create_plan(const lmg_table* table, int N, lmg_precision prec, int nc
     p->blocks = reinterpret_cast<int4*>(base + L.blocks);
     p->chan_blocks = reinterpret_cast<int*>(base + L.chan_blocks);
     p->items = reinterpret_cast<int4*>(base + L.items);
+    p->sub = p->g.lsub ? reinterpret_cast<int4*>(base + L.sub) : p->items;
     p->inv0 = reinterpret_cast<int*>(base + L.inv0);
     p->off0 = base + L.off0;
     p->off = base + L.off;
@@ -745,7 +774,7 @@ lmg_status create_plan(const lmg_table* table, int N, lmg_precision prec, int nc
     }
     {
         TraceScope ts("plan_sort_items", s);
-        LMG_HIP(launch_plan_sort(prec == LMG_F64, p->g, p->items, L.max_items, p->flags, static_cast<int>(nvis),
+        LMG_HIP(launch_plan_sort(prec == LMG_F64, p->g, p->items, p->sub, L.max_items, p->flags, static_cast<int>(nvis),
                                  p->lb, p->off0, direct ? p->inv0 : nullptr, p->off, direct ? p->inv : p->pos2,
                                  p->pieces, s));
     }

@@ -36,7 +36,7 @@ __global__ __launch_bounds__(kDegridThreads) void k_degrid_items(DegridArgs a) {
     VT* out = reinterpret_cast<VT*>(a.vis_out);     // entry order
     const PT2* off = reinterpret_cast<const PT2*>(a.off);
     const int cshift = a.Ft + a.kb;
-    const int nitems = *a.n_items;
+    const int nitems = *a.n_items << (2 * a.lsub);
     for (bool first = true;; first = false) {
         // the first items are dealt by workgroup, the others from the counter
         if (threadIdx.x == 0) s_item = first ? blockIdx.x : gridDim.x + atomicAdd(a.counter, 1);
@@ -56,7 +56,7 @@ __global__ __launch_bounds__(kDegridThreads) void k_degrid_items(DegridArgs a) {
         __syncthreads();
         for (int e = it.y + threadIdx.x; e < it.y + it.z; e += blockDim.x) {
             const PT2 d = off[e];
-            const int cu = static_cast<int>(d.x >> cshift), cv = static_cast<int>(d.y >> cshift);
+            const int cu = static_cast<int>(d.x >> cshift) & (a.T - 1), cv = static_cast<int>(d.y >> cshift) & (a.T - 1);
             R wu[W], wv[W];
             if constexpr (kTab == kTabDirect) {
                 weights_direct<R, W>(static_cast<const double*>(a.coef), d.x, a.Ft, wu);

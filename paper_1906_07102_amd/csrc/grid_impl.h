@@ -254,7 +254,7 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<Acc, W, kTab>()))) void k_grid
     for (int i = threadIdx.x; i < ntab; i += blockDim.x) tab[i] = gtab[i];
     const VT* vis = reinterpret_cast<const VT*>(a.vis);     // entry order, weights applied
     const PT2* off = reinterpret_cast<const PT2*>(a.off);   // packed offsets, entry order
-    const int nitems = *a.n_items;
+    const int nitems = *a.n_items << (2 * a.lsub);
     for (bool first = true;; first = false) {
         // the first items are dealt by workgroup, the others from the counter
         if (threadIdx.x == 0) s_item = first ? blockIdx.x : gridDim.x + atomicAdd(a.counter, 1);
@@ -355,6 +355,19 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<Acc, W, kTab>()))) void k_grid
 // returns at once, so cells outside the data's footprint are neither read nor
 // written. One workgroup per a.rows rows of a tile (chosen by the launcher).
 
+// Patches of the items that cover tile (r, c) of a channel whose first plan tile is cbase: numbers first, first + step,
+// ... before end. A transposed grid's tile rows run along u, while plan tiles are numbered along v.
+struct TilePatches {
+    int first, end;
+    __device__ __forceinline__ TilePatches(const AssembleArgs& a, int cbase, int r, int c) {
+        const int tv = a.transpose ? c : r, tu = a.transpose ? r : c;
+        const int t = cbase + (tv >> a.lsub) * (a.ntx >> a.lsub) + (tu >> a.lsub), m = (1 << a.lsub) - 1;
+        const int q = ((tv & m) << a.lsub) + (tu & m);
+        first = (a.item_start[t] << (2 * a.lsub)) + q;
+        end = a.item_start[t + 1] << (2 * a.lsub);
+    }
+};
+
 template <typename R, typename Acc>
 __global__ __launch_bounds__(kAssembleThreads) void k_assemble(AssembleArgs a) {
     using VT = typename C2<R>::T;
@@ -366,28 +379,17 @@ __global__ __launch_bounds__(kAssembleThreads) void k_assemble(AssembleArgs a) {
     const int wt = (blockIdx.x / nblk) % per_chan;          // tile within the written window
     const int rb = (blockIdx.x % nblk) * ar;
     const int tm = (a.tr0 + wt / a.tcols) & (a.ntx - 1), tn = (a.tc0 + wt % a.tcols) & (a.ntx - 1);
-    const int ntiles = a.ntx * a.ntx;
-    const int cbase = chan * ntiles;                        // global tiles of this channel
-    // a transposed grid's tile rows run along u, while tiles are numbered along v
-    auto tile = [&](int r, int c) { return cbase + (a.transpose ? c * a.ntx + r : r * a.ntx + c); };
+    const int cbase = chan * ((a.ntx * a.ntx) >> (2 * a.lsub));    // plan tiles of the channels before
     const int tmu = (tm - 1) & (a.ntx - 1), tnl = (tn - 1) & (a.ntx - 1);     // ntx is a power of two, as T is
     const int lbT = __builtin_ctz(static_cast<unsigned>(a.T));
     const int P = a.T + a.W - 1;
     const int halo = a.W - 1;
+    const int step = 1 << (2 * a.lsub);
     const Cell* patches = reinterpret_cast<const Cell*>(a.patches);
     VT* grid = reinterpret_cast<VT*>(a.grid) + static_cast<size_t>(chan) * a.N * a.N;
-    int src_t[4], src_dr[4], src_dc[4];
-    src_t[0] = tile(tm, tn);   src_dr[0] = 0;   src_dc[0] = 0;
-    src_t[1] = tile(tm, tnl);  src_dr[1] = 0;   src_dc[1] = a.T;
-    src_t[2] = tile(tmu, tn);  src_dr[2] = a.T; src_dc[2] = 0;
-    src_t[3] = tile(tmu, tnl); src_dr[3] = a.T; src_dc[3] = a.T;
-    int i0[4], i1[4];
+    const TilePatches src[4] = {{a, cbase, tm, tn}, {a, cbase, tm, tnl}, {a, cbase, tmu, tn}, {a, cbase, tmu, tnl}};
     bool any = false;
-    for (int s = 0; s < 4; ++s) {
-        i0[s] = a.item_start[src_t[s]];
-        i1[s] = a.item_start[src_t[s] + 1];
-        any = any || i1[s] > i0[s];
-    }
+    for (int s = 0; s < 4; ++s) any = any || src[s].end > src[s].first;
     if (a.accumulate && !any) return;                       // uniform across the workgroup
     if (!any) {                                             // no patch: zeros, two cells per store
         for (int pair = threadIdx.x; pair < ar * a.T / 2; pair += blockDim.x) {
@@ -404,8 +406,9 @@ __global__ __launch_bounds__(kAssembleThreads) void k_assemble(AssembleArgs a) {
         typename Acc::Sum sum;
         for (int s = 0; s < 4; ++s) {
             if ((s == 1 && lc >= halo) || (s == 2 && lr >= halo) || (s == 3 && (lr >= halo || lc >= halo))) continue;
-            const int pr = lr + src_dr[s], pc = lc + src_dc[s];
-            for (int it = i0[s]; it < i1[s]; ++it) sum.add(patches[static_cast<size_t>(it) * P * P + pr * P + pc]);
+            const int pr = lr + (s >= 2 ? a.T : 0), pc = lc + ((s & 1) ? a.T : 0);
+            for (int it = src[s].first; it < src[s].end; it += step)
+                sum.add(patches[static_cast<size_t>(it) * P * P + pr * P + pc]);
         }
         VT* dst = grid + static_cast<size_t>(tm * a.T + lr) * a.N + tn * a.T + lc;
         VT old;
@@ -428,23 +431,25 @@ __global__ __launch_bounds__(kAssembleThreads) void k_assemble(AssembleArgs a) {
 // skipped).
 template <typename R, typename Acc>
 __global__ __launch_bounds__(kAssembleThreads) void k_assemble_rows(AssembleArgs a) {
-    extern __shared__ int rng[];                           // [2][ntx + 1]: item_start of tile rows tm, tm - 1
+    extern __shared__ int rng[];                           // [2][ntx + 1]: item_start of plan tile rows of tm, tm - 1
     using VT = typename C2<R>::T;
     using Cell = typename Acc::Cell;
     const int per_chan = a.N / a.rows;
     const int chan = blockIdx.x / per_chan;
     const int r0 = (blockIdx.x % per_chan) * a.rows;       // first grid row (storage order)
     const int tm = r0 / a.T, rb = r0 % a.T;
-    const int ntiles = a.ntx * a.ntx;
-    const int cbase = chan * ntiles;
     const int tmu = (tm - 1) & (a.ntx - 1);
-    for (int i = threadIdx.x; i <= a.ntx; i += blockDim.x) {
-        rng[i] = a.item_start[cbase + tm * a.ntx + i];
-        rng[a.ntx + 1 + i] = a.item_start[cbase + tmu * a.ntx + i];
+    const int nptx = a.ntx >> a.lsub;                      // plan tiles per axis
+    const int cbase = chan * nptx * nptx;
+    for (int i = threadIdx.x; i <= nptx; i += blockDim.x) {
+        rng[i] = a.item_start[cbase + (tm >> a.lsub) * nptx + i];
+        rng[nptx + 1 + i] = a.item_start[cbase + (tmu >> a.lsub) * nptx + i];
     }
     __syncthreads();
     const int* own = rng;
-    const int* up = rng + a.ntx + 1;
+    const int* up = rng + nptx + 1;
+    const int sm1 = (1 << a.lsub) - 1, step = 1 << (2 * a.lsub);
+    const int qown = (tm & sm1) << a.lsub, qup = (tmu & sm1) << a.lsub;
     const int lbT = __builtin_ctz(static_cast<unsigned>(a.T));
     const int ncell = a.rows << lbT;                       // cells of one tile in the workgroup's rows
     const int P = a.T + a.W - 1;
@@ -454,10 +459,11 @@ __global__ __launch_bounds__(kAssembleThreads) void k_assemble_rows(AssembleArgs
     for (int tn = 0; tn < a.ntx; ++tn) {                   // uniform across the workgroup
         const int tl = (tn - 1) & (a.ntx - 1);
         int i0[4], i1[4];
-        i0[0] = own[tn]; i1[0] = own[tn + 1];              // own tile, left, upper, upper-left
-        i0[1] = own[tl]; i1[1] = own[tl + 1];
-        i0[2] = up[tn];  i1[2] = up[tn + 1];
-        i0[3] = up[tl];  i1[3] = up[tl + 1];
+        const int pn = tn >> a.lsub, pl = tl >> a.lsub, qn = tn & sm1, ql = tl & sm1;
+        i0[0] = own[pn] * step + qown + qn; i1[0] = own[pn + 1] * step;   // own tile, left, upper, upper-left
+        i0[1] = own[pl] * step + qown + ql; i1[1] = own[pl + 1] * step;
+        i0[2] = up[pn] * step + qup + qn;   i1[2] = up[pn + 1] * step;
+        i0[3] = up[pl] * step + qup + ql;   i1[3] = up[pl + 1] * step;
         const bool any = i1[0] > i0[0] || i1[1] > i0[1] || i1[2] > i0[2] || i1[3] > i0[3];
         if (!any) {
             if (a.accumulate) continue;
@@ -475,7 +481,8 @@ __global__ __launch_bounds__(kAssembleThreads) void k_assemble_rows(AssembleArgs
             for (int s = 0; s < 4; ++s) {
                 if ((s == 1 && lc >= halo) || (s == 2 && lr >= halo) || (s == 3 && (lr >= halo || lc >= halo))) continue;
                 const int pr = lr + (s >= 2 ? a.T : 0), pc = lc + ((s & 1) ? a.T : 0);
-                for (int it = i0[s]; it < i1[s]; ++it) sum.add(patches[static_cast<size_t>(it) * P * P + pr * P + pc]);
+                for (int it = i0[s]; it < i1[s]; it += step)
+                    sum.add(patches[static_cast<size_t>(it) * P * P + pr * P + pc]);
             }
             VT* dst = grid + static_cast<size_t>(cell >> lbT) * a.N + (tn << lbT) + lc;
             VT old;

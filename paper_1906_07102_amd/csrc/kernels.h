@@ -39,6 +39,7 @@ struct PlanGeom {
     int ntx;      // tiles per axis, N / T
     int ntiles;   // ntx * ntx, per channel
     int lb, lbx;  // log2 of T and of ntx (both powers of two)
+    int lsub;     // 1: work items are quadrants of tiles, 0: whole tiles
     int nchan;    // channels, each with its own grid; global tile = channel * ntiles + tile
     double ref;   // offset of the reference tap from the first tap
 };
@@ -51,11 +52,13 @@ constexpr int kTabLds = 0, kTabDirect = 1, kTabGlobal = 2;
 // Ms: table intervals (staged in LDS unless tab_global); degree: interpolation
 // degree. A direct table has Ms = -1 (nothing staged) and degree = -1, and coef
 // holds its FP64 expansion (the weights are computed per visibility).
+// T, ntx: edge of a work item's tile (a quadrant of the plan's tile with lsub = 1) and such tiles per axis.
 struct GridArgs {
     int N, W, T, ntx, Ms, degree;
+    int lsub;              // work items: n_items << (2 lsub)
     int tab_global;        // 1: read the coefficient table from device memory, not LDS
     const int* n_items;    // device: number of work items (written by the plan)
-    int max_items;         // most work items the plan can have (sizes the launch)
+    int max_items;         // most work items the plan can have (sizes the launch), quadrants counted
     int npatch, waves;     // LDS patches per workgroup; waves per workgroup, a multiple of it up to kMaxGridWaves
     int Ft, kb;            // packed offsets: bits of the in-interval fraction t and of the interval k
     const int4* items;     // (tile, first position, count, pieces)
@@ -74,18 +77,20 @@ constexpr int kAssembleThreads = 256;
 
 struct AssembleArgs {
     int N, W, T, ntx, nchan;
+    int lsub;                     // item_start counts items of tiles of 2^lsub T cells, each 4^lsub patches
     int tr0, tc0, trows, tcols;   // window of tiles written (rows tr0.., columns tc0.., wrapping)
     int rows;                     // tile rows per workgroup (set by the launcher)
     int rows_kernel;              // 1: whole grids by runs of rows (k_assemble_rows; set by the launcher)
     int transpose;                // 1: patches and grid are transposed (grid rows along u, tiles' rows along u)
     int accumulate;               // 1: add to the grid's values; 0: overwrite every cell of the window
-    const int* item_start;   // per tile, ntiles + 1
+    const int* item_start;   // per plan tile, ntiles + 1
     const void* patches;
     void* grid;
 };
 
 struct DegridArgs {
     int N, W, T, ntx, Ms, degree;
+    int lsub;              // work items: n_items << (2 lsub)
     int tab_global;        // 1: read the coefficient table from device memory, not LDS
     const int* n_items;
     int max_items;
@@ -149,7 +154,8 @@ hipError_t launch_plan_scatter(bool f64, bool direct, const double* uv, const in
 // off0[inv0[k]] = offk[k] for the valid visibilities (flags[2] of them).
 hipError_t launch_plan_place(bool f64, const int* inv0, const void* offk, const int* flags, int64_t nvis, void* off0,
                              hipStream_t s);
-hipError_t launch_plan_sort(bool f64, const PlanGeom& g, int4* items, int max_items, const int* flags, int nvis,
+// sub: the work items (items itself, with piece counts, or four quadrants of each).
+hipError_t launch_plan_sort(bool f64, const PlanGeom& g, const int4* items, int4* sub, int max_items, const int* flags, int nvis,
                             int lb, const void* off0, const int* perm0, void* off, int* map, int2* pieces,
                             hipStream_t s);
 hipError_t launch_plan_compose(const int* inv0, const int* pos2, int64_t nvis, int* inv, hipStream_t s);

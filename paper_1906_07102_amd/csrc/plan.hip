@@ -430,11 +430,15 @@ __global__ __launch_bounds__(kPermThreads) void k_plan_place(const int* __restri
 // takes 64 of them, reads one contiguous range. Piece order: the full
 // pieces, cell by cell (cell c's f = n / kPiece pieces at F(c) .. F(c)+f-1,
 // F an exclusive prefix of f), then the tails, longest first (a wave's lanes
-// run loops of similar length). Outputs: packed offsets `off` by entry,
-// map (pos2, tile-order position -> entry; with perm0, tile-order position ->
-// caller index, it is inv, caller index -> entry), pieces[] (first entry, length |
-// cell << 16) and items[i].w = number of pieces | (full pieces / 64) << 16.
-// Dropped visibilities (tile-order positions n_valid .. nvis) get -1.
+// run loops of similar length). With lsub = 1 the item is cut into the four
+// quadrants of its tile, laid out one after the other, and each becomes a work
+// item of its own (a 64-cell tile's patch would leave a compute unit one or
+// two workgroups). Outputs: packed offsets `off` by entry, map (pos2,
+// tile-order position -> entry; with perm0, tile-order position -> caller
+// index, it is inv, caller index -> entry), pieces[] (first entry, length |
+// cell << 16, the cell within the quadrant) and the work items sub[]: (tile or
+// quadrant, first entry, visibilities, number of pieces | (full pieces / 64)
+// << 16). Dropped visibilities (tile-order positions n_valid .. nvis) get -1.
 // Ranks within a cell follow the item's tile order in a fixed way: the item
 // is cut into `groups` contiguous chunks, one per group of waves, each with
 // its own LDS cell counters whose bases are the counts of the chunks before
@@ -442,34 +446,49 @@ __global__ __launch_bounds__(kPermThreads) void k_plan_place(const int* __restri
 // turns), so with one wave per group no barrier is needed at all.
 constexpr int kSortThreads = 512;     // (256: 124 us, 512: 111 us, 1024: 111 us on the 16.8M-visibility plan)
 template <typename R>
-__global__ __launch_bounds__(kSortThreads) void k_plan_sort_items(PlanGeom g, int4* __restrict__ items,
+__global__ __launch_bounds__(kSortThreads) void k_plan_sort_items(PlanGeom g, const int4* items, int4* sub,
                                                          const int* __restrict__ flags, int nvis, int lb, int groups,
                                                          const typename Pack<R>::T2* __restrict__ off0,
                                                          const int* __restrict__ perm0,
                                                          typename Pack<R>::T2* __restrict__ off,
                                                          int* __restrict__ map, int2* __restrict__ pieces) {
     extern __shared__ int sm[];
-    __shared__ int scan_sh[17];         // block scan
-    __shared__ int lcnt[kPiece];        // tails per length, then slot cursors
-    __shared__ int lfirst[kPiece];      // first tail slot of each length
-    __shared__ int lbase[kPiece];       // first entry of each length's tails
+    constexpr int kQ = 4;                  // most quadrants
+    __shared__ int scan_sh[17];            // block scan
+    __shared__ int fstart[kQ + 1];         // full pieces of the cells before each quadrant
+    __shared__ int lcnt[kQ][kPiece];       // per quadrant: tails per length, then slot cursors
+    __shared__ int lfirst[kQ][kPiece];     // first tail slot of each length
+    __shared__ int lbase[kQ][kPiece];      // first entry of each length's tails
+    __shared__ int npiece[kQ], etail[kQ];  // pieces of each quadrant, entries of its tails
     const int TT = g.T * g.T;
+    const int Q = 1 << (2 * g.lsub);
     const int sh = pack_cell_shift<R>(lb);            // position of the cell bits
-    int* cnt = sm;             // per-cell counts
-    int* cinfo = sm + TT;      // per cell: F(c) | (first tail entry) << 16   (both < 2^16: cap <= 16384)
-    // per group and cell: counts, then the group's next rank (one group: cnt itself, reset before placing)
-    int* gcnt = groups > 1 ? sm + 2 * TT : sm;
+    int* cnt = sm;             // per cell: count (low half); with one group, ranks given out (high half)
+    int* cinfo = sm + TT;      // per cell: first full entry | (first tail entry) << 16   (both < 2^16: cap <= 16384)
+    int* gcnt = groups > 1 ? sm + 2 * TT : sm;       // per group and cell: counts, then the group's next rank
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nwaves = blockDim.x >> 6;
     const int wpg = nwaves / groups;                 // waves per group
     const int grp = wave / wpg, wig = wave % wpg;
     int* gc = gcnt + grp * TT;
+    // Cells quadrant by quadrant: index m = quadrant (TT / Q) + i; each thread takes a run of m, so a quadrant's
+    // cells belong to `wpq` neighbouring waves (or to part of one).
+    const int lbs = lb - g.lsub, lbc = 2 * lbs;      // log2 of a quadrant's edge and cells
+    const int ms = (1 << lbs) - 1;
+    auto cell_of = [&](int m) {
+        const int k = m >> lbc, i = m & ((1 << lbc) - 1);
+        const int y = ((k >> g.lsub) << lbs) + (i >> lbs), x = ((k & ((1 << g.lsub) - 1)) << lbs) + (i & ms);
+        return (y << lb) + x;
+    };
+    const int seg = (TT + blockDim.x - 1) / blockDim.x;
+    const int c0 = threadIdx.x * seg, c1 = min(TT, c0 + seg);
+    const int wpq = max(1, TT / Q / seg / 64);
     const int n_items = flags[1];
     for (int e = flags[2] + blockIdx.x * blockDim.x + threadIdx.x; e < nvis; e += gridDim.x * blockDim.x)
         map[perm0 ? perm0[e] : e] = -1;
     for (int item = blockIdx.x; item < n_items; item += gridDim.x) {     // uniform across the workgroup
         const int4 it = items[item];
         for (int c = threadIdx.x; c < groups * TT; c += blockDim.x) gcnt[c] = 0;
-        if (threadIdx.x < kPiece) lcnt[threadIdx.x] = 0;
+        if (threadIdx.x < kQ * kPiece) lcnt[threadIdx.x / kPiece][threadIdx.x % kPiece] = 0;
         __syncthreads();
         // chunk of each group: a multiple of the group's 64 wpg lanes, the same for all groups
         const int chunk = ((it.z + groups - 1) / groups + 64 * wpg - 1) / (64 * wpg) * (64 * wpg);
@@ -492,83 +511,119 @@ __global__ __launch_bounds__(kSortThreads) void k_plan_sort_items(PlanGeom g, in
             __syncthreads();
         }
         // full pieces: exclusive prefix F over cells (each thread a run of cells); tails counted by length
-        const int seg = (TT + blockDim.x - 1) / blockDim.x;
-        const int c0 = threadIdx.x * seg, c1 = min(TT, c0 + seg);
         int fsum = 0;
-        for (int c = c0; c < c1; ++c) {
-            const int n = cnt[c];
+        for (int m = c0; m < c1; ++m) {
+            const int n = cnt[cell_of(m)];
             fsum += n / kPiece;
-            if (n % kPiece) atomicAdd(&lcnt[n % kPiece], 1);
+            if (n % kPiece) atomicAdd(&lcnt[m >> lbc][n % kPiece], 1);
         }
         int nf_all = 0;
         int F = block_excl_sum(fsum, scan_sh, &nf_all);     // (its barriers also publish lcnt)
-        for (int c = c0; c < c1; ++c) {
-            cinfo[c] = F;
-            F += cnt[c] / kPiece;
+        if (threadIdx.x == 0) fstart[Q] = nf_all;
+        for (int m = c0; m < c1; ++m) {
+            if ((m & ((1 << lbc) - 1)) == 0) fstart[m >> lbc] = F;
+            cinfo[cell_of(m)] = F;
+            F += cnt[cell_of(m)] / kPiece;
         }
         __syncthreads();
-        if (threadIdx.x < 64) {                          // tail slots and entries, longest first
-            const int nf = nf_all;
-            const int ln = threadIdx.x;
-            const int t = kPiece - 1 - ln;               // lengths 31 .. 1 on lanes 0 .. 30
-            const int n = (ln < kPiece - 1) ? lcnt[t] : 0;
+        if (wave < Q) {                                  // tail slots and entries of a quadrant, longest first
+            const int k = wave;
+            const int nf = fstart[k + 1] - fstart[k];
+            const int t = kPiece - 1 - lane;             // lengths 31 .. 1 on lanes 0 .. 30
+            const int n = (lane < kPiece - 1) ? lcnt[k][t] : 0;
             const int inc_n = wave_incl_sum(n);
             const int inc_e = wave_incl_sum(n * t);
-            if (ln < kPiece - 1) {
-                lfirst[t] = nf + inc_n - n;
-                lcnt[t] = nf + inc_n - n;
-                lbase[t] = nf * kPiece + inc_e - n * t;
+            if (lane < kPiece - 1) {
+                lfirst[k][t] = nf + inc_n - n;
+                lcnt[k][t] = nf + inc_n - n;
+                lbase[k][t] = nf * kPiece + inc_e - n * t;
             }
-            if (ln == 63) items[item].w = (nf + inc_n) | ((nf >> 6) << 16);
+            if (lane == 63) {
+                npiece[k] = nf + inc_n;
+                etail[k] = inc_e;
+            }
         }
         __syncthreads();
-        // Tail slots come from LDS cursors; the waves take them in a fixed turn (a barrier between turns), so
-        // that the layout, and with it the summation order of the gridding kernel, is the same on every run.
-        for (int w = 0; w < nwaves; ++w) {
-            if (wave == w) {
-                for (int c = c0; c < c1; ++c) {
-                    const int n = cnt[c];
-                    if (groups == 1) cnt[c] = 0;         // the group's ranks while placing
-                    if (!n) continue;
-                    const int f = n / kPiece, t = n % kPiece;
-                    const int lc = ((c >> lb) << 8) | (c & (g.T - 1));
-                    const int Fc = cinfo[c];
-                    for (int q = 0; q < f; ++q)
-                        pieces[it.y + Fc + q] = make_int2(it.y + (Fc + q) * kPiece, kPiece | (lc << 16));
-                    if (t) {
-                        const int slot = atomicAdd(&lcnt[t], 1);
-                        const int first = lbase[t] + t * (slot - lfirst[t]);
-                        pieces[it.y + slot] = make_int2(it.y + first, t | (lc << 16));
-                        cinfo[c] = Fc | (first << 16);
+        // First entry of each quadrant (its pieces start there too), and the work items.
+        int ebase[kQ];
+        {
+            int e = 0;
+#pragma unroll
+            for (int k = 0; k < kQ; ++k) {
+                ebase[k] = e;
+                if (k < Q) {
+                    const int nf = fstart[k + 1] - fstart[k], count = nf * kPiece + etail[k];
+                    if (threadIdx.x == k) {
+                        // quadrants numbered as the tiles of a grid of T / 2-cell tiles
+                        const int lt = it.x & (g.ntiles - 1), chan = it.x >> (2 * g.lbx);
+                        const int r = ((lt >> g.lbx) << g.lsub) + (k >> g.lsub);
+                        const int c = ((lt & (g.ntx - 1)) << g.lsub) + (k & ((1 << g.lsub) - 1));
+                        const int id = (((chan << (g.lbx + g.lsub)) + r) << (g.lbx + g.lsub)) + c;
+                        sub[item * Q + k] = make_int4(id, it.y + e, count, npiece[k] | ((nf >> 6) << 16));
                     }
+                    e += count;
+                }
+            }
+        }
+        // Tail slots come from LDS cursors; the waves of a quadrant take them in a fixed turn (a barrier between
+        // turns), so that the layout, and with it the summation order of the gridding kernel, is the same on every
+        // run.
+        for (int w = 0; w < wpq; ++w) {
+            if (wave % wpq == w) {
+                for (int m = c0; m < c1; ++m) {
+                    const int c = cell_of(m), n = cnt[c];
+                    if (!n) continue;
+                    const int k = m >> lbc;
+                    const int f = n / kPiece, t = n % kPiece;
+                    const int lc = (((c >> lb) & ms) << 8) | (c & ms);
+                    int eb = ebase[0];
+#pragma unroll
+                    for (int q = 1; q < kQ; ++q)
+                        if (k == q) eb = ebase[q];
+                    const int Fc = cinfo[c] - fstart[k];             // full pieces of the quadrant before this cell
+                    const int fe = eb + Fc * kPiece;
+                    for (int q = 0; q < f; ++q)
+                        pieces[it.y + eb + Fc + q] = make_int2(it.y + fe + q * kPiece, kPiece | (lc << 16));
+                    int first = 0;
+                    if (t) {
+                        const int slot = atomicAdd(&lcnt[k][t], 1);
+                        first = eb + lbase[k][t] + t * (slot - lfirst[k][t]);
+                        pieces[it.y + eb + slot] = make_int2(it.y + first, t | (lc << 16));
+                    }
+                    cinfo[c] = fe | (first << 16);
                 }
             }
             __syncthreads();
         }
-        const int nf = nf_all;
         const int rounds = chunk / (64 * wpg);
         for (int rd = 0; rd < rounds; ++rd) {            // uniform across the workgroup
             const int e = g0 + rd * 64 * wpg + wig * 64 + lane;
             const bool live = e < g1;
             typename Pack<R>::T2 r;
-            int c = 0, rank = 0;
+            int c = 0, rank = 0, n = 0;
             if (live) {
                 r = off0[it.y + e];
                 c = (static_cast<int>(r.y >> sh) << lb) + static_cast<int>(r.x >> sh);
             }
             if (wpg == 1) {                              // the group's counters are the wave's own
-                if (live) rank = atomicAdd(&gc[c], 1);
+                if (live) {
+                    rank = atomicAdd(&gc[c], 1);
+                    n = cnt[c];
+                }
             } else {
                 for (int w = 0; w < wpg; ++w) {          // uniform: every group has wpg waves
-                    if (wig == w && live) rank = atomicAdd(&gc[c], 1);
+                    if (wig == w && live) {
+                        n = atomicAdd(&gc[c], 1 << 16);  // one group: gc is cnt
+                        rank = n >> 16;
+                        n &= 0xffff;
+                    }
                     __syncthreads();
                 }
             }
             if (live) {
                 const int ci = cinfo[c];
-                const int Fc = ci & 0xffff;
-                const int f = ((c + 1 < TT) ? (cinfo[c + 1] & 0xffff) : nf) - Fc;
-                const int pos = rank < f * kPiece ? Fc * kPiece + rank : (ci >> 16) + rank - f * kPiece;
+                const int full = n & ~(kPiece - 1);
+                const int pos = rank < full ? (ci & 0xffff) + rank : (ci >> 16) + rank - full;
                 const int dst = it.y + pos;
                 off[dst] = r;
                 map[perm0 ? perm0[it.y + e] : it.y + e] = dst;
@@ -734,7 +789,7 @@ hipError_t launch_plan_place(bool f64, const int* inv0, const void* offk, const 
     return hipGetLastError();
 }
 
-hipError_t launch_plan_sort(bool f64, const PlanGeom& g, int4* items, int max_items, const int* flags, int nvis,
+hipError_t launch_plan_sort(bool f64, const PlanGeom& g, const int4* items, int4* sub, int max_items, const int* flags, int nvis,
                             int lb, const void* off0, const int* perm0, void* off, int* map, int2* pieces,
                             hipStream_t s) {
     // One counter group per wave while the counters fit in 40 KB with the per-cell arrays (T <= 32),
@@ -745,11 +800,11 @@ hipError_t launch_plan_sort(bool f64, const PlanGeom& g, int4* items, int max_it
     const size_t shm = (2 + (groups > 1 ? groups : 0)) * TT * sizeof(int);
     const unsigned nb = static_cast<unsigned>(std::max(1, std::min(max_items, 8192)));
     if (f64)
-        hipLaunchKernelGGL(dev::k_plan_sort_items<double>, dim3(nb), dim3(dev::kSortThreads), shm, s, g, items, flags, nvis, lb, groups,
+        hipLaunchKernelGGL(dev::k_plan_sort_items<double>, dim3(nb), dim3(dev::kSortThreads), shm, s, g, items, sub, flags, nvis, lb, groups,
                            reinterpret_cast<const ulonglong2*>(off0), perm0, reinterpret_cast<ulonglong2*>(off), map,
                            pieces);
     else
-        hipLaunchKernelGGL(dev::k_plan_sort_items<float>, dim3(nb), dim3(dev::kSortThreads), shm, s, g, items, flags, nvis, lb, groups,
+        hipLaunchKernelGGL(dev::k_plan_sort_items<float>, dim3(nb), dim3(dev::kSortThreads), shm, s, g, items, sub, flags, nvis, lb, groups,
                            reinterpret_cast<const uint2*>(off0), perm0, reinterpret_cast<uint2*>(off), map,
                            pieces);
     return hipGetLastError();
