@@ -102,7 +102,8 @@ hipError_t launch_degrid_w(const DegridArgs& a, hipStream_t s) {
     const void* fn = reinterpret_cast<const void*>(&dev::k_degrid_items<R, W, kTab>);
     static const hipError_t attr = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxDynLds);
     if (attr != hipSuccess) return attr;
-    const int nb = std::min(a.max_items, resident_blocks(shm));
+    static std::atomic<uint64_t> resident{0};
+    const int nb = std::min(a.max_items, resident_blocks(fn, dev::kDegridThreads, shm, resident));
     hipLaunchKernelGGL((dev::k_degrid_items<R, W, kTab>), dim3(nb), dim3(dev::kDegridThreads), shm, s, a);
     return hipGetLastError();
 }

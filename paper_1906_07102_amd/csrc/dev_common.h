@@ -28,6 +28,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cstdint>
 
 #include "kernels.h"
@@ -274,21 +275,31 @@ __device__ __forceinline__ void load_run(const T* __restrict__ p, T* out) {
 
 }  // namespace dev
 
-// Workgroups of a persistent launch: as many as the current device's compute
-// units hold at once by LDS (at most 8 per unit). More than fit only wait for
-// a slot and then find the work list drained, so the estimate need not be
-// exact.
-inline int resident_blocks(size_t shm) {
-    static int cus[64] = {0};
+// Workgroups of a persistent launch of `fn` (threads, dynamic LDS bytes): as many as the current device holds at once.
+// Each takes its first item by its index and stages the table once, so a workgroup beyond those would run its item
+// after the others have drained the list. `cache` remembers the last answer for one kernel, as threads, LDS and count
+// packed in a word.
+inline int resident_blocks(const void* fn, int threads, size_t shm, std::atomic<uint64_t>& cache) {
+    static std::atomic<int> cus[64];
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
-    if (cus[dev] <= 0) {
-        int n = 0;
+    int n = cus[dev].load(std::memory_order_relaxed);
+    if (n <= 0) {
         if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
-        cus[dev] = n;
+        cus[dev].store(n, std::memory_order_relaxed);
     }
-    const int by_lds = shm > 0 ? static_cast<int>((160 * 1024) / shm) : 8;
-    return cus[dev] * std::max(1, std::min(8, by_lds));
+    const uint64_t key = (static_cast<uint64_t>(threads) << 40) | (static_cast<uint64_t>(shm) << 8);
+    uint64_t c = cache.load(std::memory_order_relaxed);
+    if ((c & ~uint64_t{0xff}) != key || (c & 0xff) == 0) {
+        int per = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, fn, threads, shm) != hipSuccess || per < 1) {
+            (void)hipGetLastError();
+            per = 1;
+        }
+        c = key | static_cast<uint64_t>(std::min(per, 32));
+        cache.store(c, std::memory_order_relaxed);
+    }
+    return n * static_cast<int>(c & 0xff);
 }
 
 }  // namespace lmg

@@ -505,7 +505,8 @@ hipError_t launch_grid_w(const GridArgs& a, hipStream_t s) {
     const void* fn = reinterpret_cast<const void*>(&dev::k_grid_items<R, Acc, W, kTab>);
     static const hipError_t attr = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxDynLds);
     if (attr != hipSuccess) return attr;
-    const int nb = std::min(a.max_items, resident_blocks(shm));
+    static std::atomic<uint64_t> resident{0};
+    const int nb = std::min(a.max_items, resident_blocks(fn, 64 * a.waves, shm, resident));
     hipLaunchKernelGGL((dev::k_grid_items<R, Acc, W, kTab>), dim3(nb), dim3(64 * a.waves), shm, s, a);
     return hipGetLastError();
 }
