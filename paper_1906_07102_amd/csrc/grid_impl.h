@@ -368,10 +368,63 @@ struct TilePatches {
     }
 };
 
-template <typename R, typename Acc>
-__global__ __launch_bounds__(kAssembleThreads) void k_assemble(AssembleArgs a) {
+// Cells of one tile, rows rb .. of it (ncell cells of them), written from the patches that cover them (own tile, left,
+// upper, upper-left: numbers first[s], first[s] + step, ... before end[s]); dst: the first of them. A thread takes KC
+// cells a few rows apart and a batch of patches at a time, all loads issued before the first is added: what bounds the
+// occupied tiles is the latency of a cell's chain of patches, not their bytes (one 4096^2 grid of 16.8M visibilities
+// 64 us with one cell per thread, 51 with four; its occupied band 32, 27 with two; 4.2M on 8192^2 in FP32 164, 143).
+template <typename R, typename Acc, int KC>
+__device__ __forceinline__ void tile_cells(const AssembleArgs& a, typename C2<R>::T* dst, int rb, int ncell, int lbT,
+                                           const int* first, const int* end, int step) {
     using VT = typename C2<R>::T;
     using Cell = typename Acc::Cell;
+    constexpr int kU = KC >= 4 ? 1 : 4 / KC;               // patches per batch
+    const int P = a.T + a.W - 1, halo = a.W - 1;
+    const Cell* patches = reinterpret_cast<const Cell*>(a.patches);
+    const int lc = threadIdx.x & (a.T - 1);                // 256 threads: whole rows of a tile
+    for (int base = threadIdx.x; base < ncell; base += KC * kAssembleThreads) {
+        typename Acc::Sum sum[KC];
+        VT old[KC];
+        bool on[KC];
+        int lr[KC];
+#pragma unroll
+        for (int k = 0; k < KC; ++k) {
+            const int cell = base + k * kAssembleThreads;
+            on[k] = cell < ncell;
+            lr[k] = rb + (cell >> lbT);
+            old[k].x = 0;
+            old[k].y = 0;
+            if (a.accumulate && on[k]) old[k] = dst[static_cast<size_t>(cell >> lbT) * a.N + lc];
+        }
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            if ((s & 1) && lc >= halo) continue;
+            const int pc = lc + ((s & 1) ? a.T : 0);
+            for (int it = first[s]; it < end[s]; it += kU * step) {
+                Cell c[kU][KC];
+#pragma unroll
+                for (int u = 0; u < kU; ++u)
+#pragma unroll
+                    for (int k = 0; k < KC; ++k)
+                        if (it + u * step < end[s] && on[k] && (s < 2 || lr[k] < halo))
+                            c[u][k] = patches[(static_cast<size_t>(it + u * step) * P + lr[k] + (s >= 2 ? a.T : 0)) * P + pc];
+#pragma unroll
+                for (int u = 0; u < kU; ++u)
+#pragma unroll
+                    for (int k = 0; k < KC; ++k)
+                        if (it + u * step < end[s] && on[k] && (s < 2 || lr[k] < halo)) sum[k].add(c[u][k]);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < KC; ++k)
+            if (on[k])
+                dst[static_cast<size_t>((base + k * kAssembleThreads) >> lbT) * a.N + lc] = sum[k].value(old[k]);
+    }
+}
+
+template <typename R, typename Acc, int KC>
+__global__ __launch_bounds__(kAssembleThreads) void k_assemble(AssembleArgs a) {
+    using VT = typename C2<R>::T;
     const int ar = a.rows;
     const int nblk = a.T / ar;
     const int per_chan = a.trows * a.tcols;
@@ -382,10 +435,7 @@ __global__ __launch_bounds__(kAssembleThreads) void k_assemble(AssembleArgs a) {
     const int cbase = chan * ((a.ntx * a.ntx) >> (2 * a.lsub));    // plan tiles of the channels before
     const int tmu = (tm - 1) & (a.ntx - 1), tnl = (tn - 1) & (a.ntx - 1);     // ntx is a power of two, as T is
     const int lbT = __builtin_ctz(static_cast<unsigned>(a.T));
-    const int P = a.T + a.W - 1;
-    const int halo = a.W - 1;
     const int step = 1 << (2 * a.lsub);
-    const Cell* patches = reinterpret_cast<const Cell*>(a.patches);
     VT* grid = reinterpret_cast<VT*>(a.grid) + static_cast<size_t>(chan) * a.N * a.N;
     const TilePatches src[4] = {{a, cbase, tm, tn}, {a, cbase, tm, tnl}, {a, cbase, tmu, tn}, {a, cbase, tmu, tnl}};
     bool any = false;
@@ -401,22 +451,10 @@ __global__ __launch_bounds__(kAssembleThreads) void k_assemble(AssembleArgs a) {
         }
         return;
     }
-    for (int cell = threadIdx.x; cell < ar * a.T; cell += blockDim.x) {
-        const int lr = rb + (cell >> lbT), lc = cell & (a.T - 1);
-        typename Acc::Sum sum;
-        for (int s = 0; s < 4; ++s) {
-            if ((s == 1 && lc >= halo) || (s == 2 && lr >= halo) || (s == 3 && (lr >= halo || lc >= halo))) continue;
-            const int pr = lr + (s >= 2 ? a.T : 0), pc = lc + ((s & 1) ? a.T : 0);
-            for (int it = src[s].first; it < src[s].end; it += step)
-                sum.add(patches[static_cast<size_t>(it) * P * P + pr * P + pc]);
-        }
-        VT* dst = grid + static_cast<size_t>(tm * a.T + lr) * a.N + tn * a.T + lc;
-        VT old;
-        old.x = 0;
-        old.y = 0;
-        if (a.accumulate) old = *dst;
-        *dst = sum.value(old);
-    }
+    const int first[4] = {src[0].first, src[1].first, src[2].first, src[3].first};
+    const int end[4] = {src[0].end, src[1].end, src[2].end, src[3].end};
+    tile_cells<R, Acc, KC>(a, grid + static_cast<size_t>(tm * a.T + rb) * a.N + tn * a.T, rb, ar << lbT, lbT, first, end,
+                           step);
 }
 
 // Whole grids of many channels: one workgroup per a.rows consecutive grid
@@ -429,11 +467,10 @@ __global__ __launch_bounds__(kAssembleThreads) void k_assemble(AssembleArgs a) {
 // k_assemble, so the two give the same bits; overwrite (a tile without
 // patches takes zeros two cells per store), or accumulate (such a tile is
 // skipped).
-template <typename R, typename Acc>
+template <typename R, typename Acc, int KC>
 __global__ __launch_bounds__(kAssembleThreads) void k_assemble_rows(AssembleArgs a) {
     extern __shared__ int rng[];                           // [2][ntx + 1]: item_start of plan tile rows of tm, tm - 1
     using VT = typename C2<R>::T;
-    using Cell = typename Acc::Cell;
     const int per_chan = a.N / a.rows;
     const int chan = blockIdx.x / per_chan;
     const int r0 = (blockIdx.x % per_chan) * a.rows;       // first grid row (storage order)
@@ -452,9 +489,6 @@ __global__ __launch_bounds__(kAssembleThreads) void k_assemble_rows(AssembleArgs
     const int qown = (tm & sm1) << a.lsub, qup = (tmu & sm1) << a.lsub;
     const int lbT = __builtin_ctz(static_cast<unsigned>(a.T));
     const int ncell = a.rows << lbT;                       // cells of one tile in the workgroup's rows
-    const int P = a.T + a.W - 1;
-    const int halo = a.W - 1;
-    const Cell* patches = reinterpret_cast<const Cell*>(a.patches);
     VT* grid = reinterpret_cast<VT*>(a.grid) + static_cast<size_t>(chan) * a.N * a.N + static_cast<size_t>(r0) * a.N;
     for (int tn = 0; tn < a.ntx; ++tn) {                   // uniform across the workgroup
         const int tl = (tn - 1) & (a.ntx - 1);
@@ -475,22 +509,7 @@ __global__ __launch_bounds__(kAssembleThreads) void k_assemble_rows(AssembleArgs
             }
             continue;
         }
-        for (int cell = threadIdx.x; cell < ncell; cell += blockDim.x) {
-            const int lr = rb + (cell >> lbT), lc = cell & (a.T - 1);
-            typename Acc::Sum sum;
-            for (int s = 0; s < 4; ++s) {
-                if ((s == 1 && lc >= halo) || (s == 2 && lr >= halo) || (s == 3 && (lr >= halo || lc >= halo))) continue;
-                const int pr = lr + (s >= 2 ? a.T : 0), pc = lc + ((s & 1) ? a.T : 0);
-                for (int it = i0[s]; it < i1[s]; it += step)
-                    sum.add(patches[static_cast<size_t>(it) * P * P + pr * P + pc]);
-            }
-            VT* dst = grid + static_cast<size_t>(cell >> lbT) * a.N + (tn << lbT) + lc;
-            VT old;
-            old.x = 0;
-            old.y = 0;
-            if (a.accumulate) old = *dst;
-            *dst = sum.value(old);
-        }
+        tile_cells<R, Acc, KC>(a, grid + (tn << lbT), rb, ncell, lbT, i0, i1, step);
     }
 }
 
@@ -524,16 +543,23 @@ hipError_t dispatch_grid(const GridArgs& a, hipStream_t s) {
     }
     return hipErrorInvalidValue;
 }
-template <typename R, typename Acc>
-hipError_t assemble(const AssembleArgs& a, unsigned nt, hipStream_t s) {
+template <typename R, typename Acc, int KC>
+hipError_t launch_assemble_kc(const AssembleArgs& a, unsigned nt, hipStream_t s) {
     if (a.rows_kernel) {
         const unsigned nb = static_cast<unsigned>(a.nchan) * static_cast<unsigned>(a.N / a.rows);
         const size_t shm = 2 * (static_cast<size_t>(a.ntx) + 1) * sizeof(int);
-        hipLaunchKernelGGL((dev::k_assemble_rows<R, Acc>), dim3(nb), dim3(kAssembleThreads), shm, s, a);
-        return hipGetLastError();
+        hipLaunchKernelGGL((dev::k_assemble_rows<R, Acc, KC>), dim3(nb), dim3(kAssembleThreads), shm, s, a);
+    } else {
+        hipLaunchKernelGGL((dev::k_assemble<R, Acc, KC>), dim3(nt), dim3(kAssembleThreads), 0, s, a);
     }
-    hipLaunchKernelGGL((dev::k_assemble<R, Acc>), dim3(nt), dim3(kAssembleThreads), 0, s, a);
     return hipGetLastError();
+}
+template <typename R, typename Acc>
+hipError_t assemble(const AssembleArgs& a, unsigned nt, hipStream_t s) {
+    const int cells = a.rows * a.T;                         // of one tile per workgroup
+    if (cells >= 4 * kAssembleThreads) return launch_assemble_kc<R, Acc, 4>(a, nt, s);
+    if (cells >= 2 * kAssembleThreads) return launch_assemble_kc<R, Acc, 2>(a, nt, s);
+    return launch_assemble_kc<R, Acc, 1>(a, nt, s);
 }
 }  // namespace grid_impl
 }  // namespace lmg
