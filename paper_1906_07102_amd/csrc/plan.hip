@@ -444,8 +444,13 @@ __global__ __launch_bounds__(kPermThreads) void k_plan_place(const int* __restri
 // its own LDS cell counters whose bases are the counts of the chunks before
 // it; the waves of one group take their turns in order (a barrier between
 // turns), so with one wave per group no barrier is needed at all.
-constexpr int kSortThreads = 512;     // (256: 124 us, 512: 111 us, 1024: 111 us on the 16.8M-visibility plan)
-template <typename R>
+// What bounds it is latency: an item's phases follow one another, and a dense item's rounds of load, LDS rank and store
+// (a plan of few items runs as long as its densest). So a lane has kSortU entries in flight (16.8M visibilities on
+// 4096^2: 1 144 us, 2 124, 4 119, 8 146, where the registers cost a workgroup), and the tails' slots come from cursors of
+// each wave, not in turns (105 us; 201,600 on 1024^2: 32 -> 23 us). 256 threads: 108 and 26 us; 128: 120 and 36.
+constexpr int kSortU = 4;
+constexpr int kSortThreads = 512;
+template <typename R, int kLsub>
 __global__ __launch_bounds__(kSortThreads) void k_plan_sort_items(PlanGeom g, const int4* items, int4* sub,
                                                          const int* __restrict__ flags, int nvis, int lb, int groups,
                                                          const typename Pack<R>::T2* __restrict__ off0,
@@ -453,15 +458,14 @@ __global__ __launch_bounds__(kSortThreads) void k_plan_sort_items(PlanGeom g, co
                                                          typename Pack<R>::T2* __restrict__ off,
                                                          int* __restrict__ map, int2* __restrict__ pieces) {
     extern __shared__ int sm[];
-    constexpr int kQ = 4;                  // most quadrants
+    constexpr int Q = 1 << (2 * kLsub);    // items cut from one
     __shared__ int scan_sh[17];            // block scan
-    __shared__ int fstart[kQ + 1];         // full pieces of the cells before each quadrant
-    __shared__ int lcnt[kQ][kPiece];       // per quadrant: tails per length, then slot cursors
-    __shared__ int lfirst[kQ][kPiece];     // first tail slot of each length
-    __shared__ int lbase[kQ][kPiece];      // first entry of each length's tails
-    __shared__ int npiece[kQ], etail[kQ];  // pieces of each quadrant, entries of its tails
+    __shared__ int fstart[Q + 1];         // full pieces of the cells before each quadrant
+    __shared__ int lcnt[kSortThreads / 64][kPiece];   // per wave: tails per length of its cells, then slot cursors
+    __shared__ int lfirst[Q][kPiece];     // first tail slot of each length
+    __shared__ int lbase[Q][kPiece];      // first entry of each length's tails
+    __shared__ int npiece[Q], etail[Q];  // pieces of each quadrant, entries of its tails
     const int TT = g.T * g.T;
-    const int Q = 1 << (2 * g.lsub);
     const int sh = pack_cell_shift<R>(lb);            // position of the cell bits
     int* cnt = sm;             // per cell: count (low half); with one group, ranks given out (high half)
     int* cinfo = sm + TT;      // per cell: first full entry | (first tail entry) << 16   (both < 2^16: cap <= 16384)
@@ -472,11 +476,12 @@ __global__ __launch_bounds__(kSortThreads) void k_plan_sort_items(PlanGeom g, co
     int* gc = gcnt + grp * TT;
     // Cells quadrant by quadrant: index m = quadrant (TT / Q) + i; each thread takes a run of m, so a quadrant's
     // cells belong to `wpq` neighbouring waves (or to part of one).
-    const int lbs = lb - g.lsub, lbc = 2 * lbs;      // log2 of a quadrant's edge and cells
+    const int lbs = lb - kLsub, lbc = 2 * lbs;      // log2 of a quadrant's edge and cells
     const int ms = (1 << lbs) - 1;
     auto cell_of = [&](int m) {
+        if constexpr (kLsub == 0) return m;
         const int k = m >> lbc, i = m & ((1 << lbc) - 1);
-        const int y = ((k >> g.lsub) << lbs) + (i >> lbs), x = ((k & ((1 << g.lsub) - 1)) << lbs) + (i & ms);
+        const int y = ((k >> kLsub) << lbs) + (i >> lbs), x = ((k & ((1 << kLsub) - 1)) << lbs) + (i & ms);
         return (y << lb) + x;
     };
     const int seg = (TT + blockDim.x - 1) / blockDim.x;
@@ -488,14 +493,24 @@ __global__ __launch_bounds__(kSortThreads) void k_plan_sort_items(PlanGeom g, co
     for (int item = blockIdx.x; item < n_items; item += gridDim.x) {     // uniform across the workgroup
         const int4 it = items[item];
         for (int c = threadIdx.x; c < groups * TT; c += blockDim.x) gcnt[c] = 0;
-        if (threadIdx.x < kQ * kPiece) lcnt[threadIdx.x / kPiece][threadIdx.x % kPiece] = 0;
+        if (lane < kPiece) lcnt[wave][lane] = 0;
         __syncthreads();
         // chunk of each group: a multiple of the group's 64 wpg lanes, the same for all groups
         const int chunk = ((it.z + groups - 1) / groups + 64 * wpg - 1) / (64 * wpg) * (64 * wpg);
         const int g0 = grp * chunk, g1 = min(it.z, g0 + chunk);
-        for (int e = g0 + wig * 64 + lane; e < g1; e += 64 * wpg) {
-            const typename Pack<R>::T2 r = off0[it.y + e];
-            atomicAdd(&gc[(static_cast<int>(r.y >> sh) << lb) + static_cast<int>(r.x >> sh)], 1);
+        // entries of a lane per round, all loaded before the first is used: e0 + 64 u, u < ku (waves of a group take
+        // runs of 64 ku in turn, so a round's entries are in order of wave, u, lane)
+        const int ku = min(kSortU, chunk / (64 * wpg));
+        const int step = 64 * wpg * ku;
+        for (int e0 = g0 + wig * 64 * ku + lane; e0 < g1; e0 += step) {
+            typename Pack<R>::T2 r[kSortU];
+#pragma unroll
+            for (int u = 0; u < kSortU; ++u)
+                if (u < ku && e0 + 64 * u < g1) r[u] = off0[it.y + e0 + 64 * u];
+#pragma unroll
+            for (int u = 0; u < kSortU; ++u)
+                if (u < ku && e0 + 64 * u < g1)
+                    atomicAdd(&gc[(static_cast<int>(r[u].y >> sh) << lb) + static_cast<int>(r[u].x >> sh)], 1);
         }
         __syncthreads();
         if (groups > 1) {
@@ -515,7 +530,7 @@ __global__ __launch_bounds__(kSortThreads) void k_plan_sort_items(PlanGeom g, co
         for (int m = c0; m < c1; ++m) {
             const int n = cnt[cell_of(m)];
             fsum += n / kPiece;
-            if (n % kPiece) atomicAdd(&lcnt[m >> lbc][n % kPiece], 1);
+            if (n % kPiece) atomicAdd(&lcnt[wave][n % kPiece], 1);
         }
         int nf_all = 0;
         int F = block_excl_sum(fsum, scan_sh, &nf_all);     // (its barriers also publish lcnt)
@@ -530,12 +545,19 @@ __global__ __launch_bounds__(kSortThreads) void k_plan_sort_items(PlanGeom g, co
             const int k = wave;
             const int nf = fstart[k + 1] - fstart[k];
             const int t = kPiece - 1 - lane;             // lengths 31 .. 1 on lanes 0 .. 30
-            const int n = (lane < kPiece - 1) ? lcnt[k][t] : 0;
+            int before[kSortThreads / 64], n = 0;        // tails of this length in the quadrant's waves before each
+#pragma unroll
+            for (int w = 0; w < kSortThreads / 64; ++w) {
+                before[w] = n;
+                if (lane < kPiece - 1 && w < wpq) n += lcnt[k * wpq + w][t];
+            }
             const int inc_n = wave_incl_sum(n);
             const int inc_e = wave_incl_sum(n * t);
             if (lane < kPiece - 1) {
                 lfirst[k][t] = nf + inc_n - n;
-                lcnt[k][t] = nf + inc_n - n;
+#pragma unroll
+                for (int w = 0; w < kSortThreads / 64; ++w)
+                    if (w < wpq) lcnt[k * wpq + w][t] = nf + inc_n - n + before[w];
                 lbase[k][t] = nf * kPiece + inc_e - n * t;
             }
             if (lane == 63) {
@@ -545,88 +567,97 @@ __global__ __launch_bounds__(kSortThreads) void k_plan_sort_items(PlanGeom g, co
         }
         __syncthreads();
         // First entry of each quadrant (its pieces start there too), and the work items.
-        int ebase[kQ];
+        int ebase[Q];
         {
             int e = 0;
 #pragma unroll
-            for (int k = 0; k < kQ; ++k) {
+            for (int k = 0; k < Q; ++k) {
                 ebase[k] = e;
-                if (k < Q) {
+                {
                     const int nf = fstart[k + 1] - fstart[k], count = nf * kPiece + etail[k];
                     if (threadIdx.x == k) {
                         // quadrants numbered as the tiles of a grid of T / 2-cell tiles
                         const int lt = it.x & (g.ntiles - 1), chan = it.x >> (2 * g.lbx);
-                        const int r = ((lt >> g.lbx) << g.lsub) + (k >> g.lsub);
-                        const int c = ((lt & (g.ntx - 1)) << g.lsub) + (k & ((1 << g.lsub) - 1));
-                        const int id = (((chan << (g.lbx + g.lsub)) + r) << (g.lbx + g.lsub)) + c;
+                        const int r = ((lt >> g.lbx) << kLsub) + (k >> kLsub);
+                        const int c = ((lt & (g.ntx - 1)) << kLsub) + (k & ((1 << kLsub) - 1));
+                        const int id = (((chan << (g.lbx + kLsub)) + r) << (g.lbx + kLsub)) + c;
                         sub[item * Q + k] = make_int4(id, it.y + e, count, npiece[k] | ((nf >> 6) << 16));
                     }
                     e += count;
                 }
             }
         }
-        // Tail slots come from LDS cursors; the waves of a quadrant take them in a fixed turn (a barrier between
-        // turns), so that the layout, and with it the summation order of the gridding kernel, is the same on every
-        // run.
-        for (int w = 0; w < wpq; ++w) {
-            if (wave % wpq == w) {
-                for (int m = c0; m < c1; ++m) {
-                    const int c = cell_of(m), n = cnt[c];
-                    if (!n) continue;
-                    const int k = m >> lbc;
-                    const int f = n / kPiece, t = n % kPiece;
-                    const int lc = (((c >> lb) & ms) << 8) | (c & ms);
-                    int eb = ebase[0];
+        // Tail slots come from the wave's own LDS cursors, so that the layout, and with it the summation order of the
+        // gridding kernel, is the same on every run.
+        for (int m = c0; m < c1; ++m) {
+            const int c = cell_of(m), n = cnt[c];
+            if (!n) continue;
+            const int k = m >> lbc;
+            const int f = n / kPiece, t = n % kPiece;
+            const int lc = (((c >> lb) & ms) << 8) | (c & ms);
+            int eb = ebase[0];
 #pragma unroll
-                    for (int q = 1; q < kQ; ++q)
-                        if (k == q) eb = ebase[q];
-                    const int Fc = cinfo[c] - fstart[k];             // full pieces of the quadrant before this cell
-                    const int fe = eb + Fc * kPiece;
-                    for (int q = 0; q < f; ++q)
-                        pieces[it.y + eb + Fc + q] = make_int2(it.y + fe + q * kPiece, kPiece | (lc << 16));
-                    int first = 0;
-                    if (t) {
-                        const int slot = atomicAdd(&lcnt[k][t], 1);
-                        first = eb + lbase[k][t] + t * (slot - lfirst[k][t]);
-                        pieces[it.y + eb + slot] = make_int2(it.y + first, t | (lc << 16));
-                    }
-                    cinfo[c] = fe | (first << 16);
-                }
+            for (int q = 1; q < Q; ++q)
+                if (k == q) eb = ebase[q];
+            const int Fc = cinfo[c] - fstart[k];             // full pieces of the quadrant before this cell
+            const int fe = eb + Fc * kPiece;
+            for (int q = 0; q < f; ++q)
+                pieces[it.y + eb + Fc + q] = make_int2(it.y + fe + q * kPiece, kPiece | (lc << 16));
+            int first = 0;
+            if (t) {
+                const int slot = atomicAdd(&lcnt[wave][t], 1);
+                first = eb + lbase[k][t] + t * (slot - lfirst[k][t]);
+                pieces[it.y + eb + slot] = make_int2(it.y + first, t | (lc << 16));
             }
-            __syncthreads();
+            cinfo[c] = fe | (first << 16);
         }
-        const int rounds = chunk / (64 * wpg);
+        __syncthreads();
+        const int rounds = (chunk + step - 1) / step;
         for (int rd = 0; rd < rounds; ++rd) {            // uniform across the workgroup
-            const int e = g0 + rd * 64 * wpg + wig * 64 + lane;
-            const bool live = e < g1;
-            typename Pack<R>::T2 r;
-            int c = 0, rank = 0, n = 0;
-            if (live) {
-                r = off0[it.y + e];
-                c = (static_cast<int>(r.y >> sh) << lb) + static_cast<int>(r.x >> sh);
-            }
-            if (wpg == 1) {                              // the group's counters are the wave's own
-                if (live) {
-                    rank = atomicAdd(&gc[c], 1);
-                    n = cnt[c];
+            const int e0 = g0 + rd * step + wig * 64 * ku + lane;
+            typename Pack<R>::T2 r[kSortU];
+            int c[kSortU], rank[kSortU], n[kSortU], from[kSortU];
+#pragma unroll
+            for (int u = 0; u < kSortU; ++u) {
+                from[u] = -1;
+                if (u < ku && e0 + 64 * u < g1) {
+                    r[u] = off0[it.y + e0 + 64 * u];
+                    from[u] = perm0 ? perm0[it.y + e0 + 64 * u] : it.y + e0 + 64 * u;
                 }
+            }
+#pragma unroll
+            for (int u = 0; u < kSortU; ++u)
+                c[u] = from[u] < 0 ? 0 : (static_cast<int>(r[u].y >> sh) << lb) + static_cast<int>(r[u].x >> sh);
+            if (wpg == 1) {                              // the group's counters are the wave's own
+#pragma unroll
+                for (int u = 0; u < kSortU; ++u)
+                    if (from[u] >= 0) {
+                        rank[u] = atomicAdd(&gc[c[u]], 1);
+                        n[u] = cnt[c[u]];
+                    }
             } else {
                 for (int w = 0; w < wpg; ++w) {          // uniform: every group has wpg waves
-                    if (wig == w && live) {
-                        n = atomicAdd(&gc[c], 1 << 16);  // one group: gc is cnt
-                        rank = n >> 16;
-                        n &= 0xffff;
+                    if (wig == w) {
+#pragma unroll
+                        for (int u = 0; u < kSortU; ++u)
+                            if (from[u] >= 0) {
+                                n[u] = atomicAdd(&gc[c[u]], 1 << 16);  // one group: gc is cnt
+                                rank[u] = n[u] >> 16;
+                                n[u] &= 0xffff;
+                            }
                     }
                     __syncthreads();
                 }
             }
-            if (live) {
-                const int ci = cinfo[c];
-                const int full = n & ~(kPiece - 1);
-                const int pos = rank < full ? (ci & 0xffff) + rank : (ci >> 16) + rank - full;
+#pragma unroll
+            for (int u = 0; u < kSortU; ++u) {
+                if (from[u] < 0) continue;
+                const int ci = cinfo[c[u]];
+                const int full = n[u] & ~(kPiece - 1);
+                const int pos = rank[u] < full ? (ci & 0xffff) + rank[u] : (ci >> 16) + rank[u] - full;
                 const int dst = it.y + pos;
-                off[dst] = r;
-                map[perm0 ? perm0[it.y + e] : it.y + e] = dst;
+                off[dst] = r[u];
+                map[from[u]] = dst;
             }
         }
         __syncthreads();                                 // LDS counters are reused by the next item
@@ -789,6 +820,16 @@ hipError_t launch_plan_place(bool f64, const int* inv0, const void* offk, const 
     return hipGetLastError();
 }
 
+namespace {
+template <typename R, int kLsub>
+void sort_items(unsigned nb, size_t shm, const PlanGeom& g, const int4* items, int4* sub, const int* flags, int nvis, int lb,
+                int groups, const void* off0, const int* perm0, void* off, int* map, int2* pieces, hipStream_t s) {
+    using P2 = typename dev::Pack<R>::T2;
+    hipLaunchKernelGGL((dev::k_plan_sort_items<R, kLsub>), dim3(nb), dim3(dev::kSortThreads), shm, s, g, items, sub, flags,
+                       nvis, lb, groups, reinterpret_cast<const P2*>(off0), perm0, reinterpret_cast<P2*>(off), map, pieces);
+}
+}  // namespace
+
 hipError_t launch_plan_sort(bool f64, const PlanGeom& g, const int4* items, int4* sub, int max_items, const int* flags, int nvis,
                             int lb, const void* off0, const int* perm0, void* off, int* map, int2* pieces,
                             hipStream_t s) {
@@ -799,14 +840,10 @@ hipError_t launch_plan_sort(bool f64, const PlanGeom& g, const int4* items, int4
     const int groups = (2 + waves) * TT * sizeof(int) <= 40 * 1024 ? waves : 1;
     const size_t shm = (2 + (groups > 1 ? groups : 0)) * TT * sizeof(int);
     const unsigned nb = static_cast<unsigned>(std::max(1, std::min(max_items, 8192)));
-    if (f64)
-        hipLaunchKernelGGL(dev::k_plan_sort_items<double>, dim3(nb), dim3(dev::kSortThreads), shm, s, g, items, sub, flags, nvis, lb, groups,
-                           reinterpret_cast<const ulonglong2*>(off0), perm0, reinterpret_cast<ulonglong2*>(off), map,
-                           pieces);
-    else
-        hipLaunchKernelGGL(dev::k_plan_sort_items<float>, dim3(nb), dim3(dev::kSortThreads), shm, s, g, items, sub, flags, nvis, lb, groups,
-                           reinterpret_cast<const uint2*>(off0), perm0, reinterpret_cast<uint2*>(off), map,
-                           pieces);
+    if (f64 && g.lsub) sort_items<double, 1>(nb, shm, g, items, sub, flags, nvis, lb, groups, off0, perm0, off, map, pieces, s);
+    else if (f64) sort_items<double, 0>(nb, shm, g, items, sub, flags, nvis, lb, groups, off0, perm0, off, map, pieces, s);
+    else if (g.lsub) sort_items<float, 1>(nb, shm, g, items, sub, flags, nvis, lb, groups, off0, perm0, off, map, pieces, s);
+    else sort_items<float, 0>(nb, shm, g, items, sub, flags, nvis, lb, groups, off0, perm0, off, map, pieces, s);
     return hipGetLastError();
 }
 
@@ -861,8 +898,10 @@ hipError_t set_kernel_attributes() {
     LMG_ATTR(72 * 1024, &dev::k_plan_scatter<float, true>);
     LMG_ATTR(72 * 1024, &dev::k_plan_scatter<double, false>);
     LMG_ATTR(72 * 1024, &dev::k_plan_scatter<double, true>);
-    LMG_ATTR(128 * 1024, &dev::k_plan_sort_items<float>);
-    LMG_ATTR(128 * 1024, &dev::k_plan_sort_items<double>);
+    LMG_ATTR(128 * 1024, &dev::k_plan_sort_items<float, 0>);
+    LMG_ATTR(128 * 1024, &dev::k_plan_sort_items<float, 1>);
+    LMG_ATTR(128 * 1024, &dev::k_plan_sort_items<double, 0>);
+    LMG_ATTR(128 * 1024, &dev::k_plan_sort_items<double, 1>);
 #undef LMG_ATTR
     return e;
 }
