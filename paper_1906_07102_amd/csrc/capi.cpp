@@ -671,8 +671,8 @@ lmg_status create_plan(const lmg_table* table, int N, lmg_precision prec, int nc
     p->twiddle = base + L.twiddle;
     p->hpix = base + L.hpix;
 
-    // Plan blocks: runs of at most plan_block_vis() visibilities of one channel. A single channel's tables are written
-    // by the setup kernel; a batch's are staged in pinned memory.
+    // Plan blocks: runs of at most plan_block_vis() visibilities of one channel. A batch's tables are staged in
+    // pinned memory; a single channel's blocks follow from their size.
     const int block_vis = plan_block_vis(N, nvis);
     std::vector<int4> blocks;
     std::vector<int> chan_blocks;
@@ -695,12 +695,9 @@ lmg_status create_plan(const lmg_table* table, int N, lmg_precision prec, int nc
     std::vector<double> h(N);
     if (lmg_correction(table, N, h.data()) != LMG_OK) return LMG_EINVAL;
     PlanSetup su{};
-    su.flags = p->flags;
-    su.blocks = p->blocks;
-    su.chan_blocks = p->chan_blocks;
-    su.gen_blocks = nchan == 1 ? p->nblocks : -1;
-    su.block_vis = block_vis;
-    su.nvis = static_cast<int>(nvis);
+    PlanBlocks bl{};
+    bl.block_vis = block_vis;
+    bl.nvis = static_cast<int>(nvis);
     int copies = 0;
     auto from_pinned = [&](void* dst, const void* src, size_t bytes) {
         su.dst[copies] = dst;
@@ -731,42 +728,45 @@ lmg_status create_plan(const lmg_table* table, int N, lmg_precision prec, int nc
             std::memcpy(st + align_up(bb), chan_blocks.data(), cb);
             from_pinned(p->blocks, st, bb);
             from_pinned(p->chan_blocks, st + align_up(bb), cb);
+            bl.table = reinterpret_cast<const int4*>(st);      // the first launch reads it where it lies
             staged = true;
         } else {
             if (upload(p->blocks, blocks.data(), bb, s) != LMG_OK) return LMG_EHIP;
             if (upload(p->chan_blocks, chan_blocks.data(), cb, s) != LMG_OK) return LMG_EHIP;
+            bl.table = p->blocks;
         }
     }
-    {
-        TraceScope ts("plan_setup", s);
-        LMG_HIP(launch_plan_setup(su, s));
-    }
-    if (staged) {
-        if (!g_staging.done) LMG_HIP(hipEventCreateWithFlags(&g_staging.done, hipEventDisableTiming));
-        LMG_HIP(hipEventRecord(g_staging.done, s));
-        g_staging.pending = true;
-    }
-    {
-        TraceScope ts("plan_count", s);
-        LMG_HIP(launch_plan_count(uv, p->blocks, p->nblocks, p->g, p->blockhist, p->flags, s));
-    }
-    {
-        TraceScope ts("plan_colscan", s);
-        LMG_HIP(launch_plan_colscan(p->g, p->blockhist, p->chan_blocks, p->tile_count, s));
-    }
-    {
-        TraceScope ts("plan_scan", s);
-        p->host_flags = take_flag_slot();
-        LMG_HIP(launch_plan_scan(p->g, p->tile_count, p->tile_start, p->item_start, p->items, p->flags, cap,
-                                 p->host_flags, s));
-    }
     const bool direct = nvis <= kDirectPlanVis;
-    {
+    p->host_flags = take_flag_slot();
+    if (small_plan(p->g, nvis)) {
+        TraceScope ts("plan_small", s);
+        LMG_HIP(launch_plan_small(prec == LMG_F64, uv, p->g, static_cast<int>(nvis), p->tile_start, p->item_start, p->items,
+                                  p->flags, cap, p->host_flags, delta_low(table->W), p->ms_enc, p->kb, p->inv0, p->off0,
+                                  su, s));
+    } else {
+        {
+            TraceScope ts("plan_count", s);
+            LMG_HIP(launch_plan_count(uv, bl, p->nblocks, p->g, p->blockhist, su, s));
+        }
+        if (staged) {
+            if (!g_staging.done) LMG_HIP(hipEventCreateWithFlags(&g_staging.done, hipEventDisableTiming));
+            LMG_HIP(hipEventRecord(g_staging.done, s));
+            g_staging.pending = true;
+            bl.table = p->blocks;
+        }
+        {
+            TraceScope ts("plan_colscan", s);
+            LMG_HIP(launch_plan_colscan(p->g, p->blockhist, p->chan_blocks, p->nblocks, p->tile_count, s));
+        }
+        {
+            TraceScope ts("plan_scan", s);
+            LMG_HIP(launch_plan_scan(p->g, p->tile_count, p->tile_start, p->item_start, p->items, p->flags, cap,
+                                     p->host_flags, s));
+        }
         TraceScope ts("plan_scatter", s);
         // packed offsets by caller index go to `off` for now (the item sort overwrites it)
-        LMG_HIP(launch_plan_scatter(prec == LMG_F64, direct, uv, p->blocks, p->nblocks, p->g, p->tile_start,
-                                    p->blockhist, delta_low(table->W), p->lb, p->ms_enc, p->kb, p->inv0,
-                                    direct ? p->off0 : p->off, s));
+        LMG_HIP(launch_plan_scatter(prec == LMG_F64, direct, uv, bl, p->nblocks, p->g, p->tile_start, p->blockhist,
+                                    delta_low(table->W), p->ms_enc, p->kb, p->inv0, direct ? p->off0 : p->off, s));
     }
     if (!direct) {
         TraceScope ts("plan_place", s);

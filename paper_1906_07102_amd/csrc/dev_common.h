@@ -216,42 +216,22 @@ __device__ __forceinline__ int wave_incl_sum(int v) {
 }
 
 // Workgroup-wide exclusive sum of one int per thread (blockDim.x a multiple
-// of 64, at most 1024); returns the prefix and the total. `sh` holds 17 ints.
+// of 64, at most 1024); returns the prefix and the total. `sh` holds 16 ints.
 __device__ __forceinline__ int block_excl_sum(int v, int* sh, int* total) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
     const int inc = wave_incl_sum(v);
     if (lane == 63) sh[wave] = inc;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        int a = 0;
-        for (int i = 0; i < nw; ++i) {
-            const int x = sh[i];
-            sh[i] = a;
-            a += x;
-        }
-        sh[16] = a;
-    }
-    __syncthreads();
-    const int r = sh[wave] + inc - v;
-    *total = sh[16];
-    __syncthreads();
-    return r;
-}
-
-// Workgroup-wide min or max reduction (op 0: min, 1: max, 2: sum).
-__device__ __forceinline__ int block_reduce(int v, int op, int* sh) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    int before = 0, all = 0;
 #pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-        const int o = __shfl_xor(v, d, 64);
-        v = op == 0 ? min(v, o) : op == 1 ? max(v, o) : v + o;
+    for (int i = 0; i < 16; ++i) {               // independent reads, one address per wave
+        const int x = i < nw ? sh[i] : 0;
+        before += i < wave ? x : 0;
+        all += x;
     }
-    if (lane == 0) sh[wave] = v;
+    *total = all;
     __syncthreads();
-    int r = sh[0];
-    for (int i = 1; i < nw; ++i) r = op == 0 ? min(r, sh[i]) : op == 1 ? max(r, sh[i]) : r + sh[i];
-    __syncthreads();
-    return r;
+    return before + inc - v;
 }
 
 // K consecutive elements from p into out. 8-byte elements travel in 16-byte

@@ -25,6 +25,10 @@ inline int plan_block_vis(int N, int64_t nvis) {
 }
 // Plans of at most this many visibilities scatter directly (k_plan_scatter).
 constexpr int64_t kDirectPlanVis = 1 << 18;
+// Plans of one channel and at most this many visibilities take one launch up to the scatter (k_plan_small): up to there
+// one workgroup is no slower than the general passes' four launches (2,000 visibilities 43 us, general 50; 8,000 52 and
+// 52; 16,000 74 and 57; the whole plan with its item sort).
+constexpr int64_t kSmallPlanVis = 1 << 12;
 // Longest run of one footprint cell handled by one lane (a "piece").
 constexpr int kPiece = 32;
 // Elements of padding after the entry-order arrays the item kernels read in runs.
@@ -126,31 +130,36 @@ struct FftArgs {
     int row_off;
 };
 
-// What a plan's workspace starts from: up to five arrays copied from pinned host memory (16-byte aligned on both
-// sides, sizes multiples of four), 16 zeroed flags, and for a single channel (gen_blocks >= 0) the block tables.
+// What a plan's first launch copies from pinned host memory: up to five arrays (16-byte aligned on both sides, sizes
+// multiples of four).
 struct PlanSetup {
     static constexpr int kCopies = 5;
     const void* src[kCopies];
     void* dst[kCopies];
     int bytes[kCopies];
-    int* flags;
-    int4* blocks;
-    int* chan_blocks;
-    int gen_blocks, block_vis, nvis;
 };
-hipError_t launch_plan_setup(const PlanSetup& a, hipStream_t s);
-hipError_t launch_plan_count(const double* uv, const int4* blocks, int nb, const PlanGeom& g, int* blockhist,
-                             int* flags, hipStream_t s);
-hipError_t launch_plan_colscan(const PlanGeom& g, int* blockhist, const int* chan_blocks, int* tile_count,
+// The plan blocks: a batch's table, or (nullptr) runs of block_vis of nvis visibilities.
+struct PlanBlocks {
+    const int4* table;
+    int block_vis, nvis;
+};
+hipError_t launch_plan_count(const double* uv, const PlanBlocks& blocks, int nb, const PlanGeom& g, int* blockhist,
+                             const PlanSetup& setup, hipStream_t s);
+// One launch for the passes up to the scatter (which is direct): one channel of at most kSmallPlanVis visibilities.
+bool small_plan(const PlanGeom& g, int64_t nvis);
+hipError_t launch_plan_small(bool f64, const double* uv, const PlanGeom& g, int nvis, int* tile_start, int* item_start,
+                             int4* items, int* flags, int cap, int* host_flags, double dlo, int ms, int kb, int* perm0,
+                             void* off0, const PlanSetup& setup, hipStream_t s);
+hipError_t launch_plan_colscan(const PlanGeom& g, int* blockhist, const int* chan_blocks, int nb, int* tile_count,
                                hipStream_t s);
 // host_flags (or nullptr): pinned host copy of flags[0 .. 7].
 hipError_t launch_plan_scan(const PlanGeom& g, const int* tile_count, int* tile_start, int* item_start, int4* items,
                             int* flags, int cap, int* host_flags, hipStream_t s);
 // By caller index: index[k] = tile-order position, offs[k] = packed offsets, packed for a table of ms intervals (1 for
 // a direct table), kb = bits of ms. With `direct`, by tile-order position: index[p] = caller index, offs[p].
-hipError_t launch_plan_scatter(bool f64, bool direct, const double* uv, const int4* blocks, int nb, const PlanGeom& g,
-                               const int* tile_start, const int* blockhist, double dlo, int lb, int ms, int kb,
-                               int* index, void* offs, hipStream_t s);
+hipError_t launch_plan_scatter(bool f64, bool direct, const double* uv, const PlanBlocks& blocks, int nb, const PlanGeom& g,
+                               const int* tile_start, const int* blockhist, double dlo, int ms, int kb, int* index,
+                               void* offs, hipStream_t s);
 // off0[inv0[k]] = offk[k] for the valid visibilities (flags[2] of them).
 hipError_t launch_plan_place(bool f64, const int* inv0, const void* offk, const int* flags, int64_t nvis, void* off0,
                              hipStream_t s);

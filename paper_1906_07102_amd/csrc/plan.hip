@@ -10,18 +10,12 @@ namespace dev {
 // read and cleared by lmg_sync_status through the runtime's symbol copies.
 __device__ int g_data_error;
 
-// Before pass 1: the constants a plan keeps (coefficients, twiddles,
-// correction) and, for a batch, the block tables, read from pinned host memory
-// in 16-byte pieces (one per thread, all in flight at once); the block tables
-// of a single channel, which follow from its size; the flags, zeroed. One
-// launch instead of five copies and a fill, which took 30 to 40 us of host and
-// queue time per plan.
-__global__ __launch_bounds__(256) void k_plan_setup(PlanSetup a) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i < 16) a.flags[i] = 0;
-    for (int b = i; b < a.gen_blocks; b += gridDim.x * 256)
-        a.blocks[b] = make_int4(0, b * a.block_vis, min(a.block_vis, a.nvis - b * a.block_vis), 0);
-    if (a.gen_blocks >= 0 && i < 2) a.chan_blocks[i] = i ? a.gen_blocks : 0;
+// The constants a plan keeps (coefficients, twiddles, correction) and, for a
+// batch, the block tables, read from pinned host memory in 16-byte pieces (one
+// per thread, all in flight at once) by the workgroups of the plan's first
+// launch that have no visibilities to count: i is the thread's number among
+// them. (A launch of its own took 8 us per plan, copies and a fill 30 to 40.)
+__device__ __forceinline__ void copy_constants(const PlanSetup& a, int i) {
     int at = i;
 #pragma unroll
     for (int q = 0; q < PlanSetup::kCopies; ++q) {
@@ -40,24 +34,21 @@ __global__ __launch_bounds__(256) void k_plan_setup(PlanSetup a) {
     }
 }
 
-// Pass 1: count visibilities per tile, per plan block (a run of at most
-// plan_block_vis() visibilities of one channel, kept per block so that pass 3
-// can place each block's visibilities of a tile in one contiguous run). The
-// slot after the tiles counts visibilities whose coordinates are not finite
-// (they are dropped). blocks[b] = (channel, first visibility, count, 0).
-__global__ __launch_bounds__(kPlanThreads) void k_plan_count(const double2* __restrict__ uv, const int4* __restrict__ blocks,
-                                                             int nb, PlanGeom g, int* __restrict__ blockhist,
-                                                             int* __restrict__ flags) {
-    extern __shared__ int hist[];
-    const int hs = g.ntiles + 1;
-    for (int t = threadIdx.x; t < hs; t += blockDim.x) hist[t] = 0;
-    __syncthreads();
-    const int chunk = xcd_chunk(blockIdx.x, nb);
-    const int4 bd = blocks[chunk];
-    const int64_t base = bd.y, end = static_cast<int64_t>(bd.y) + bd.z;
-    int bad = 0;
+// Plan block b: (channel, first visibility, count, 0); from the batch's table, or for a single channel (no table) by
+// its size.
+__device__ __forceinline__ int4 plan_block(const PlanBlocks& p, int b) {
+    if (p.table) return p.table[b];
+    return make_int4(0, b * p.block_vis, min(p.block_vis, p.nvis - b * p.block_vis), 0);
+}
+
+// Visibilities base .. base + count of one channel: one count each in hist (slot g.ntiles: coordinates that are not
+// finite). True if this thread met such coordinates.
+__device__ __forceinline__ bool count_run(const double2* __restrict__ uv, int64_t base, int count, const PlanGeom& g,
+                                          int* hist) {
+    const int64_t end = base + count;
+    bool bad = false;
     constexpr int kB = 8;
-    for (int i0 = 0; i0 < bd.z; i0 += kB * kPlanThreads) {
+    for (int i0 = 0; i0 < count; i0 += kB * kPlanThreads) {
         double2 c[kB];
 #pragma unroll
         for (int u = 0; u < kB; ++u) {
@@ -74,14 +65,31 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_count(const double2* __re
                 atomicAdd(&hist[((cv >> g.lb) << g.lbx) + (cu >> g.lb)], 1);
             } else {
                 atomicAdd(&hist[g.ntiles], 1);
-                bad = 1;
+                bad = true;
             }
         }
     }
-    if (bad) {
-        atomicOr(&flags[0], 1);
-        atomicOr(&g_data_error, 1);
+    return bad;
+}
+
+// Pass 1: count visibilities per tile, per plan block (a run of at most
+// plan_block_vis() visibilities of one channel, kept per block so that pass 3
+// can place each block's visibilities of a tile in one contiguous run). The
+// slot after the tiles counts visibilities whose coordinates are not finite
+// (they are dropped). Workgroups nb .. copy the plan's constants.
+__global__ __launch_bounds__(kPlanThreads) void k_plan_count(const double2* __restrict__ uv, PlanBlocks blocks, int nb,
+                                                             PlanGeom g, int* __restrict__ blockhist, PlanSetup setup) {
+    extern __shared__ int hist[];
+    if (static_cast<int>(blockIdx.x) >= nb) {                // uniform across the workgroup
+        copy_constants(setup, (blockIdx.x - nb) * kPlanThreads + threadIdx.x);
+        return;
     }
+    const int hs = g.ntiles + 1;
+    for (int t = threadIdx.x; t < hs; t += blockDim.x) hist[t] = 0;
+    __syncthreads();
+    const int chunk = xcd_chunk(blockIdx.x, nb);
+    const int4 bd = plan_block(blocks, chunk);
+    if (count_run(uv, bd.y, bd.z, g, hist)) atomicOr(&g_data_error, 1);
     __syncthreads();
     int* row = blockhist + static_cast<size_t>(chunk) * hs;
     for (int t = threadIdx.x; t < hs; t += blockDim.x) row[t] = hist[t];
@@ -94,7 +102,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_count(const double2* __re
 // kScanGroups runs of blocks.
 constexpr int kScanGroups = 16;
 __global__ __launch_bounds__(64 * kScanGroups) void k_plan_colscan(PlanGeom g, int* __restrict__ blockhist,
-                                                                   const int* __restrict__ chan_blocks,
+                                                                   const int* __restrict__ chan_blocks, int nb,
                                                                    int* __restrict__ tile_count) {
     __shared__ int part[kScanGroups][64];
     const int64_t tot = static_cast<int64_t>(g.ntiles) * g.nchan;
@@ -106,8 +114,11 @@ __global__ __launch_bounds__(64 * kScanGroups) void k_plan_colscan(PlanGeom g, i
     if (live) {
         if (slot == tot) {
             b0 = 0;
-            b1 = chan_blocks[g.nchan];
+            b1 = nb;
             col = g.ntiles;
+        } else if (g.nchan == 1) {
+            b1 = nb;
+            col = static_cast<int>(slot);
         } else {
             const int c = static_cast<int>(slot >> (2 * g.lbx));
             b0 = chan_blocks[c];
@@ -154,6 +165,7 @@ __global__ __launch_bounds__(64 * kScanGroups) void k_plan_colscan(PlanGeom g, i
     if (live && grp == kScanGroups - 1) tile_count[slot] = run;
 }
 
+constexpr int kScanSums = 96;    // ints of LDS for the block sums and reductions of the scan
 struct ScanAcc {
     int s, si, busy, rmin, rmax, cmin, cmax;
 };
@@ -175,6 +187,7 @@ __device__ __forceinline__ void scan_place(const PlanGeom& g, int t, int c, int 
                                            int* item_start, int4* items, int* flags, ScanAcc& a, bool write_items) {
     tile_start[t] = a.s;
     if (t == tot) {
+        flags[0] = c > 0;
         flags[2] = a.s;
         a.s += c;
         return;
@@ -209,7 +222,7 @@ __device__ __forceinline__ void scan_place(const PlanGeom& g, int t, int c, int 
 }
 
 // Pass 2 (one workgroup): slot offsets, work items of at most `cap`
-// visibilities, counts and the occupied band (flags[1] items, [2] valid
+// visibilities, counts and the occupied band (flags[0] any dropped, [1] items, [2] valid
 // visibilities, [3] busy tiles, [4..7] min / max occupied tile row and
 // column). tile_start has nslots + 1 entries (the last is nvis).
 // Each thread scans a contiguous run of slots. With `staged` (slots fit
@@ -235,12 +248,87 @@ __device__ __forceinline__ void scan_slots(const PlanGeom& g, const int* cnt, in
     }
 }
 
+// With the counts of all slots in s_start (LDS, ns of them): the slot offsets take their place, the item offsets go to
+// s_items, both are copied out, and the work items are written.
+__device__ __forceinline__ void scan_staged(const PlanGeom& g, int* s_start, int* s_items, int lo, int hi, int ns, int cap,
+                                            int* tile_start, int* item_start, int4* items, int* flags, int* sh, int* nvis,
+                                            int* n_items, ScanAcc& acc) {
+    const int tot = ns - 1;
+    __syncthreads();
+    scan_slots<true>(g, s_start, s_start, s_items, lo, hi, tot, cap, items, flags, sh, nvis, n_items, acc);
+    const int nitems = *n_items;
+    if (threadIdx.x == 0) s_items[tot] = nitems;
+    __syncthreads();
+    for (int t = threadIdx.x; t < ns; t += blockDim.x) tile_start[t] = s_start[t];
+    for (int t = threadIdx.x; t < tot; t += blockDim.x) item_start[t] = s_items[t];
+    // Work items in parallel (a tile above cap has several, and the dense tiles are neighbours in
+    // one thread's run): item i belongs to the last slot whose first item is <= i.
+    for (int i = threadIdx.x; i < nitems; i += blockDim.x) {
+        int a = 0, b = tot;          // s_items[a] <= i < s_items[b]
+        while (b - a > 1) {
+        const int m = (a + b) >> 1;
+        if (s_items[m] <= i) a = m; else b = m;
+        }
+        const int c = s_start[a + 1] - s_start[a];
+        const int ni = slot_items(c, cap);
+        const int q = i - s_items[a];
+        const int base = c / ni, extra = c - base * ni;     // the first extra items take one more
+        const int first = q * base + min(q, extra);
+        items[i] = make_int4(a, s_start[a] + first, base + (q < extra ? 1 : 0), 0);
+    }
+}
+
+// The plan's counts and occupied band.
+__device__ __forceinline__ void scan_flags(const ScanAcc& acc, int ns, int nvis, int nitems, int* tile_start,
+                                           int* item_start, int* flags, int* host_flags, int* sh) {
+    int v[5] = {acc.busy, -acc.rmin, acc.rmax, -acc.cmin, acc.cmax};     // a sum and four maxima
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+#pragma unroll
+        for (int q = 0; q < 5; ++q) {
+            const int o = __shfl_xor(v[q], d, 64);
+            v[q] = q == 0 ? v[q] + o : max(v[q], o);
+        }
+    }
+    if (lane == 0) {
+#pragma unroll
+        for (int q = 0; q < 5; ++q) sh[q * 16 + wave] = v[q];
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int q = 0; q < 5; ++q) {
+            for (int w = 1; w < nw; ++w) v[q] = q == 0 ? v[q] + sh[w] : max(v[q], sh[q * 16 + w]);
+        }
+        tile_start[ns] = nvis;
+        item_start[ns - 1] = nitems;
+        flags[1] = nitems;
+        flags[3] = v[0];
+        flags[4] = -v[1];
+        flags[5] = v[2];
+        flags[6] = -v[3];
+        flags[7] = v[4];
+        if (host_flags) {                        // the host's copy, in pinned memory
+            host_flags[0] = flags[0];
+            host_flags[1] = nitems;
+            host_flags[2] = flags[2];
+            host_flags[3] = v[0];
+            host_flags[4] = -v[1];
+            host_flags[5] = v[2];
+            host_flags[6] = -v[3];
+            host_flags[7] = v[4];
+            __threadfence_system();
+        }
+    }
+}
+
 __global__ __launch_bounds__(1024) void k_plan_scan(PlanGeom g, const int* __restrict__ tile_count,
                                                     int* __restrict__ tile_start, int* __restrict__ item_start,
                                                     int4* __restrict__ items, int* __restrict__ flags, int cap,
                                                     int staged, int* __restrict__ host_flags) {
     extern __shared__ int lds[];
-    int* sh = lds;                               // 17 ints for the block reductions
+    int* sh = lds;
     const int tot = g.ntiles * g.nchan;          // tile slots, channel-major; slot tot = dropped
     const int ns = tot + 1;
     const int per = (ns + blockDim.x - 1) / blockDim.x;
@@ -248,7 +336,7 @@ __global__ __launch_bounds__(1024) void k_plan_scan(PlanGeom g, const int* __res
     int nvis = 0, nitems = 0;
     ScanAcc acc;
     if (staged) {
-        int* s_start = lds + 32;                 // counts, then slot offsets
+        int* s_start = lds + kScanSums;          // counts, then slot offsets
         int* s_items = s_start + ns;             // item offsets
         constexpr int kL = 8;                    // loads in flight per thread
         for (int t0 = 0; t0 < ns; t0 += kL * blockDim.x) {
@@ -264,58 +352,12 @@ __global__ __launch_bounds__(1024) void k_plan_scan(PlanGeom g, const int* __res
                 if (t < ns) s_start[t] = v[u];
             }
         }
-        __syncthreads();
-        scan_slots<true>(g, s_start, s_start, s_items, lo, hi, tot, cap, items, flags, sh, &nvis, &nitems, acc);
-        if (threadIdx.x == 0) s_items[tot] = nitems;
-        __syncthreads();
-        for (int t = threadIdx.x; t < ns; t += blockDim.x) tile_start[t] = s_start[t];
-        for (int t = threadIdx.x; t < tot; t += blockDim.x) item_start[t] = s_items[t];
-        // Work items in parallel (a tile above cap has several, and the dense tiles are neighbours in
-        // one thread's run): item i belongs to the last slot whose first item is <= i.
-        for (int i = threadIdx.x; i < nitems; i += blockDim.x) {
-            int a = 0, b = tot;                  // s_items[a] <= i < s_items[b]
-            while (b - a > 1) {
-                const int m = (a + b) >> 1;
-                if (s_items[m] <= i) a = m; else b = m;
-            }
-            const int c = s_start[a + 1] - s_start[a];
-            const int ni = slot_items(c, cap);
-            const int q = i - s_items[a];
-            const int base = c / ni, extra = c - base * ni;     // the first extra items take one more
-            const int lo = q * base + min(q, extra);
-            items[i] = make_int4(a, s_start[a] + lo, base + (q < extra ? 1 : 0), 0);
-        }
+        scan_staged(g, s_start, s_items, lo, hi, ns, cap, tile_start, item_start, items, flags, sh, &nvis, &nitems, acc);
     } else {
         scan_slots<false>(g, tile_count, tile_start, item_start, lo, hi, tot, cap, items, flags, sh, &nvis, &nitems,
                           acc);
     }
-    int busy = acc.busy, rmin = acc.rmin, rmax = acc.rmax, cmin = acc.cmin, cmax = acc.cmax;
-    busy = block_reduce(busy, 2, sh);
-    rmin = block_reduce(rmin, 0, sh);
-    rmax = block_reduce(rmax, 1, sh);
-    cmin = block_reduce(cmin, 0, sh);
-    cmax = block_reduce(cmax, 1, sh);
-    if (threadIdx.x == 0) {
-        tile_start[ns] = nvis;
-        item_start[tot] = nitems;
-        flags[1] = nitems;
-        flags[3] = busy;
-        flags[4] = rmin;
-        flags[5] = rmax;
-        flags[6] = cmin;
-        flags[7] = cmax;
-        if (host_flags) {                        // the host's copy, in pinned memory
-            host_flags[0] = flags[0];
-            host_flags[1] = nitems;
-            host_flags[2] = flags[2];
-            host_flags[3] = busy;
-            host_flags[4] = rmin;
-            host_flags[5] = rmax;
-            host_flags[6] = cmin;
-            host_flags[7] = cmax;
-            __threadfence_system();
-        }
-    }
+    scan_flags(acc, ns, nvis, nitems, tile_start, item_start, flags, host_flags, sh);
 }
 
 // Pass 3: give each visibility its tile-order position (index = inv0, by
@@ -335,27 +377,15 @@ __global__ __launch_bounds__(1024) void k_plan_scan(PlanGeom g, const int* __res
 // the item sort writes caller index -> entry itself; the place and compose
 // passes are not run.
 template <typename R, bool kDirect>
-__global__ __launch_bounds__(kPlanThreads) void k_plan_scatter(const double2* __restrict__ uv,
-                                                               const int4* __restrict__ blocks, int nb, PlanGeom g,
-                                                               const int* __restrict__ tile_start,
-                                                               const int* __restrict__ blockhist, double dlo, int lb,
-                                                               int ms, int kb, int* __restrict__ index,
-                                                               typename Pack<R>::T2* __restrict__ offs) {
-    extern __shared__ int cur[];
-    const int hs = g.ntiles + 1;
-    const int chunk = xcd_chunk(blockIdx.x, nb);
-    const int4 bd = blocks[chunk];
-    const int* row = blockhist + static_cast<size_t>(chunk) * hs;
-    const int* ts = tile_start + static_cast<size_t>(bd.x) * g.ntiles;
-    for (int t = threadIdx.x; t < g.ntiles; t += blockDim.x) cur[t] = ts[t] + row[t];
-    if (threadIdx.x == 0) cur[g.ntiles] = tile_start[static_cast<size_t>(g.ntiles) * g.nchan] + row[g.ntiles];
-    __syncthreads();
+__device__ __forceinline__ void scatter_run(const double2* __restrict__ uv, int64_t base, int count, const PlanGeom& g,
+                                            int* cur, double dlo, int ms, int kb, int* __restrict__ index,
+                                            typename Pack<R>::T2* __restrict__ offs) {
     const int wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
-    const int64_t base = bd.y, end = static_cast<int64_t>(bd.y) + bd.z;
+    const int64_t end = base + count;
     constexpr int kB = 8;                                    // most coordinates loaded together per thread
-    const int kb_run = min(kB, (bd.z + kPlanThreads - 1) / kPlanThreads);     // coordinates per thread and step
+    const int kb_run = min(kB, (count + kPlanThreads - 1) / kPlanThreads);     // coordinates per thread and step
     const int first = wave * 64 * kb_run + (threadIdx.x & 63);
-    for (int i0 = 0; i0 < bd.z; i0 += kb_run * kPlanThreads) {  // uniform across the workgroup
+    for (int i0 = 0; i0 < count; i0 += kb_run * kPlanThreads) {  // uniform across the workgroup
         double2 c[kB];
         const int64_t k0 = base + i0 + first;                // this thread's coordinates: k0 + 64 u, u < kb_run
 #pragma unroll
@@ -375,8 +405,8 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_scatter(const double2* __
             if (tap_geometry(c[u].x, g.W, g.ref, g.N, &cu, &du) && tap_geometry(c[u].y, g.W, g.ref, g.N, &cv, &dv)) {
                 key[u] = ((cv >> g.lb) << g.lbx) + (cu >> g.lb);
                 typename Pack<R>::T2 o;
-                o.x = pack_axis<R>(cu & (g.T - 1), du, dlo, lb, ms, kb);
-                o.y = pack_axis<R>(cv & (g.T - 1), dv, dlo, lb, ms, kb);
+                o.x = pack_axis<R>(cu & (g.T - 1), du, dlo, g.lb, ms, kb);
+                o.y = pack_axis<R>(cv & (g.T - 1), dv, dlo, g.lb, ms, kb);
                 packed[u] = o;
                 if (!kDirect) offs[k] = o;
             } else {
@@ -403,6 +433,57 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_scatter(const double2* __
             }
         }
     }
+}
+
+template <typename R, bool kDirect>
+__global__ __launch_bounds__(kPlanThreads) void k_plan_scatter(const double2* __restrict__ uv, PlanBlocks blocks, int nb,
+                                                               PlanGeom g, const int* __restrict__ tile_start,
+                                                               const int* __restrict__ blockhist, double dlo, int ms,
+                                                               int kb, int* __restrict__ index,
+                                                               typename Pack<R>::T2* __restrict__ offs) {
+    extern __shared__ int cur[];
+    const int hs = g.ntiles + 1;
+    const int chunk = xcd_chunk(blockIdx.x, nb);
+    const int4 bd = plan_block(blocks, chunk);
+    const int* row = blockhist + static_cast<size_t>(chunk) * hs;
+    const int* ts = tile_start + static_cast<size_t>(bd.x) * g.ntiles;
+    for (int t = threadIdx.x; t < g.ntiles; t += blockDim.x) cur[t] = ts[t] + row[t];
+    if (threadIdx.x == 0) cur[g.ntiles] = tile_start[static_cast<size_t>(g.ntiles) * g.nchan] + row[g.ntiles];
+    __syncthreads();
+    scatter_run<R, kDirect>(uv, bd.y, bd.z, g, cur, dlo, ms, kb, index, offs);
+}
+
+// Passes 1 to 3 of a plan of one channel and at most kSmallPlanVis
+// visibilities, by one workgroup, with the counts and offsets of all tiles in
+// LDS (workgroups 1 .. copy the plan's constants). Such a plan is bound by its
+// launches (2,000 visibilities on 128^2: 50 us in five, 43 in two).
+template <typename R>
+__global__ __launch_bounds__(kPlanThreads) void k_plan_small(const double2* __restrict__ uv, PlanGeom g, int nvis,
+                                                             int* __restrict__ tile_start, int* __restrict__ item_start,
+                                                             int4* __restrict__ items, int* __restrict__ flags, int cap,
+                                                             int* __restrict__ host_flags, double dlo, int ms, int kb,
+                                                             int* __restrict__ perm0,
+                                                             typename Pack<R>::T2* __restrict__ off0, PlanSetup setup) {
+    extern __shared__ int lds[];
+    if (blockIdx.x > 0) {                        // uniform across the workgroup
+        copy_constants(setup, (blockIdx.x - 1) * kPlanThreads + threadIdx.x);
+        return;
+    }
+    const int ns = g.ntiles + 1;
+    int* sh = lds;
+    int* s_start = lds + kScanSums;              // counts, then slot offsets, then cursors
+    int* s_items = s_start + ns;
+    for (int t = threadIdx.x; t < ns; t += blockDim.x) s_start[t] = 0;
+    __syncthreads();
+    if (count_run(uv, 0, nvis, g, s_start)) atomicOr(&g_data_error, 1);
+    const int per = (ns + blockDim.x - 1) / blockDim.x;
+    const int lo = threadIdx.x * per, hi = min(ns, lo + per);
+    int n = 0, nitems = 0;
+    ScanAcc acc;
+    scan_staged(g, s_start, s_items, lo, hi, ns, cap, tile_start, item_start, items, flags, sh, &n, &nitems, acc);
+    scan_flags(acc, ns, n, nitems, tile_start, item_start, flags, host_flags, sh);
+    __syncthreads();                             // the offsets have been read
+    scatter_run<R, true>(uv, 0, nvis, g, s_start, dlo, ms, kb, perm0, off0);
 }
 
 // Threads per workgroup of the permutation passes (place, compose, permute in / out).
@@ -745,39 +826,62 @@ __global__ void k_zero_ints(int* __restrict__ p, int n) {
 
 }  // namespace dev
 
-hipError_t launch_plan_setup(const PlanSetup& a, hipStream_t s) {
-    int n = 16;
+namespace {
+unsigned copy_groups(const PlanSetup& a) {
+    int n = 0;
     for (int q = 0; q < PlanSetup::kCopies; ++q) n += (a.bytes[q] + 15) / 16;
-    hipLaunchKernelGGL(dev::k_plan_setup, dim3((n + 255) / 256), dim3(256), 0, s, a);
+    return static_cast<unsigned>((n + kPlanThreads - 1) / kPlanThreads);
+}
+// LDS of the scan over ns slots with their counts and two offset arrays in it; 0 if it does not fit.
+size_t staged_scan_bytes(size_t ns) {
+    const size_t bytes = (dev::kScanSums + 2 * ns) * sizeof(int);
+    return bytes <= kMaxDynLds ? bytes : 0;
+}
+}  // namespace
+
+hipError_t launch_plan_count(const double* uv, const PlanBlocks& blocks, int nb, const PlanGeom& g, int* blockhist,
+                             const PlanSetup& setup, hipStream_t s) {
+    const unsigned groups = nb + copy_groups(setup);
+    if (groups == 0) return hipSuccess;
+    hipLaunchKernelGGL(dev::k_plan_count, dim3(groups), dim3(kPlanThreads), (g.ntiles + 1) * sizeof(int), s,
+                       reinterpret_cast<const double2*>(uv), blocks, nb, g, blockhist, setup);
     return hipGetLastError();
 }
 
-hipError_t launch_plan_count(const double* uv, const int4* blocks, int nb, const PlanGeom& g, int* blockhist,
-                             int* flags, hipStream_t s) {
-    if (nb == 0) return hipSuccess;
-    hipLaunchKernelGGL(dev::k_plan_count, dim3(nb), dim3(kPlanThreads), (g.ntiles + 1) * sizeof(int), s,
-                       reinterpret_cast<const double2*>(uv), blocks, nb, g, blockhist, flags);
+bool small_plan(const PlanGeom& g, int64_t nvis) {
+    return g.nchan == 1 && nvis <= kSmallPlanVis && staged_scan_bytes(static_cast<size_t>(g.ntiles) + 1) != 0;
+}
+
+hipError_t launch_plan_small(bool f64, const double* uv, const PlanGeom& g, int nvis, int* tile_start, int* item_start,
+                             int4* items, int* flags, int cap, int* host_flags, double dlo, int ms, int kb, int* perm0,
+                             void* off0, const PlanSetup& setup, hipStream_t s) {
+    const size_t shm = staged_scan_bytes(static_cast<size_t>(g.ntiles) + 1);
+    const dim3 groups(1 + copy_groups(setup));
+    const double2* c = reinterpret_cast<const double2*>(uv);
+    if (f64)
+        hipLaunchKernelGGL(dev::k_plan_small<double>, groups, dim3(kPlanThreads), shm, s, c, g, nvis, tile_start, item_start,
+                           items, flags, cap, host_flags, dlo, ms, kb, perm0, reinterpret_cast<ulonglong2*>(off0), setup);
+    else
+        hipLaunchKernelGGL(dev::k_plan_small<float>, groups, dim3(kPlanThreads), shm, s, c, g, nvis, tile_start, item_start,
+                           items, flags, cap, host_flags, dlo, ms, kb, perm0, reinterpret_cast<uint2*>(off0), setup);
     return hipGetLastError();
 }
 
-hipError_t launch_plan_colscan(const PlanGeom& g, int* blockhist, const int* chan_blocks, int* tile_count,
+hipError_t launch_plan_colscan(const PlanGeom& g, int* blockhist, const int* chan_blocks, int nb, int* tile_count,
                                hipStream_t s) {
     const int64_t ns = static_cast<int64_t>(g.ntiles) * g.nchan + 1;
     hipLaunchKernelGGL(dev::k_plan_colscan, dim3(static_cast<unsigned>((ns + 63) / 64)), dim3(64 * dev::kScanGroups),
-                       0, s, g, blockhist, chan_blocks, tile_count);
+                       0, s, g, blockhist, chan_blocks, nb, tile_count);
     return hipGetLastError();
 }
 
 hipError_t launch_plan_scan(const PlanGeom& g, const int* tile_count, int* tile_start, int* item_start, int4* items,
                             int* flags, int cap, int* host_flags, hipStream_t s) {
-    // Staged through LDS when the counts and two offset arrays fit (and the
-    // per-thread run fits the kernel's registers: ns <= 1024 * 24).
-    const size_t ns = static_cast<size_t>(g.ntiles) * g.nchan + 1;
-    const size_t staged_bytes = (32 + 2 * ns) * sizeof(int);
-    const int staged = (staged_bytes <= kMaxDynLds && ns <= 1024 * 24) ? 1 : 0;
-    const size_t shm = staged ? staged_bytes : 32 * sizeof(int);
+    // Staged through LDS when the counts and two offset arrays fit.
+    const size_t staged = staged_scan_bytes(static_cast<size_t>(g.ntiles) * g.nchan + 1);
+    const size_t shm = staged ? staged : dev::kScanSums * sizeof(int);
     hipLaunchKernelGGL(dev::k_plan_scan, dim3(1), dim3(1024), shm, s, g, tile_count, tile_start, item_start, items,
-                       flags, cap, staged, host_flags);
+                       flags, cap, staged ? 1 : 0, host_flags);
     return hipGetLastError();
 }
 
@@ -788,22 +892,22 @@ int packed_cell_shift(bool f64, int lb) {
 
 namespace {
 template <typename R, bool kDirect>
-void scatter(const double* uv, const int4* blocks, int nb, const PlanGeom& g, const int* tile_start,
-             const int* blockhist, double dlo, int lb, int ms, int kb, int* index, void* offs, hipStream_t s) {
+void scatter(const double* uv, const PlanBlocks& blocks, int nb, const PlanGeom& g, const int* tile_start,
+             const int* blockhist, double dlo, int ms, int kb, int* index, void* offs, hipStream_t s) {
     hipLaunchKernelGGL((dev::k_plan_scatter<R, kDirect>), dim3(nb), dim3(kPlanThreads), (g.ntiles + 1) * sizeof(int), s,
-                       reinterpret_cast<const double2*>(uv), blocks, nb, g, tile_start, blockhist, dlo, lb, ms, kb,
+                       reinterpret_cast<const double2*>(uv), blocks, nb, g, tile_start, blockhist, dlo, ms, kb,
                        index, reinterpret_cast<typename dev::Pack<R>::T2*>(offs));
 }
 }  // namespace
 
-hipError_t launch_plan_scatter(bool f64, bool direct, const double* uv, const int4* blocks, int nb, const PlanGeom& g,
-                               const int* tile_start, const int* blockhist, double dlo, int lb, int ms, int kb,
+hipError_t launch_plan_scatter(bool f64, bool direct, const double* uv, const PlanBlocks& blocks, int nb, const PlanGeom& g,
+                               const int* tile_start, const int* blockhist, double dlo, int ms, int kb,
                                int* index, void* offs, hipStream_t s) {
     if (nb == 0) return hipSuccess;
-    if (f64 && direct) scatter<double, true>(uv, blocks, nb, g, tile_start, blockhist, dlo, lb, ms, kb, index, offs, s);
-    else if (f64) scatter<double, false>(uv, blocks, nb, g, tile_start, blockhist, dlo, lb, ms, kb, index, offs, s);
-    else if (direct) scatter<float, true>(uv, blocks, nb, g, tile_start, blockhist, dlo, lb, ms, kb, index, offs, s);
-    else scatter<float, false>(uv, blocks, nb, g, tile_start, blockhist, dlo, lb, ms, kb, index, offs, s);
+    if (f64 && direct) scatter<double, true>(uv, blocks, nb, g, tile_start, blockhist, dlo, ms, kb, index, offs, s);
+    else if (f64) scatter<double, false>(uv, blocks, nb, g, tile_start, blockhist, dlo, ms, kb, index, offs, s);
+    else if (direct) scatter<float, true>(uv, blocks, nb, g, tile_start, blockhist, dlo, ms, kb, index, offs, s);
+    else scatter<float, false>(uv, blocks, nb, g, tile_start, blockhist, dlo, ms, kb, index, offs, s);
     return hipGetLastError();
 }
 
@@ -894,6 +998,8 @@ hipError_t set_kernel_attributes() {
     // Per-tile histograms of up to 128 x 128 ints; the item sort keeps two per-cell arrays of up to 128 x 128.
     LMG_ATTR(72 * 1024, &dev::k_plan_count);
     LMG_ATTR(kMaxDynLds, &dev::k_plan_scan);
+    LMG_ATTR(kMaxDynLds, &dev::k_plan_small<float>);
+    LMG_ATTR(kMaxDynLds, &dev::k_plan_small<double>);
     LMG_ATTR(72 * 1024, &dev::k_plan_scatter<float, false>);
     LMG_ATTR(72 * 1024, &dev::k_plan_scatter<float, true>);
     LMG_ATTR(72 * 1024, &dev::k_plan_scatter<double, false>);
