@@ -490,17 +490,16 @@ lmg_status wait_plan(const lmg_plan* p, hipStream_t s) {
 // the plan: overwrite the grid (every cell of the window written), or add to
 // it (accumulate: only tiles that receive patches are read and written).
 lmg_status run_grid_entries(const lmg_plan* p, const void* vs, void* grid, void* patches, int* counters, hipStream_t s,
-                            bool band_only, bool accumulate) {
+                            bool counter_zero, bool band_only, bool accumulate) {
     const lmg_table* t = p->table;
     if (wait_plan(p, s) != LMG_OK) return LMG_EHIP;
-    LMG_HIP(launch_zero_ints(counters, 1, s));
     GridArgs a{};
     a.N = p->g.N; a.W = p->g.W; a.T = p->g.T >> p->g.lsub; a.ntx = p->g.ntx << p->g.lsub; a.lsub = p->g.lsub;
     a.Ms = table_ms(t); a.degree = kernel_degree(t);
     a.tab_global = table_global(t, p->prec) ? 1 : 0;
     a.n_items = p->flags + 1; a.max_items = p->max_items << (2 * p->g.lsub); a.npatch = p->npatch; a.waves = p->waves; a.Ft = p->Ft; a.kb = p->kb;
     a.items = p->sub; a.pieces = p->pieces; a.off = p->off; a.coef = p->coef;
-    a.vis = vs; a.patches = patches; a.counter = counters;
+    a.vis = vs; a.patches = patches; a.counter = counters; a.counter_zero = counter_zero ? 1 : 0;
     a.transpose = band_only ? 1 : 0;
     {
         TraceScope ts("grid_items", s);
@@ -530,17 +529,16 @@ lmg_status run_grid(const lmg_plan* p, const void* vis, const float* w, void* gr
     if (wait_plan(p, s) != LMG_OK) return LMG_EHIP;
     {
         TraceScope ts("permute_in", s);
-        LMG_HIP(launch_permute_in(p->prec == LMG_F64, vis, w, p->inv, p->nvis, vs, s));
+        LMG_HIP(launch_permute_in(p->prec == LMG_F64, vis, w, p->inv, p->nvis, vs, counters, s));
     }
-    return run_grid_entries(p, vs, grid, patches, counters, s, band_only, accumulate);
+    return run_grid_entries(p, vs, grid, patches, counters, s, p->nvis > 0, band_only, accumulate);
 }
 
 // Degridding into entry order.
 lmg_status run_degrid_entries(const lmg_plan* p, const void* grid, bool transposed, void* vs, int* counters,
-                              hipStream_t s) {
+                              bool counter_zero, hipStream_t s) {
     const lmg_table* t = p->table;
     if (wait_plan(p, s) != LMG_OK) return LMG_EHIP;
-    LMG_HIP(launch_zero_ints(counters + 1, 1, s));
     DegridArgs a{};
     // FP32 grids by whole tiles also where gridding takes quadrants (16.8M visibilities on 8192^2: 195 us against 223)
     const int lsub = p->prec == LMG_F64 ? p->g.lsub : 0;
@@ -550,6 +548,7 @@ lmg_status run_degrid_entries(const lmg_plan* p, const void* grid, bool transpos
     a.n_items = p->flags + 1; a.max_items = p->max_items << (2 * lsub); a.Ft = p->Ft; a.kb = p->kb;
     a.items = lsub ? p->sub : p->items; a.pieces = p->pieces; a.off = p->off; a.coef = p->coef;
     a.grid = grid; a.transpose = transposed ? 1 : 0; a.vis_out = vs; a.counter = counters + 1;
+    a.counter_zero = counter_zero ? 1 : 0;
     TraceScope ts("degrid_items", s);
     LMG_HIP(launch_degrid(p->prec, a, s));
     return LMG_OK;
@@ -557,8 +556,8 @@ lmg_status run_degrid_entries(const lmg_plan* p, const void* grid, bool transpos
 
 // Degridding, then entry order -> caller order.
 lmg_status run_degrid(const lmg_plan* p, const void* grid, bool transposed, void* vis_out, void* vs, int* counters,
-                      hipStream_t s) {
-    const lmg_status st = run_degrid_entries(p, grid, transposed, vs, counters, s);
+                      bool counter_zero, hipStream_t s) {
+    const lmg_status st = run_degrid_entries(p, grid, transposed, vs, counters, counter_zero, s);
     if (st != LMG_OK) return st;
     TraceScope ts("permute_out", s);
     LMG_HIP(launch_permute_out(p->prec == LMG_F64, vs, p->inv, p->nvis, vis_out, s));
@@ -893,7 +892,7 @@ lmg_status lmg_degrid_planned(const lmg_plan* p, const void* grid, void* vis_out
     if (!scratch_ok(p, LMG_OP_DEGRID, scratch, scratch_bytes)) return LMG_EWORKSPACE;
     const Scratch L = plan_scratch(p, LMG_OP_DEGRID);
     char* sc = static_cast<char*>(scratch);
-    return run_degrid(p, grid, false, vis_out, sc + L.vs, reinterpret_cast<int*>(sc + L.counters),
+    return run_degrid(p, grid, false, vis_out, sc + L.vs, reinterpret_cast<int*>(sc + L.counters), false,
                       static_cast<hipStream_t>(stream));
 }
 
@@ -908,7 +907,7 @@ lmg_status lmg_to_plan_order(const lmg_plan* p, const void* vis, const float* w,
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (wait_plan(p, s) != LMG_OK) return LMG_EHIP;
     TraceScope ts("permute_in", s);
-    LMG_HIP(launch_permute_in(p->prec == LMG_F64, vis, w, p->inv, p->nvis, vis_plan, s));
+    LMG_HIP(launch_permute_in(p->prec == LMG_F64, vis, w, p->inv, p->nvis, vis_plan, nullptr, s));
     return LMG_OK;
 }
 
@@ -928,7 +927,7 @@ lmg_status lmg_grid_planned_ordered(const lmg_plan* p, const void* vis_plan, voi
     const Scratch L = plan_scratch(p, LMG_OP_GRID);
     char* sc = static_cast<char*>(scratch);
     return run_grid_entries(p, vis_plan, grid, sc + L.patches, reinterpret_cast<int*>(sc + L.counters),
-                            static_cast<hipStream_t>(stream), false, accumulate != 0);
+                            static_cast<hipStream_t>(stream), false, false, accumulate != 0);
 }
 
 lmg_status lmg_degrid_planned_ordered(const lmg_plan* p, const void* grid, void* vis_plan_out, void* scratch,
@@ -937,7 +936,7 @@ lmg_status lmg_degrid_planned_ordered(const lmg_plan* p, const void* grid, void*
     if (!scratch_ok(p, LMG_OP_DEGRID, scratch, scratch_bytes)) return LMG_EWORKSPACE;
     const Scratch L = plan_scratch(p, LMG_OP_DEGRID);
     char* sc = static_cast<char*>(scratch);
-    return run_degrid_entries(p, grid, false, vis_plan_out, reinterpret_cast<int*>(sc + L.counters),
+    return run_degrid_entries(p, grid, false, vis_plan_out, reinterpret_cast<int*>(sc + L.counters), false,
                               static_cast<hipStream_t>(stream));
 }
 
@@ -1000,6 +999,7 @@ lmg_status lmg_predict_visibilities_planned(const lmg_plan* p, const void* image
     char* sc = static_cast<char*>(scratch);
     void* grid = sc + L.grid;
     void* tmp = sc + L.tmp;
+    int* counters = reinterpret_cast<int*>(sc + L.counters);
     const bool f64 = p->prec == LMG_F64;
     const size_t cs = cplx_size(p->prec);
     const int r0 = p->band_r0, nr = p->band_r1 - p->band_r0, c0 = p->band_c0, nc = p->band_c1 - p->band_c0;
@@ -1020,12 +1020,13 @@ lmg_status lmg_predict_visibilities_planned(const lmg_plan* p, const void* image
         b.nrows = nc; b.src = tmp; b.src_pitch = M; b.src_blocked = 1; b.in_count = M; b.in_pos = N / 2 - M / 2;
         b.dst = static_cast<char*>(grid) + (static_cast<size_t>(c0) * N + r0) * cs; b.dst_pitch = N; b.straight = 1;
         b.out_count = nr; b.out_pos = r0;
+        b.zero = counters + 1;
         {
             TraceScope ts("fft_cols_forward", s);
             LMG_HIP(launch_fft_pass(f64, b, s));
         }
     }
-    return run_degrid(p, grid, true, vis_out, sc + L.vs, reinterpret_cast<int*>(sc + L.counters), s);
+    return run_degrid(p, grid, true, vis_out, sc + L.vs, counters, nr > 0, s);
 }
 
 lmg_status lmg_workspace_size(int N, int W, double x0, int64_t nvis, lmg_precision prec, int op, size_t* bytes) {

@@ -38,8 +38,11 @@ __global__ __launch_bounds__(kDegridThreads) void k_degrid_items(DegridArgs a) {
     const int cshift = a.Ft + a.kb;
     const int nitems = *a.n_items << (2 * a.lsub);
     for (bool first = true;; first = false) {
-        // the first items are dealt by workgroup, the others from the counter
-        if (threadIdx.x == 0) s_item = first ? blockIdx.x : gridDim.x + atomicAdd(a.counter, 1);
+        // the first items are dealt by workgroup, the others (if there can be any) from the counter
+        if (threadIdx.x == 0) {
+            if (first) s_item = blockIdx.x;
+            else s_item = static_cast<int>(gridDim.x) < a.max_items ? gridDim.x + atomicAdd(a.counter, 1) : nitems;
+        }
         __syncthreads();
         const int item = s_item;
         if (item >= nitems) break;                   // uniform across the workgroup
@@ -104,6 +107,10 @@ hipError_t launch_degrid_w(const DegridArgs& a, hipStream_t s) {
     if (attr != hipSuccess) return attr;
     static std::atomic<uint64_t> resident{0};
     const int nb = std::min(a.max_items, resident_blocks(fn, dev::kDegridThreads, shm, resident));
+    if (nb < a.max_items && !a.counter_zero) {
+        const hipError_t e = launch_zero_ints(a.counter, 1, s);
+        if (e != hipSuccess) return e;
+    }
     hipLaunchKernelGGL((dev::k_degrid_items<R, W, kTab>), dim3(nb), dim3(dev::kDegridThreads), shm, s, a);
     return hipGetLastError();
 }

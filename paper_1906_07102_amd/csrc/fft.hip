@@ -280,6 +280,7 @@ __global__ __launch_bounds__((FftShape<N, ROWS>::kThreads)) void k_fft_pass(FftA
     constexpr int KB = ROWS * nb / NT;
     static_assert(KB >= 1 && KB * NT == ROWS * nb, "butterflies per thread");
     VT* buf = reinterpret_cast<VT*>(smem);
+    if (a.zero && blockIdx.x == 0 && threadIdx.x == 0) *a.zero = 0;
     // Consecutive row blocks go to one XCD, so that its L2 gathers the narrow transposed writes of
     // neighbouring blocks into whole lines.
     const int row0 = xcd_chunk(blockIdx.x, gridDim.x) * ROWS;

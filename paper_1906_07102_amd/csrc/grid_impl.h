@@ -256,8 +256,11 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<Acc, W, kTab>()))) void k_grid
     const PT2* off = reinterpret_cast<const PT2*>(a.off);   // packed offsets, entry order
     const int nitems = *a.n_items << (2 * a.lsub);
     for (bool first = true;; first = false) {
-        // the first items are dealt by workgroup, the others from the counter
-        if (threadIdx.x == 0) s_item = first ? blockIdx.x : gridDim.x + atomicAdd(a.counter, 1);
+        // the first items are dealt by workgroup, the others (if there can be any) from the counter
+        if (threadIdx.x == 0) {
+            if (first) s_item = blockIdx.x;
+            else s_item = static_cast<int>(gridDim.x) < a.max_items ? gridDim.x + atomicAdd(a.counter, 1) : nitems;
+        }
         if (threadIdx.x < S) s_turn[threadIdx.x] = 0;
         for (int i = threadIdx.x; i < S * P2; i += blockDim.x) Acc::zero_cell(&patches[i]);
         __syncthreads();
@@ -526,6 +529,10 @@ hipError_t launch_grid_w(const GridArgs& a, hipStream_t s) {
     if (attr != hipSuccess) return attr;
     static std::atomic<uint64_t> resident{0};
     const int nb = std::min(a.max_items, resident_blocks(fn, 64 * a.waves, shm, resident));
+    if (nb < a.max_items && !a.counter_zero) {
+        const hipError_t e = launch_zero_ints(a.counter, 1, s);
+        if (e != hipSuccess) return e;
+    }
     hipLaunchKernelGGL((dev::k_grid_items<R, Acc, W, kTab>), dim3(nb), dim3(64 * a.waves), shm, s, a);
     return hipGetLastError();
 }

@@ -72,7 +72,8 @@ struct GridArgs {
     const void* vis;       // complex, entry order, weights applied
     void* patches;         // n_items patches of (T + W - 1)^2 cells
     int transpose;         // 1: patches are written transposed (a grid stored with rows along u)
-    int* counter;          // work-item counter, zero at launch
+    int* counter;          // work-item counter
+    int counter_zero;      // 1: an earlier launch zeroed it; 0: the launcher does, where it is read at all
 };
 
 // Threads of an assemble workgroup (512 / 1024 threads: band 37 -> 47 / 72 us, batched 0.84 -> 1.19 /
@@ -106,7 +107,8 @@ struct DegridArgs {
     const void* grid;      // nchan grids of N x N
     int transpose;         // 1: the grid is stored transposed (rows along u)
     void* vis_out;         // entry order
-    int* counter;          // work-item counter, zero at launch
+    int* counter;          // work-item counter
+    int counter_zero;      // 1: an earlier launch zeroed it; 0: the launcher does, where it is read at all
 };
 
 struct FftArgs {
@@ -128,6 +130,7 @@ struct FftArgs {
     const void* h_out;     // per output position, or nullptr
     const void* h_row;     // per source row (index row + row_off), or nullptr
     int row_off;
+    int* zero;             // an int to zero (the work-item counter of the kernel that follows), or nullptr
 };
 
 // What a plan's first launch copies from pinned host memory: up to five arrays (16-byte aligned on both sides, sizes
@@ -173,7 +176,7 @@ size_t packed_offset_bytes(bool f64);
 // Position of the cell bits in a packed offset word for tile edge 2^lb.
 int packed_cell_shift(bool f64, int lb);
 hipError_t launch_permute_in(bool f64, const void* vis, const float* w, const int* inv, int64_t nvis, void* vs,
-                             hipStream_t s);
+                             int* zero, hipStream_t s);
 hipError_t launch_zero_ints(int* p, int n, hipStream_t s);
 hipError_t launch_permute_out(bool f64, const void* vs, const int* inv, int64_t nvis, void* out, hipStream_t s);
 hipError_t launch_grid(lmg_precision prec, const GridArgs& a, hipStream_t s);

@@ -770,12 +770,15 @@ __global__ __launch_bounds__(kPermThreads) void k_plan_compose(const int* __rest
 }
 
 // Caller order -> entry order: vs[inv[k]] = w_k V_k. Reads are sequential;
-// the writes of one block land in a few runs per footprint cell.
+// the writes of one block land in a few runs per footprint cell. `zero` (or
+// nullptr): the work-item counter of the gridding launch that follows, which
+// would otherwise take a launch of its own.
 template <typename R>
 __global__ __launch_bounds__(kPermThreads) void k_permute_in(const typename C2<R>::T* __restrict__ vis, const float* __restrict__ w,
                                                     const int* __restrict__ inv, int64_t nvis,
-                                                    typename C2<R>::T* __restrict__ vs) {
+                                                    typename C2<R>::T* __restrict__ vs, int* zero) {
     const int64_t k = static_cast<int64_t>(xcd_chunk(blockIdx.x, gridDim.x)) * blockDim.x + threadIdx.x;
+    if (zero && k == 0) *zero = 0;
     if (k >= nvis) return;
     const int d = nt_load(inv + k);
     if (d < 0) return;
@@ -960,15 +963,15 @@ hipError_t launch_plan_compose(const int* inv0, const int* pos2, int64_t nvis, i
 }
 
 hipError_t launch_permute_in(bool f64, const void* vis, const float* w, const int* inv, int64_t nvis, void* vs,
-                             hipStream_t s) {
+                             int* zero, hipStream_t s) {
     if (nvis == 0) return hipSuccess;
     const unsigned nb = static_cast<unsigned>((nvis + dev::kPermThreads - 1) / dev::kPermThreads);
     if (f64)
         hipLaunchKernelGGL(dev::k_permute_in<double>, dim3(nb), dim3(dev::kPermThreads), 0, s,
-                           reinterpret_cast<const double2*>(vis), w, inv, nvis, reinterpret_cast<double2*>(vs));
+                           reinterpret_cast<const double2*>(vis), w, inv, nvis, reinterpret_cast<double2*>(vs), zero);
     else
         hipLaunchKernelGGL(dev::k_permute_in<float>, dim3(nb), dim3(dev::kPermThreads), 0, s,
-                           reinterpret_cast<const float2*>(vis), w, inv, nvis, reinterpret_cast<float2*>(vs));
+                           reinterpret_cast<const float2*>(vis), w, inv, nvis, reinterpret_cast<float2*>(vs), zero);
     return hipGetLastError();
 }
 
