@@ -482,6 +482,7 @@ lmg_status ensure_flags(const lmg_plan* p) {
 // A planned call on another stream than the plan's creation waits (on the
 // device) for the plan's kernels.
 lmg_status wait_plan(const lmg_plan* p, hipStream_t s) {
+    if (!p->ready) return LMG_OK;                      // a one-shot call's plan: made and used on one stream
     LMG_HIP(hipStreamWaitEvent(s, p->ready, 0));
     return LMG_OK;
 }
@@ -588,8 +589,11 @@ bool scratch_ok(const lmg_plan* p, int op, void* scratch, size_t bytes) {
 
 // Plan for nchan channels; channel c owns visibilities [offsets[c], offsets[c + 1]) and grid c.
 // tile = 0 picks the default tile edge; otherwise a power of two in [8, min(128, N)] with N / tile <= 128.
+// With `counts` false the host never learns the plan's counts, and the plan is used on this stream only: images are made
+// over the whole grid, and neither its use nor its end waits for the device.
 lmg_status create_plan(const lmg_table* table, int N, lmg_precision prec, int nchan, const int64_t* offsets,
-                       const double* uv, int tile, void* workspace, size_t ws_bytes, void* stream, lmg_plan** out) {
+                       const double* uv, int tile, void* workspace, size_t ws_bytes, void* stream, lmg_plan** out,
+                       bool counts = true) {
     int M = 0;
     if (!table || !out || !offsets || prec < LMG_F32 || prec > LMG_F64 || nchan < 1 || nchan > kMaxChannels ||
         !valid_grid(N, table->W, table->x0, &M))
@@ -736,7 +740,7 @@ lmg_status create_plan(const lmg_table* table, int N, lmg_precision prec, int nc
         }
     }
     const bool direct = nvis <= kDirectPlanVis;
-    p->host_flags = take_flag_slot();
+    if (counts) p->host_flags = take_flag_slot();
     if (small_plan(p->g, nvis)) {
         TraceScope ts("plan_small", s);
         LMG_HIP(launch_plan_small(prec == LMG_F64, uv, p->g, static_cast<int>(nvis), p->tile_start, p->item_start, p->items,
@@ -780,6 +784,16 @@ lmg_status create_plan(const lmg_table* table, int N, lmg_precision prec, int nc
     if (!direct) {
         TraceScope ts("plan_compose", s);
         LMG_HIP(launch_plan_compose(p->inv0, p->pos2, nvis, p->inv, s));
+    }
+    if (!counts) {
+        int dev = 0;
+        LMG_HIP(hipGetDevice(&dev));
+        table->unwaited.fetch_or(uint64_t(1) << (dev & 63));
+        p->n_busy = nvis > 0 ? 1 : 0;
+        set_band(p.get(), 0, p->g.ntx - 1, 0, p->g.ntx - 1);
+        p->flags_read = true;
+        *out = p.release();
+        return LMG_OK;
     }
     // The counts came back with the scan; the host reads them when it first needs them.
     hipEvent_t ready = nullptr;
@@ -1045,6 +1059,12 @@ lmg_status lmg_workspace_size(int N, int W, double x0, int64_t nvis, lmg_precisi
 }  // extern "C"
 
 namespace {
+// Largest grid on which a one-shot image call transforms the whole grid rather than wait for the band its
+// visibilities occupy: the wait drains the queue and holds the host for the plan's kernels (dirty image and
+// prediction, whole against waiting: 2,000 visibilities on 128^2 90 and 114 us, 201,600 on 1024^2 204 and 216; 1.0M on
+// 2048^2 277 and 273, in FP64 419 and 390).
+constexpr int kWholeImageN = 1024;
+
 template <typename F>
 lmg_status one_shot(const lmg_table* t, int N, lmg_precision prec, int64_t nvis, const double* uv, void* ws,
                     size_t ws_bytes, void* stream, int op, F&& body) {
@@ -1056,7 +1076,9 @@ lmg_status one_shot(const lmg_table* t, int N, lmg_precision prec, int64_t nvis,
     size_t pbytes = 0;
     lmg_plan_workspace_size(N, t->W, nvis, prec, &pbytes);
     lmg_plan* p = nullptr;
-    st = lmg_plan_create(t, N, prec, nvis, uv, ws, pbytes, stream, &p);
+    const int64_t offsets[2] = {0, nvis};
+    const bool counts = (op == LMG_OP_DIRTY || op == LMG_OP_PREDICT) && N > kWholeImageN;
+    st = create_plan(t, N, prec, 1, offsets, uv, 0, ws, pbytes, stream, &p, counts);
     if (st != LMG_OK) return st;
     st = body(p, static_cast<char*>(ws) + pbytes, ws_bytes - pbytes);
     lmg_plan_destroy(p);
@@ -1076,7 +1098,7 @@ lmg_status one_shot_batched(const lmg_table* t, int N, lmg_precision prec, int n
     size_t pbytes = 0;
     lmg_batch_workspace_size(N, t->W, nchan, offsets[nchan], prec, &pbytes);
     lmg_plan* p = nullptr;
-    st = create_plan(t, N, prec, nchan, offsets, uv, choose_tile(N, t->W), ws, pbytes, stream, &p);
+    st = create_plan(t, N, prec, nchan, offsets, uv, choose_tile(N, t->W), ws, pbytes, stream, &p, false);
     if (st != LMG_OK) return st;
     st = body(p, static_cast<char*>(ws) + pbytes, ws_bytes - pbytes);
     lmg_plan_destroy(p);
