@@ -482,7 +482,6 @@ lmg_status ensure_flags(const lmg_plan* p) {
 // A planned call on another stream than the plan's creation waits (on the
 // device) for the plan's kernels.
 lmg_status wait_plan(const lmg_plan* p, hipStream_t s) {
-    if (!p->ready) return LMG_OK;                      // a one-shot call's plan: made and used on one stream
     LMG_HIP(hipStreamWaitEvent(s, p->ready, 0));
     return LMG_OK;
 }
@@ -589,8 +588,8 @@ bool scratch_ok(const lmg_plan* p, int op, void* scratch, size_t bytes) {
 
 // Plan for nchan channels; channel c owns visibilities [offsets[c], offsets[c + 1]) and grid c.
 // tile = 0 picks the default tile edge; otherwise a power of two in [8, min(128, N)] with N / tile <= 128.
-// With `counts` false the host never learns the plan's counts, and the plan is used on this stream only: images are made
-// over the whole grid, and neither its use nor its end waits for the device.
+// With `counts` false the host never learns the plan's counts, and images are made over the whole grid: no call through
+// the plan waits for the device (its end does, for the plan's kernels).
 lmg_status create_plan(const lmg_table* table, int N, lmg_precision prec, int nchan, const int64_t* offsets,
                        const double* uv, int tile, void* workspace, size_t ws_bytes, void* stream, lmg_plan** out,
                        bool counts = true) {
@@ -786,14 +785,9 @@ lmg_status create_plan(const lmg_table* table, int N, lmg_precision prec, int nc
         LMG_HIP(launch_plan_compose(p->inv0, p->pos2, nvis, p->inv, s));
     }
     if (!counts) {
-        int dev = 0;
-        LMG_HIP(hipGetDevice(&dev));
-        table->unwaited.fetch_or(uint64_t(1) << (dev & 63));
         p->n_busy = nvis > 0 ? 1 : 0;
         set_band(p.get(), 0, p->g.ntx - 1, 0, p->g.ntx - 1);
         p->flags_read = true;
-        *out = p.release();
-        return LMG_OK;
     }
     // The counts came back with the scan; the host reads them when it first needs them.
     hipEvent_t ready = nullptr;
@@ -802,7 +796,7 @@ lmg_status create_plan(const lmg_table* table, int N, lmg_precision prec, int nc
     if (rec != hipSuccess) (void)hipEventDestroy(ready);
     LMG_HIP(rec);
     p->ready = ready;
-    if (!p->host_flags) {                                  // no pinned memory: read back synchronously
+    if (counts && !p->host_flags) {                        // no pinned memory: read back synchronously
         static thread_local int fallback[8];
         LMG_HIP(hipMemcpyAsync(fallback, p->flags, sizeof(fallback), hipMemcpyDeviceToHost, s));
         LMG_HIP(hipStreamSynchronize(s));
@@ -1060,9 +1054,9 @@ lmg_status lmg_workspace_size(int N, int W, double x0, int64_t nvis, lmg_precisi
 
 namespace {
 // Largest grid on which a one-shot image call transforms the whole grid rather than wait for the band its
-// visibilities occupy: the wait drains the queue and holds the host for the plan's kernels (dirty image and
-// prediction, whole against waiting: 2,000 visibilities on 128^2 90 and 114 us, 201,600 on 1024^2 204 and 216; 1.0M on
-// 2048^2 277 and 273, in FP64 419 and 390).
+// visibilities occupy: that wait, in the middle of the call, drains the queue; the wait for the plan at the call's end
+// finds the rest queued (dirty image and prediction, waiting against whole: 2,000 visibilities on 128^2 114 and 103 us,
+// 201,600 on 1024^2 214 and 210; 1.0M on 2048^2 273 and 283, in FP64 390 and 421).
 constexpr int kWholeImageN = 1024;
 
 template <typename F>
@@ -1077,7 +1071,15 @@ lmg_status one_shot(const lmg_table* t, int N, lmg_precision prec, int64_t nvis,
     lmg_plan_workspace_size(N, t->W, nvis, prec, &pbytes);
     lmg_plan* p = nullptr;
     const int64_t offsets[2] = {0, nvis};
-    const bool counts = (op == LMG_OP_DIRTY || op == LMG_OP_PREDICT) && N > kWholeImageN;
+    bool counts = false;
+    if (op == LMG_OP_DIRTY || op == LMG_OP_PREDICT) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;       // a capture still meets the wait, which refuses it
+        if (hipStreamIsCapturing(static_cast<hipStream_t>(stream), &cap) != hipSuccess) {
+            (void)hipGetLastError();
+            cap = hipStreamCaptureStatusActive;
+        }
+        counts = N > kWholeImageN || cap != hipStreamCaptureStatusNone;
+    }
     st = create_plan(t, N, prec, 1, offsets, uv, 0, ws, pbytes, stream, &p, counts);
     if (st != LMG_OK) return st;
     st = body(p, static_cast<char*>(ws) + pbytes, ws_bytes - pbytes);

@@ -1,7 +1,6 @@
 // Internal definitions shared by the host table code and the HIP kernels.
 #pragma once
 
-#include <atomic>
 #include <cstddef>
 #include <cstdint>
 #include <map>
@@ -56,8 +55,6 @@ struct lmg_table {
         size_t coef_bytes = 0, twiddle_bytes = 0, hpix_bytes = 0;
     };
     mutable std::map<std::pair<int, int>, Pinned> pinned;
-    // Devices (modulo 64) on which calls that did not wait for their plan read the pinned copies.
-    mutable std::atomic<uint64_t> unwaited{0};
     ~lmg_table();
 };
 

@@ -734,17 +734,6 @@ const char* lmg_status_string(lmg_status s) {
 }  // extern "C"
 
 lmg_table::~lmg_table() {
-    if (const uint64_t devices = unwaited.load()) {    // plans whose copies from the pinned constants nobody waited for
-        int current = 0, n = 0;
-        if (hipGetDevice(&current) == hipSuccess && hipGetDeviceCount(&n) == hipSuccess) {
-            for (int d = 0; d < n; ++d)
-                if ((devices >> (d & 63)) & 1) {
-                    (void)hipSetDevice(d);
-                    (void)hipDeviceSynchronize();
-                }
-            (void)hipSetDevice(current);
-        }
-    }
     for (auto& kv : pinned)
         if (kv.second.host) (void)hipHostFree(kv.second.host);
 }

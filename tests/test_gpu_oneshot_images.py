@@ -1,4 +1,4 @@
-"""Image calls without a plan: over the whole grid up to 1024^2, over the occupied band above, with no wait in between."""
+"""Image calls without a plan: over the whole grid up to 1024^2, over the occupied band above."""
 import gc
 
 import numpy as np
