@@ -268,8 +268,9 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<Acc, W, kTab>()))) void k_grid
         if (item >= nitems) break;                       // uniform across the workgroup
         const int4 it = a.items[item];
         // entries whose loads are issued together (FP64 at W = 7 with 1 / 2: 16.8M visibilities 453 / 460 us, 3.0M of
-        // one density 138 / 145; with 4 it spills at two waves per SIMD)
-        constexpr int kB = sizeof(R) == 8 && W <= 8 ? 1 : 4;
+        // one density 138 / 145; with 4 it spills at two waves per SIMD; direct weights, 8.4M, W = 5 with 1 / 2 / 4:
+        // 772 / 702 / 705, W = 8: 2165 / 1928 / 2321)
+        constexpr int kB = sizeof(R) == 8 && W <= 8 ? (kTab == kTabDirect ? 2 : 1) : 4;
         const int np = it.w & 0xffff, fturns = it.w >> 16;  // pieces; turns of full pieces only
         const int turns = (np + 63) >> 6;
         auto piece_of = [&](int j) { return j < fturns ? lane * fturns + j : j * 64 + lane; };
