@@ -37,9 +37,10 @@ hipError_t launch_assemble(lmg_precision prec, const AssembleArgs& args, hipStre
     a.rows = (tiles > 32768 || whole_grid) ? std::min(a.T, 1024 / a.T) : std::min(a.T, 16);
     // Whole grids of a batch: runs of grid rows, tile by tile (two cells of a tile per thread: 256 channels of 1024^2
     // overwritten / added to 622 / 354 us; one cell 631 / 476, four 821 / 493, and 818 / 552 tile by tile), while that
-    // still makes 2,048 workgroups (48 channels added to: 78 us against 93 tile by tile).
+    // still makes 2,048 workgroups (48 channels added to: 78 us against 93 tile by tile). Its item ranges are those of
+    // tile rows along v: an image's transposed grid goes tile by tile.
     a.rows_kernel = 0;
-    if (a.trows == a.ntx && a.tcols == a.ntx && a.tr0 == 0 && a.tc0 == 0) {
+    if (!a.transpose && a.trows == a.ntx && a.tcols == a.ntx && a.tr0 == 0 && a.tc0 == 0) {
         const int rr = std::max(1, std::min(a.T, 2 * kAssembleThreads / a.T));
         if (static_cast<int64_t>(a.nchan) * (a.N / rr) >= 2048) {
             a.rows = rr;
