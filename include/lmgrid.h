@@ -341,7 +341,8 @@ lmg_status lmg_degrid_batched(const lmg_table* t, int N, lmg_precision prec, int
 /* ------------------------------------------------------- 2D FFT building block
  * Centred 2D transform F[q][p] = sum_{m,n} G[m][n] exp(sign i 2 pi (n p + m q) / N)
  * of an N x N device array in place of `data` (all indices centred in
- * [-N/2, N/2)); sign = +1 or -1. scratch: N*N complex device elements. */
+ * [-N/2, N/2)); sign = +1 or -1. scratch: N*N complex device elements (the twiddles
+ * lie in a device array of the library, 384 KiB for all sizes and both precisions). */
 lmg_status lmg_fft2_centred(int N, lmg_precision prec, int sign, void* data, void* scratch, void* stream);
 
 /* ------------------------------------------------------------------ tracing

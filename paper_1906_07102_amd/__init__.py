@@ -910,8 +910,7 @@ def fft2_centred(data, sign: int, stream=None):
         raise TypeError("data must be complex64 or complex128")
     _check_tensor(data, "data", data.dtype, (N, N))
     prec = _prec_of(data.dtype, False)
-    cs = 16 if prec == F64 else 8
-    scratch = _bytes(((N * N * cs + 255) // 256) * 256 + N * cs, data.device)
+    scratch = _bytes(N * N * (16 if prec == F64 else 8), data.device)
     _check(load().lmg_fft2_centred(N, prec, sign, _ptr(data), _ptr(scratch), _stream_handle(stream)),
            "lmg_fft2_centred")
     return data

@@ -1176,13 +1176,9 @@ lmg_status lmg_fft2_centred(int N, lmg_precision prec, int sign, void* data, voi
     if (ensure_attributes() != hipSuccess) return LMG_EHIP;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const bool f64 = prec == LMG_F64;
-    const size_t cs = cplx_size(prec);
-    void* tw = static_cast<char*>(scratch) + align_up(static_cast<size_t>(N) * N * cs);
-    if (f64) {
-        if (upload(tw, twiddles_f64(N).data(), 2 * sizeof(double) * N, s) != LMG_OK) return LMG_EHIP;
-    } else {
-        if (upload(tw, twiddles_f32(N).data(), 2 * sizeof(float) * N, s) != LMG_OK) return LMG_EHIP;
-    }
+    const void* host = f64 ? static_cast<const void*>(twiddles_f64(N).data()) : twiddles_f32(N).data();
+    void* tw = nullptr;
+    LMG_HIP(fft2_twiddles(f64, N, host, &tw, s));
     FftArgs a = fft_args(N, sign, tw);
     a.nrows = N; a.src = data; a.src_pitch = N; a.in_count = N; a.in_pos = 0;
     a.dst = scratch; a.dst_pitch = N; a.dst_blocked = 1; a.out_count = N; a.out_pos = 0;

@@ -1,9 +1,16 @@
 // Centred 2D FFT passes (Stockham radix 8, LDS-resident rows) with the correction,
 // crop and zero pad fused into their loads and stores.
+#include <mutex>
+
 #include "dev_common.h"
 
 namespace lmg {
 namespace dev {
+
+// Twiddles of the transform that a caller runs by itself (fft2_twiddles): its scratch holds the N x N intermediate and
+// nothing else. N elements from element N on for each N = 4 .. 8192.
+__device__ float2 g_twiddles32[2 * 8192];
+__device__ double2 g_twiddles64[2 * 8192];
 
 // ------------------------------------------------------------------ FFT
 // One pass of the centred 2D transform: ROWS rows of `src` (`in_count` values
@@ -449,6 +456,25 @@ hipError_t launch_fft_t(const FftArgs& a, hipStream_t s) {
     return hipErrorInvalidValue;
 }
 }  // namespace
+
+hipError_t fft2_twiddles(bool f64, int N, const void* host, void** out, hipStream_t s) {
+    constexpr int kMaxDevices = 64;
+    static std::mutex mu;
+    static void* base[kMaxDevices][2] = {};
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
+    {
+        std::lock_guard<std::mutex> lk(mu);
+        void*& p = base[dev][f64 ? 1 : 0];
+        if (!p) e = f64 ? hipGetSymbolAddress(&p, HIP_SYMBOL(dev::g_twiddles64)) : hipGetSymbolAddress(&p, HIP_SYMBOL(dev::g_twiddles32));
+        if (e != hipSuccess) return e;
+        *out = static_cast<char*>(p) + static_cast<size_t>(N) * (f64 ? sizeof(double2) : sizeof(float2));
+    }
+    return hipMemcpyAsync(*out, host, static_cast<size_t>(N) * (f64 ? sizeof(double2) : sizeof(float2)),
+                          hipMemcpyHostToDevice, s);
+}
 
 hipError_t launch_fft_pass(bool f64, const FftArgs& a, hipStream_t s) {
     if (a.nrows == 0) return hipSuccess;

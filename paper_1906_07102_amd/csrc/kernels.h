@@ -182,6 +182,9 @@ hipError_t launch_permute_out(bool f64, const void* vs, const int* inv, int64_t 
 hipError_t launch_grid(lmg_precision prec, const GridArgs& a, hipStream_t s);
 hipError_t launch_assemble(lmg_precision prec, const AssembleArgs& a, hipStream_t s);
 hipError_t launch_degrid(lmg_precision prec, const DegridArgs& a, hipStream_t s);
+// The library's own device copy of the N host twiddles (FFT stage order) on the current device, for a transform outside
+// of a plan. Every call enqueues the copy before its passes; calls on several streams write the same bytes.
+hipError_t fft2_twiddles(bool f64, int N, const void* host, void** out, hipStream_t s);
 hipError_t launch_fft_pass(bool f64, const FftArgs& a, hipStream_t s);
 hipError_t set_kernel_attributes();
 // Read (and, if set, clear) the device-wide flag the plans raise on non-finite coordinates, on the
