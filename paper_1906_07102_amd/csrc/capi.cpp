@@ -40,6 +40,7 @@ struct lmg_plan {
     int M = 0;                  // retained image size 2 x0 N
     int npatch = 1;             // LDS patches per gridding workgroup
     int waves = 0;              // waves per gridding workgroup
+    bool by_entry = false;      // patches numbered by their items' first entries, not by item
     int nchan = 1;              // channels (grids), each with its own run of visibilities
     int nblocks = 0;            // plan blocks (runs of <= plan_block_vis() visibilities of one channel)
     mutable bool bad_data = false;
@@ -213,9 +214,19 @@ struct Scratch {
 };
 constexpr int kCounters = 2;    // work-item counters of the gridding and degridding kernels
 
-Scratch scratch_layout(int N, int W, int T, int lsub, int M, int items, int64_t nvis, lmg_precision prec, int op) {
+// Most work items of a plan: its tiles (only those with visibilities have items), plus one per cap visibilities.
+int64_t most_items(int N, int T, int nchan, int64_t nvis, int cap) {
+    return std::min<int64_t>(static_cast<int64_t>(N / T) * (N / T) * nchan, nvis) + (nvis + cap - 1) / cap + 1;
+}
+
+// Quadrants' patches are numbered by their first entries where a plan has fewer visibilities than quadrants (most are
+// empty then): a sparse plan's scratch is no larger than with whole tiles, and the allocation-free call takes it.
+bool patches_by_entry(int lsub, int64_t items, int64_t nvis) { return lsub > 0 && nvis < (items << (2 * lsub)); }
+
+Scratch scratch_layout(int N, int W, int T, int lsub, int M, int64_t items, int64_t nvis, lmg_precision prec, int op) {
     const size_t P = static_cast<size_t>((T >> lsub) + W - 1);
-    const size_t patches = align_up((static_cast<size_t>(items) << (2 * lsub)) * P * P * patch_cell_size(prec));
+    const int64_t npatches = patches_by_entry(lsub, items, nvis) ? nvis : items << (2 * lsub);
+    const size_t patches = align_up(static_cast<size_t>(npatches) * P * P * patch_cell_size(prec));
     const size_t grid = align_up(static_cast<size_t>(N) * N * cplx_size(prec));
     const size_t tmp = align_up(static_cast<size_t>((M + 3) / 4 * 4) * N * cplx_size(prec));     // blocks of four rows
     const size_t vs = align_up(static_cast<size_t>(nvis + kRunPad) * cplx_size(prec));
@@ -499,7 +510,7 @@ lmg_status run_grid_entries(const lmg_plan* p, const void* vs, void* grid, void*
     a.tab_global = table_global(t, p->prec) ? 1 : 0;
     a.n_items = p->flags + 1; a.max_items = p->max_items << (2 * p->g.lsub); a.npatch = p->npatch; a.waves = p->waves; a.Ft = p->Ft; a.kb = p->kb;
     a.items = p->sub; a.pieces = p->pieces; a.off = p->off; a.coef = p->coef;
-    a.vis = vs; a.patches = patches; a.counter = counters; a.counter_zero = counter_zero ? 1 : 0;
+    a.vis = vs; a.patches = patches; a.by_entry = p->by_entry ? 1 : 0; a.counter = counters; a.counter_zero = counter_zero ? 1 : 0;
     a.transpose = band_only ? 1 : 0;
     {
         TraceScope ts("grid_items", s);
@@ -517,7 +528,7 @@ lmg_status run_grid_entries(const lmg_plan* p, const void* vs, void* grid, void*
     } else {
         b.tr0 = 0; b.trows = a.ntx; b.tc0 = 0; b.tcols = a.ntx;
     }
-    b.item_start = p->item_start; b.patches = patches; b.grid = grid;
+    b.item_start = p->item_start; b.sub = p->by_entry ? p->sub : nullptr; b.patches = patches; b.grid = grid;
     TraceScope ts("assemble", s);
     LMG_HIP(launch_assemble(p->prec, b, s));
     return LMG_OK;
@@ -573,11 +584,8 @@ FftArgs fft_args(int N, int sign, const void* tw) {
 }
 
 Scratch plan_scratch(const lmg_plan* p, int op) {
-    // Sized for the most work items this plan can have (its tiles, plus one per cap visibilities), so
-    // that no query waits for its counts.
-    const int64_t bound = std::min<int64_t>(static_cast<int64_t>(p->g.ntiles) * p->nchan, p->nvis) +
-                          (p->nvis + p->cap - 1) / p->cap + 1;
-    return scratch_layout(p->g.N, p->g.W, p->g.T, p->g.lsub, p->M, static_cast<int>(std::min<int64_t>(bound, p->max_items)),
+    // Sized for the most work items this plan can have, so that no query waits for its counts.
+    return scratch_layout(p->g.N, p->g.W, p->g.T, p->g.lsub, p->M, most_items(p->g.N, p->g.T, p->nchan, p->nvis, p->cap),
                           p->nvis, p->prec, op);
 }
 
@@ -610,16 +618,10 @@ lmg_status create_plan(const lmg_table* table, int N, lmg_precision prec, int nc
     if (T < table->W || N / T > 128) return LMG_ENOTSUP;      // cannot happen for N >= 2W, N <= 8192
     const int cap = choose_cap();
     const int Ms = staged_ms(table, prec);
-    // Quadrants, unless their patches alone would take the plan out of reach of the allocation-free call.
-    int lsub = tile_lsub(N, T, prec);
-    if (lsub) {
-        const int64_t bound = std::min<int64_t>(static_cast<int64_t>(N / T) * (N / T) * nchan, nvis) + (nvis + cap - 1) / cap + 1;
-        const int items = static_cast<int>(std::min<int64_t>(bound, INT32_MAX / 4));
-        auto fits = [&](int l) {
-            return scratch_layout(N, table->W, T, l, M, items, nvis, prec, LMG_OP_GRID).total <= LMG_STATIC_SCRATCH_BYTES;
-        };
-        if (bound > INT32_MAX / 4 || (fits(0) && !fits(1))) lsub = 0;
-    }
+    // A function of the grid, the tile and the mode: the order of the sums depends on it, and a batch's channel has the
+    // bits of that channel alone. (Item numbers past 31 bits take more channels than a device holds grids of.)
+    const int64_t items = most_items(N, T, nchan, nvis, cap);
+    const int lsub = items <= INT32_MAX / 4 ? tile_lsub(N, T, prec) : 0;
     const int Tq = T >> lsub;
     int npatch = fit_patches(Tq, prec, table->W, Ms);
     const int waves = fit_waves(Tq, N, nchan, nvis, cap, prec, table->W, &npatch);
@@ -636,6 +638,7 @@ lmg_status create_plan(const lmg_table* table, int N, lmg_precision prec, int nc
     p->g.N = N; p->g.W = table->W; p->g.T = T; p->g.ntx = N / T; p->g.ntiles = (N / T) * (N / T);
     p->g.nchan = nchan;
     p->g.lsub = lsub;
+    p->by_entry = patches_by_entry(lsub, items, nvis);
     p->g.ref = tap_reference(table->W);
     p->waves = waves;
     p->npatch = npatch;

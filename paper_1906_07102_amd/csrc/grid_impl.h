@@ -339,8 +339,9 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<Acc, W, kTab>()))) void k_grid
             }
         }
         __syncthreads();
-        Cell* out = reinterpret_cast<Cell*>(a.patches) + static_cast<size_t>(item) * P2;
-        for (int i = threadIdx.x; i < P2; i += blockDim.x) {
+        Cell* out = reinterpret_cast<Cell*>(a.patches) + static_cast<size_t>(a.by_entry ? it.y : item) * P2;
+        const int nout = a.by_entry && it.z == 0 ? 0 : P2;
+        for (int i = threadIdx.x; i < nout; i += blockDim.x) {
             const int row = __umulhi(static_cast<unsigned>(i), inv_p);
             const int from = a.transpose ? (i - row * P) * P + row : i;
             typename Acc::Sum sum;
@@ -406,17 +407,24 @@ __device__ __forceinline__ void tile_cells(const AssembleArgs& a, typename C2<R>
             const int pc = lc + ((s & 1) ? a.T : 0);
             for (int it = first[s]; it < end[s]; it += kU * step) {
                 Cell c[kU][KC];
+                int slot[kU];                                    // the patch of item it + u step, -1: none
+#pragma unroll
+                for (int u = 0; u < kU; ++u) {
+                    const int i = it + u * step;
+                    slot[u] = i < end[s] ? i : -1;
+                    if (a.sub && i < end[s]) slot[u] = a.sub[i].z > 0 ? a.sub[i].y : -1;     // uniform
+                }
 #pragma unroll
                 for (int u = 0; u < kU; ++u)
 #pragma unroll
                     for (int k = 0; k < KC; ++k)
-                        if (it + u * step < end[s] && on[k] && (s < 2 || lr[k] < halo))
-                            c[u][k] = patches[(static_cast<size_t>(it + u * step) * P + lr[k] + (s >= 2 ? a.T : 0)) * P + pc];
+                        if (slot[u] >= 0 && on[k] && (s < 2 || lr[k] < halo))
+                            c[u][k] = patches[(static_cast<size_t>(slot[u]) * P + lr[k] + (s >= 2 ? a.T : 0)) * P + pc];
 #pragma unroll
                 for (int u = 0; u < kU; ++u)
 #pragma unroll
                     for (int k = 0; k < KC; ++k)
-                        if (it + u * step < end[s] && on[k] && (s < 2 || lr[k] < halo)) sum[k].add(c[u][k]);
+                        if (slot[u] >= 0 && on[k] && (s < 2 || lr[k] < halo)) sum[k].add(c[u][k]);
             }
         }
 #pragma unroll

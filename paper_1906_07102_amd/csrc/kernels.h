@@ -70,7 +70,8 @@ struct GridArgs {
     const void* off;       // packed offsets (uint2 or ulonglong2), entry order
     const void* coef;      // coefficient table, float or double; FP64 expansion for a direct table
     const void* vis;       // complex, entry order, weights applied
-    void* patches;         // n_items patches of (T + W - 1)^2 cells
+    void* patches;         // patches of (T + W - 1)^2 cells, one per work item
+    int by_entry;          // 1: an item's patch is numbered by its first entry (and an empty item has none), 0: by the item
     int transpose;         // 1: patches are written transposed (a grid stored with rows along u)
     int* counter;          // work-item counter
     int counter_zero;      // 1: an earlier launch zeroed it; 0: the launcher does, where it is read at all
@@ -89,6 +90,7 @@ struct AssembleArgs {
     int transpose;                // 1: patches and grid are transposed (grid rows along u, tiles' rows along u)
     int accumulate;               // 1: add to the grid's values; 0: overwrite every cell of the window
     const int* item_start;   // per plan tile, ntiles + 1
+    const int4* sub;         // the work items, where patches are numbered by their first entries; else nullptr
     const void* patches;
     void* grid;
 };
