@@ -545,14 +545,22 @@ lmg_status run_grid(const lmg_plan* p, const void* vis, const float* w, void* gr
     return run_grid_entries(p, vs, grid, patches, counters, s, p->nvis > 0, band_only, accumulate);
 }
 
+// Degridding by the quadrants of a plan that grids by quadrants: dense FP64 data at W = 6 .. 8. The fill of four small
+// patches costs more than that of a large one, so sparse data go by whole tiles: 8192^2 in FP64, whole / quadrants, 1.0M
+// visibilities at W = 7 70 / 119 us, 3.0M 113 / 132 (W = 8 240 / 226), 6.0M 234 / 219, 16.8M 348 / 317 (W = 5 267 / 250,
+// but 6.0M 187 / 215; W = 3 151 / 199, 9 488 / 547). FP32 grids' patches are half as large (16.8M 195 / 223). Each visibility's sum is its own, so
+// the results are the same bits.
+bool degrid_by_quadrants(const lmg_plan* p) {
+    return p->prec == LMG_F64 && p->g.W >= 6 && p->g.W <= 8 && p->nvis >= 6000000;
+}
+
 // Degridding into entry order.
 lmg_status run_degrid_entries(const lmg_plan* p, const void* grid, bool transposed, void* vs, int* counters,
                               bool counter_zero, hipStream_t s) {
     const lmg_table* t = p->table;
     if (wait_plan(p, s) != LMG_OK) return LMG_EHIP;
     DegridArgs a{};
-    // FP32 grids by whole tiles also where gridding takes quadrants (16.8M visibilities on 8192^2: 195 us against 223)
-    const int lsub = p->prec == LMG_F64 ? p->g.lsub : 0;
+    const int lsub = degrid_by_quadrants(p) ? p->g.lsub : 0;
     a.N = p->g.N; a.W = p->g.W; a.T = p->g.T >> lsub; a.ntx = p->g.ntx << lsub; a.lsub = lsub;
     a.Ms = table_ms(t); a.degree = kernel_degree(t);
     a.tab_global = table_global(t, p->prec) ? 1 : 0;

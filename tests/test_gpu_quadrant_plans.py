@@ -85,3 +85,18 @@ def test_sparse_grids_and_images(prec, W, n):
     ref = torch.from_numpy(im.degrid(uv, G.cpu().numpy(), otab)).to(DEV)
     assert close(plan.predict_visibilities(model.to(ctype(prec))), ref)
     assert close(plan.degrid(G.to(ctype(prec))), ref)
+
+
+@pytest.mark.parametrize("W", [6, 8])
+def test_degridding_by_quadrants(W):
+    """6,000,003 visibilities in FP64, which are degridded by quadrants, give the bits of the same visibilities in two plans
+    of half as many, which are degridded by whole tiles."""
+    print(f"degridding by quadrants W={W}", flush=True)
+    n = 6_000_003
+    gtab = lmg.Table.create(W, 0.25, 300, 3)
+    g = torch.Generator(device=DEV).manual_seed(W)
+    uv = torch.rand(n, 2, generator=g, device=DEV, dtype=torch.float64) * 8192 - 4096
+    grid = torch.randn(N, N, generator=g, device=DEV, dtype=torch.complex128)
+    out = lmg.Plan(gtab, N, uv, lmg.F64).degrid(grid)
+    for a, b in ((0, n // 2), (n // 2, n)):
+        assert torch.equal(out[a:b], lmg.Plan(gtab, N, uv[a:b].contiguous(), lmg.F64).degrid(grid))
