@@ -126,32 +126,39 @@ int fit_tile(int T, int N, lmg_precision prec, int W, int Ms) {
     while (T / 2 >= min_tile(W) && grid_lds_bytes(prec, W, T, Ms, 4) > kMaxDynLds && N / (T / 2) <= 128) T /= 2;
     return T;
 }
-// LDS patches of a gridding workgroup: two where two workgroups of two patches share a compute unit (tiles of 32
-// cells), else one (64-cell tiles: 4.2M visibilities on 8192^2 in FP32 154 us with one, 207 with two). With one patch
-// the flushes of a workgroup's waves wait for each other: four waves on one / two patches, W = 7 kernel times, 16.8M
+// LDS patches of a gridding workgroup, among which it divides each sum: two where two workgroups of two patches share a
+// compute unit (tiles of 32 cells), else one (64-cell tiles: 4.2M visibilities on 8192^2 in FP32 154 us with one, 207
+// with two). With one patch the flushes of a workgroup's waves wait for each other: four waves on one / two patches, W = 7 kernel times, 16.8M
 // visibilities FP32 206 / 187 us, compensated 293 / 274, FP64 474 / 450; 3.0M of one density on 2048^2 FP32 114 / 84,
 // compensated 176 / 122, FP64 188 / 147. (256 sparse channels at W = 5, compensated, are the exception: 458 with one
-// patch and three waves, 510 with two and four.) A function of the mode, support and tile alone: the number of
-// patches fixes the order of the sums, which a batch and a single channel share.
-int fit_patches(int T, lmg_precision prec, int W, int Ms) {
-    return 2 * (grid_lds_bytes(prec, W, T, Ms, 2) + 256) <= kMaxLds ? 2 : 1;
+// patch and three waves, 510 with two and four.) A function of the grid, mode, support, table and tile: the
+// number of patches fixes the order of the sums, which a batch and a single channel share.
+//
+// Wide plain FP32 and FP64 sums take more, as many more flushes reach a cell: from W = 9 on four in FP32 where two
+// workgroups of four fit (1.0M visibilities on 2048^2, W = 14: two 8.8e-8 against FP64, four 6.6e-8), three on 64-cell
+// tiles (1.0M on 8192^2, W = 12: one 1.05e-7, three 7.2e-8; with six waves also the faster, 283 and 230 us); in FP64 two
+// where only one workgroup of two fits (W = 15 and 16).
+int fit_patches(int T, int lsub, lmg_precision prec, int W, int Ms) {
+    auto groups = [&](int s) { return static_cast<int>(kMaxLds / (grid_lds_bytes(prec, W, T, Ms, s) + 256)); };
+    const int two = groups(2) >= 2 ? 2 : 1;
+    if (prec == LMG_F32 && W >= 9) return groups(4) >= 2 ? 4 : T > 32 && groups(3) >= 1 ? 3 : two;
+    if (prec == LMG_F64 && T <= 32 && lsub == 0 && groups(2) >= 1) return 2;
+    return two;
 }
 // Waves per gridding workgroup, a multiple of its patches: four, as an item has about four turns (16.8M visibilities:
 // 4.1) and the waves beyond an item's turns only wait (4.2M, W = 10, compensated: 234 us with four, 344 with six).
 // A launch of few items gets six, since it does not fill the chip and an item's latency is what counts: 202K
 // visibilities on 1024^2 58 us with four, 45 with six; 1.0M on 2048^2, W = 5, 54 and 47; but 3.0M of one density on
 // 2048^2, 84 and 129. The estimate takes a quarter of the tiles as occupied, as an image's data are. (env
-// LMG_GRID_WAVES overrides, 1 .. kMaxGridWaves)
-int fit_waves(int T, int N, int nchan, int64_t nvis, int cap, lmg_precision prec, int W, int* npatch) {
+// LMG_GRID_WAVES overrides, 1 .. kMaxGridWaves, to the next multiple of the patches)
+int fit_waves(int T, int N, int nchan, int64_t nvis, int cap, lmg_precision prec, int W, int npatch) {
     const int most = max_grid_waves(prec, W);
     const int forced = env_int("LMG_GRID_WAVES", 0);
-    if (forced >= 1 && forced <= kMaxGridWaves) {
-        const int w = std::min(forced, most);
-        if (w % *npatch) *npatch = 1;
-        return w;
-    }
+    if (forced >= 1 && forced <= kMaxGridWaves)
+        return std::min((forced + npatch - 1) / npatch, most / npatch) * npatch;
+    if (npatch == 3) return 6;
     const int64_t tiles = static_cast<int64_t>(N / T) * (N / T) * nchan;
-    if (nvis <= (int64_t{1} << 20) && std::min((tiles + 3) / 4, nvis) + nvis / cap <= 2048) return std::min(6, most);
+    if (nvis <= (int64_t{1} << 20) && std::min((tiles + 3) / 4, nvis) + nvis / cap <= 2048) return std::min(npatch == 4 ? 8 : 6, most);
     return 4;
 }
 
@@ -631,8 +638,8 @@ lmg_status create_plan(const lmg_table* table, int N, lmg_precision prec, int nc
     const int64_t items = most_items(N, T, nchan, nvis, cap);
     const int lsub = items <= INT32_MAX / 4 ? tile_lsub(N, T, prec) : 0;
     const int Tq = T >> lsub;
-    int npatch = fit_patches(Tq, prec, table->W, Ms);
-    const int waves = fit_waves(Tq, N, nchan, nvis, cap, prec, table->W, &npatch);
+    const int npatch = fit_patches(Tq, lsub, prec, table->W, Ms);
+    const int waves = fit_waves(Tq, N, nchan, nvis, cap, prec, table->W, npatch);
     if (grid_lds_bytes(prec, table->W, Tq, Ms, npatch) > kMaxDynLds) return LMG_ENOTSUP;
     const Layout L = plan_layout(N, nvis, prec, cap, nchan);
     if (!workspace || ws_bytes < L.total) return LMG_EWORKSPACE;

@@ -20,8 +20,8 @@ namespace dev {
 // wavefront scope and sequential consistency, which the compiler neither
 // merges nor reorders (LDS executes one wave's operations in order, so they
 // cost no waits). `Sum` adds the wave patches of a workgroup, and the patches
-// covering a grid cell, in the mode's own arithmetic: FP32, compensated FP32
-// (TwoSum into (hi, lo) pairs) or FP64.
+// covering a grid cell: FP64 for plain FP32 and FP64, compensated FP32 (TwoSum
+// into (hi, lo) pairs) for the compensated form.
 using u64 = unsigned long long;
 
 __device__ __forceinline__ u64 lds_ld(const void* p) {
@@ -59,15 +59,20 @@ struct AccF32 {
         v.y += r.y;
         lds_st(c, as_u64(v));
     }
-    // Sum of cells (the wave patches of an item, then the patches covering a grid cell), in FP32.
+    // Sum of cells (the patches of an item, then the patches covering a grid cell), in FP64, rounded once: the merges
+    // add no error to the flushes' own (16.8M visibilities, W = 7: relative RMS against FP64 6.41e-8 with FP32 merges,
+    // 5.47e-8; assembling a 4096^2 grid of 4.2M 36 us and 37).
     struct Sum {
-        float2 s = make_float2(0.f, 0.f);
+        double2 s = make_double2(0.0, 0.0);
         __device__ void add(const Cell& c) {
             s.x += c.x;
             s.y += c.y;
         }
-        __device__ Cell cell() const { return s; }
-        __device__ float2 value(float2 old) const { return make_float2(old.x + s.x, old.y + s.y); }
+        __device__ Cell cell() const { return make_float2(static_cast<float>(s.x), static_cast<float>(s.y)); }
+        __device__ float2 value(float2 old) const {
+            const Cell c = cell();
+            return make_float2(old.x + c.x, old.y + c.y);
+        }
     };
 };
 
@@ -221,7 +226,11 @@ __device__ __forceinline__ void flush_rows(typename Acc::Cell* patch, unsigned c
 // sizes) balance dynamically.
 //
 // Pieces are taken 64 at a time (a "turn"; neighbouring full pieces, often of
-// one cell, go to different turns). A workgroup has S = a.npatch patches and
+// one cell, go to different turns), the shortest first: a cell's plain FP32 sum
+// then rounds while it is small, which halves the error that the flushes add
+// (relative RMS of the grid against FP64, W = 7, longest first / shortest first
+// with the FP64 merges: 201,600 visibilities on 1024^2 8.19e-8 / 6.37e-8, 16.8M on
+// 4096^2 6.82e-8 / 5.47e-8; the time does not change by more than 2 %). A workgroup has S = a.npatch patches and
 // `waves` waves, a multiple of S; turn j is accumulated in registers by wave
 // j mod waves and flushed into patch j mod S, after the turns before it on
 // that patch (s_turn counts them). So the order of every sum is that of the
@@ -273,7 +282,11 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<Acc, W, kTab>()))) void k_grid
         constexpr int kB = sizeof(R) == 8 && W <= 8 ? (kTab == kTabDirect ? 2 : 1) : 4;
         const int np = it.w & 0xffff, fturns = it.w >> 16;  // pieces; turns of full pieces only
         const int turns = (np + 63) >> 6;
-        auto piece_of = [&](int j) { return j < fturns ? lane * fturns + j : j * 64 + lane; };
+        // the lane's piece of turn j: turns count from the shortest tails (a ragged last run of 64) to the full pieces
+        auto piece_of = [&](int j) {
+            const int run = turns - 1 - j;
+            return run < 0 ? np : run < fturns ? lane * fturns + run : run * 64 + lane;
+        };
 #pragma unroll
         for (int pass = 0; pass < NPASS; ++pass) {
             const int r0 = pass * RG;
