@@ -391,7 +391,8 @@ struct TilePatches {
 // cells a few rows apart and a batch of patches at a time, all loads issued before the first is added: what bounds the
 // occupied tiles is the latency of a cell's chain of patches, not their bytes (one 4096^2 grid of 16.8M visibilities
 // 64 us with one cell per thread, 51 with four; its occupied band 32, 27 with two; 4.2M on 8192^2 in FP32 164, 143).
-template <typename R, typename Acc, int KC>
+// kSub: patches are numbered by their items' first entries (a.sub), not by item.
+template <typename R, typename Acc, int KC, bool kSub>
 __device__ __forceinline__ void tile_cells(const AssembleArgs& a, typename C2<R>::T* dst, int rb, int ncell, int lbT,
                                            const int* first, const int* end, int step) {
     using VT = typename C2<R>::T;
@@ -420,24 +421,29 @@ __device__ __forceinline__ void tile_cells(const AssembleArgs& a, typename C2<R>
             const int pc = lc + ((s & 1) ? a.T : 0);
             for (int it = first[s]; it < end[s]; it += kU * step) {
                 Cell c[kU][KC];
-                int slot[kU];                                    // the patch of item it + u step, -1: none
+                int slot[kU];                                    // the patch of item it + u step
+                bool have[kU];
 #pragma unroll
                 for (int u = 0; u < kU; ++u) {
-                    const int i = it + u * step;
-                    slot[u] = i < end[s] ? i : -1;
-                    if (a.sub && i < end[s]) slot[u] = a.sub[i].z > 0 ? a.sub[i].y : -1;     // uniform
+                    slot[u] = it + u * step;
+                    have[u] = slot[u] < end[s];
+                    if constexpr (kSub) {
+                        const int4 q = have[u] ? a.sub[slot[u]] : make_int4(0, 0, 0, 0);     // uniform
+                        slot[u] = q.y;
+                        have[u] = q.z > 0;
+                    }
                 }
 #pragma unroll
                 for (int u = 0; u < kU; ++u)
 #pragma unroll
                     for (int k = 0; k < KC; ++k)
-                        if (slot[u] >= 0 && on[k] && (s < 2 || lr[k] < halo))
+                        if (have[u] && on[k] && (s < 2 || lr[k] < halo))
                             c[u][k] = patches[(static_cast<size_t>(slot[u]) * P + lr[k] + (s >= 2 ? a.T : 0)) * P + pc];
 #pragma unroll
                 for (int u = 0; u < kU; ++u)
 #pragma unroll
                     for (int k = 0; k < KC; ++k)
-                        if (slot[u] >= 0 && on[k] && (s < 2 || lr[k] < halo)) sum[k].add(c[u][k]);
+                        if (have[u] && on[k] && (s < 2 || lr[k] < halo)) sum[k].add(c[u][k]);
             }
         }
 #pragma unroll
@@ -447,7 +453,7 @@ __device__ __forceinline__ void tile_cells(const AssembleArgs& a, typename C2<R>
     }
 }
 
-template <typename R, typename Acc, int KC>
+template <typename R, typename Acc, int KC, bool kSub>
 __global__ __launch_bounds__(kAssembleThreads) void k_assemble(AssembleArgs a) {
     using VT = typename C2<R>::T;
     const int ar = a.rows;
@@ -478,7 +484,7 @@ __global__ __launch_bounds__(kAssembleThreads) void k_assemble(AssembleArgs a) {
     }
     const int first[4] = {src[0].first, src[1].first, src[2].first, src[3].first};
     const int end[4] = {src[0].end, src[1].end, src[2].end, src[3].end};
-    tile_cells<R, Acc, KC>(a, grid + static_cast<size_t>(tm * a.T + rb) * a.N + tn * a.T, rb, ar << lbT, lbT, first, end,
+    tile_cells<R, Acc, KC, kSub>(a, grid + static_cast<size_t>(tm * a.T + rb) * a.N + tn * a.T, rb, ar << lbT, lbT, first, end,
                            step);
 }
 
@@ -492,7 +498,7 @@ __global__ __launch_bounds__(kAssembleThreads) void k_assemble(AssembleArgs a) {
 // k_assemble, so the two give the same bits; overwrite (a tile without
 // patches takes zeros two cells per store), or accumulate (such a tile is
 // skipped).
-template <typename R, typename Acc, int KC>
+template <typename R, typename Acc, int KC, bool kSub>
 __global__ __launch_bounds__(kAssembleThreads) void k_assemble_rows(AssembleArgs a) {
     extern __shared__ int rng[];                           // [2][ntx + 1]: item_start of plan tile rows of tm, tm - 1
     using VT = typename C2<R>::T;
@@ -534,7 +540,7 @@ __global__ __launch_bounds__(kAssembleThreads) void k_assemble_rows(AssembleArgs
             }
             continue;
         }
-        tile_cells<R, Acc, KC>(a, grid + (tn << lbT), rb, ncell, lbT, i0, i1, step);
+        tile_cells<R, Acc, KC, kSub>(a, grid + (tn << lbT), rb, ncell, lbT, i0, i1, step);
     }
 }
 
@@ -572,23 +578,29 @@ hipError_t dispatch_grid(const GridArgs& a, hipStream_t s) {
     }
     return hipErrorInvalidValue;
 }
-template <typename R, typename Acc, int KC>
+template <typename R, typename Acc, int KC, bool kSub>
 hipError_t launch_assemble_kc(const AssembleArgs& a, unsigned nt, hipStream_t s) {
     if (a.rows_kernel) {
         const unsigned nb = static_cast<unsigned>(a.nchan) * static_cast<unsigned>(a.N / a.rows);
         const size_t shm = 2 * (static_cast<size_t>(a.ntx) + 1) * sizeof(int);
-        hipLaunchKernelGGL((dev::k_assemble_rows<R, Acc, KC>), dim3(nb), dim3(kAssembleThreads), shm, s, a);
+        hipLaunchKernelGGL((dev::k_assemble_rows<R, Acc, KC, kSub>), dim3(nb), dim3(kAssembleThreads), shm, s, a);
     } else {
-        hipLaunchKernelGGL((dev::k_assemble<R, Acc, KC>), dim3(nt), dim3(kAssembleThreads), 0, s, a);
+        hipLaunchKernelGGL((dev::k_assemble<R, Acc, KC, kSub>), dim3(nt), dim3(kAssembleThreads), 0, s, a);
     }
     return hipGetLastError();
 }
+template <typename R, typename Acc, bool kSub>
+hipError_t assemble_cells(const AssembleArgs& a, unsigned nt, hipStream_t s) {
+    const int cells = a.rows * a.T;                         // of one tile per workgroup
+    if (cells >= 4 * kAssembleThreads) return launch_assemble_kc<R, Acc, 4, kSub>(a, nt, s);
+    if (cells >= 2 * kAssembleThreads) return launch_assemble_kc<R, Acc, 2, kSub>(a, nt, s);
+    return launch_assemble_kc<R, Acc, 1, kSub>(a, nt, s);
+}
 template <typename R, typename Acc>
 hipError_t assemble(const AssembleArgs& a, unsigned nt, hipStream_t s) {
-    const int cells = a.rows * a.T;                         // of one tile per workgroup
-    if (cells >= 4 * kAssembleThreads) return launch_assemble_kc<R, Acc, 4>(a, nt, s);
-    if (cells >= 2 * kAssembleThreads) return launch_assemble_kc<R, Acc, 2>(a, nt, s);
-    return launch_assemble_kc<R, Acc, 1>(a, nt, s);
+    if constexpr (sizeof(typename Acc::Cell) == 16)         // the modes whose tiles are gridded by quadrants
+        if (a.sub) return assemble_cells<R, Acc, true>(a, nt, s);
+    return assemble_cells<R, Acc, false>(a, nt, s);
 }
 }  // namespace grid_impl
 }  // namespace lmg
