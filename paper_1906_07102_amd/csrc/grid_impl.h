@@ -255,7 +255,11 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<Acc, W, kTab>()))) void k_grid
     Cell* patches = reinterpret_cast<Cell*>(smem + ((ntab * sizeof(R) + 15) & ~size_t(15)));
     const int S = a.npatch;
     unsigned char* owners = reinterpret_cast<unsigned char*>(patches + S * P2);   // a lane id per cell
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+    // The wave's number, and with it its patch, turns and order of flushes, in scalar registers: in vector registers they
+    // spilled at W = 7, where three waves share a SIMD's (3.0M visibilities of one density on 2048^2, four waves,
+    // compensated 150.5 -> 145 us; 16.8M in FP32 182 -> 176).
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
     Cell* patch = patches + (wave % S) * P2;
     unsigned char* owner = owners + (wave % S) * P2;
     int* turn_of = &s_turn[wave % S];
