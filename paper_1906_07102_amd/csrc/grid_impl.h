@@ -170,7 +170,9 @@ struct AccF64 {
 // RG footprint rows (RG x W accumulators) and then adds them to the patch;
 // footprints wider than the mode's register budget (Acc::kAccRegBudget) take
 // several such passes over the piece. The FP32 forms keep the accumulators
-// near 112 registers, so that three waves fit a SIMD; FP64 takes 224, one pass
+// near 112 registers, so that three waves fit a SIMD, but for W = 8, whose 128
+// in one pass leave room for two (3.0M of one density on 2048^2, two passes of
+// four rows / one, FP32 143 / 108 us, compensated 185 / 160). FP64 takes 224, one pass
 // at W = 7, where two waves fit (16.8M visibilities, 0.59 -> 0.48 ms with one
 // pass instead of two), but two passes of four rows at W = 8, which leave room
 // for two waves as well (4.2M: 555 -> 445 us with one pass of seven and one of
@@ -179,7 +181,7 @@ template <typename Acc, int W>
 struct RowGroup {
     static constexpr bool kF64 = sizeof(typename Acc::Reg) == 16;
     static constexpr int kRegsPerTap = static_cast<int>(sizeof(typename Acc::Reg) / 4);
-    static constexpr int kRG0 = (kF64 && W == 8 ? 144 : Acc::kAccRegBudget) / (kRegsPerTap * W);
+    static constexpr int kRG0 = (W == 8 ? (kF64 ? 144 : 128) : Acc::kAccRegBudget) / (kRegsPerTap * W);
     static constexpr int kRG1 = kRG0 < 1 ? 1 : (kRG0 > W ? W : kRG0);
     static constexpr int kPasses = (W + kRG1 - 1) / kRG1;
     static constexpr int RG = (W + kPasses - 1) / kPasses;     // the passes' rows as even as they go
@@ -256,8 +258,8 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<Acc, W, kTab>()))) void k_grid
     const int S = a.npatch;
     unsigned char* owners = reinterpret_cast<unsigned char*>(patches + S * P2);   // a lane id per cell
     // The wave's number, and with it its patch, turns and order of flushes, in scalar registers: in vector registers they
-    // spilled at W = 7, where three waves share a SIMD's (3.0M visibilities of one density on 2048^2, four waves,
-    // compensated 150.5 -> 145 us; 16.8M in FP32 182 -> 176).
+    // spilled at W = 7, where three waves share a SIMD's (3.0M visibilities of one density on 2048^2, FP32
+    // 76 -> 70 us, compensated 152 -> 141).
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
     Cell* patch = patches + (wave % S) * P2;
