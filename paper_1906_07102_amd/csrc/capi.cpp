@@ -152,13 +152,12 @@ int fit_patches(int T, int lsub, lmg_precision prec, int W, int Ms) {
 // 2048^2, 84 and 129. The estimate takes a quarter of the tiles as occupied, as an image's data are. (env
 // LMG_GRID_WAVES overrides, 1 .. kMaxGridWaves, to the next multiple of the patches)
 int fit_waves(int T, int N, int nchan, int64_t nvis, int cap, lmg_precision prec, int W, int npatch) {
-    const int most = max_grid_waves(prec, W);
     const int forced = env_int("LMG_GRID_WAVES", 0);
     if (forced >= 1 && forced <= kMaxGridWaves)
-        return std::min((forced + npatch - 1) / npatch, most / npatch) * npatch;
+        return std::min((forced + npatch - 1) / npatch, kMaxGridWaves / npatch) * npatch;
     if (npatch == 3) return 6;
     const int64_t tiles = static_cast<int64_t>(N / T) * (N / T) * nchan;
-    if (nvis <= (int64_t{1} << 20) && std::min((tiles + 3) / 4, nvis) + nvis / cap <= 2048) return std::min(npatch == 4 ? 8 : 6, most);
+    if (nvis <= (int64_t{1} << 20) && std::min((tiles + 3) / 4, nvis) + nvis / cap <= 2048) return npatch == 4 ? 8 : 6;
     return 4;
 }
 

@@ -46,7 +46,7 @@ __device__ __forceinline__ u64 as_u64(double d) { return __builtin_bit_cast(u64,
 struct AccF32 {
     using Cell = float2;
     using Reg = float2;
-    static constexpr int kAccRegBudget = 112;
+    static constexpr int kAccRegs = 112;
     __device__ static void zero_cell(Cell* c) { *c = make_float2(0.f, 0.f); }
     __device__ static void set(Reg& r, float re, float im) { r = make_float2(re, im); }
     __device__ static void add(Reg& r, float re, float im) {
@@ -86,7 +86,7 @@ struct AccF32 {
 struct AccKahan {
     using Cell = float4;      // (hi re, hi im, lo re, lo im)
     using Reg = float2;
-    static constexpr int kAccRegBudget = 112;
+    static constexpr int kAccRegs = 112;
     __device__ static void zero_cell(Cell* c) { *c = make_float4(0.f, 0.f, 0.f, 0.f); }
     __device__ static void set(Reg& r, float re, float im) { r = make_float2(re, im); }
     __device__ static void add(Reg& r, float re, float im) {
@@ -141,7 +141,7 @@ struct AccKahan {
 struct AccF64 {
     using Cell = double2;
     using Reg = double2;
-    static constexpr int kAccRegBudget = 224;
+    static constexpr int kAccRegs = 224;
     __device__ static void zero_cell(Cell* c) { *c = make_double2(0.0, 0.0); }
     __device__ static void set(Reg& r, double re, double im) { r = make_double2(re, im); }
     __device__ static void add(Reg& r, double re, double im) {
@@ -168,30 +168,32 @@ struct AccF64 {
 
 // Register accumulation: a lane sums one piece's contributions to a group of
 // RG footprint rows (RG x W accumulators) and then adds them to the patch;
-// footprints wider than the mode's register budget (Acc::kAccRegBudget) take
+// footprints wider than the mode's register budget (kBudget) take
 // several such passes over the piece. The FP32 forms keep the accumulators
 // near 112 registers, so that three waves fit a SIMD, but for W = 8, whose 128
 // in one pass leave room for two (3.0M of one density on 2048^2, two passes of
-// four rows / one, FP32 143 / 108 us, compensated 185 / 160). FP64 takes 224, one pass
-// at W = 7, where two waves fit (16.8M visibilities, 0.59 -> 0.48 ms with one
-// pass instead of two), but two passes of four rows at W = 8, which leave room
-// for two waves as well (4.2M: 555 -> 445 us with one pass of seven and one of
-// a single row before); wider FP64 footprints keep one wave per SIMD.
+// four rows / one, FP32 143 / 108 us, compensated 185 / 160). FP64 takes 224,
+// one pass at W = 7, where two waves fit (16.8M visibilities, 0.59 -> 0.48 ms
+// with one pass instead of two), and 160 above, which leave room for two waves
+// as well: more passes over a piece, but twice the waves and the patches that a
+// compute unit works on (4.2M on 4096^2, W = 8 445 us; 3.0M of one density on
+// 2048^2, one wave per SIMD with 224 / two with 160, W = 9 275 / 231 us, W = 14
+// 863 / 631).
 template <typename Acc, int W>
 struct RowGroup {
     static constexpr bool kF64 = sizeof(typename Acc::Reg) == 16;
     static constexpr int kRegsPerTap = static_cast<int>(sizeof(typename Acc::Reg) / 4);
-    static constexpr int kRG0 = (W == 8 ? (kF64 ? 144 : 128) : Acc::kAccRegBudget) / (kRegsPerTap * W);
+    static constexpr int kBudget = kF64 ? (W >= 8 ? 160 : Acc::kAccRegs) : W == 8 ? 128 : Acc::kAccRegs;
+    static constexpr int kRG0 = kBudget / (kRegsPerTap * W);
     static constexpr int kRG1 = kRG0 < 1 ? 1 : (kRG0 > W ? W : kRG0);
     static constexpr int kPasses = (W + kRG1 - 1) / kRG1;
     static constexpr int RG = (W + kPasses - 1) / kPasses;     // the passes' rows as even as they go
-    static constexpr int kMaxWaves = max_grid_waves(kF64 ? LMG_F64 : LMG_F32, W);
 };
 // Waves per SIMD the compiler keeps room for.
 template <typename Acc, int W, int kTab>
 constexpr int waves_per_simd() {
     using G = RowGroup<Acc, W>;
-    return G::kMaxWaves == 4 ? 1 : (!G::kF64 && W <= 7 && kTab != kTabDirect) ? 3 : 2;
+    return (!G::kF64 && W <= 7 && kTab != kTabDirect) ? 3 : 2;
 }
 
 // Add the piece's accumulated rows r0 .. r0 + RG - 1 (those below W) to the
@@ -240,7 +242,7 @@ __device__ __forceinline__ void flush_rows(typename Acc::Cell* patch, unsigned c
 // nothing waits; more waves hide more latency where LDS holds few patches or
 // the launch has few items.
 template <typename R, typename Acc, int W, int kTab>
-__global__ __launch_bounds__((64 * RowGroup<Acc, W>::kMaxWaves))
+__global__ __launch_bounds__(64 * kMaxGridWaves)
 __attribute__((amdgpu_waves_per_eu(waves_per_simd<Acc, W, kTab>()))) void k_grid_items(GridArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int s_item, s_turn[kMaxGridWaves];
@@ -283,9 +285,9 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<Acc, W, kTab>()))) void k_grid
         if (item >= nitems) break;                       // uniform across the workgroup
         const int4 it = a.items[item];
         // entries whose loads are issued together (FP64 at W = 7 with 1 / 2: 16.8M visibilities 453 / 460 us, 3.0M of
-        // one density 138 / 145; with 4 it spills at two waves per SIMD; direct weights, 8.4M, W = 5 with 1 / 2 / 4:
+        // one density 138 / 145; with 4 it spills, and above W = 8 leaves one wave per SIMD; direct weights, 8.4M, W = 5 with 1 / 2 / 4:
         // 772 / 702 / 705, W = 8: 2165 / 1928 / 2321)
-        constexpr int kB = sizeof(R) == 8 && W <= 8 ? (kTab == kTabDirect ? 2 : 1) : 4;
+        constexpr int kB = sizeof(R) == 8 ? (kTab == kTabDirect ? 2 : 1) : 4;
         const int np = it.w & 0xffff, fturns = it.w >> 16;  // pieces; turns of full pieces only
         const int turns = (np + 63) >> 6;
         // the lane's piece of turn j: turns count from the shortest tails (a ragged last run of 64) to the full pieces

@@ -196,8 +196,6 @@ hipError_t take_data_error(int* flag);
 // kernel needs no more than one patch).
 size_t grid_lds_bytes(lmg_precision prec, int W, int T, int Ms, int npatch);
 constexpr int kMaxGridWaves = 8;
-// Most waves of a gridding workgroup: four where the accumulators need a SIMD's whole register file.
-constexpr int max_grid_waves(lmg_precision prec, int W) { return prec == LMG_F64 && W >= 9 ? 4 : kMaxGridWaves; }
 constexpr size_t kMaxLds = 160 * 1024;
 // Dynamic LDS the item kernels may request: they also hold a few bytes of
 // static LDS (the current work item), and both must fit the 160 KB.
