@@ -132,7 +132,10 @@ __device__ __forceinline__ void weights_direct(const double* pq_global, P p, int
 #pragma unroll
     for (int j = 0; j < W; ++j) acc[j] = pq[j * NI];            // i = 0: cos 0 = 1, sin 0 = 0
     double ci = 1.0, si = 0.0;
-#pragma unroll 4
+    // Steps taken together share their scalar loads; four steps' coefficients (16 W scalar registers of 102) spill from
+    // W = 6 on in FP64 and W = 9 in FP32, whose kernels differ in what else they hold there (gridding 4.2M visibilities
+    // on 4096^2 with four / two, FP64 W = 5 420 / 464 us, 6 739 / 499, 7 999 / 684; FP32 7 522 / 557, 9 1830 / 1256).
+#pragma unroll (W >= (sizeof(R) == 8 ? 6 : 9) ? 2 : 4)
     for (int i = 1; i < NI; ++i) {
         const double cn = ci * c1 - si * s1;
         si = si * c1 + ci * s1;

@@ -284,11 +284,11 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<Acc, W, kTab>()))) void k_grid
         const int item = s_item;
         if (item >= nitems) break;                       // uniform across the workgroup
         const int4 it = a.items[item];
-        // entries whose loads are issued together (FP64, 8.4M visibilities on 4096^2 with 1 / 4: W = 3 188 / 125 us,
-        // W = 5 222 / 163; at W = 7 with 1 / 2: 16.8M visibilities 453 / 460 us, 3.0M of
-        // one density 138 / 145; with 4 it spills, and above W = 8 leaves one wave per SIMD; direct weights, 8.4M, W = 5 with 1 / 2 / 4:
-        // 772 / 702 / 705, W = 8: 2165 / 1928 / 2321)
-        constexpr int kB = sizeof(R) == 8 ? (kTab == kTabDirect ? 2 : W <= 5 ? 4 : 1) : 4;
+        // entries whose loads are issued together: FP64, 8.4M visibilities on 4096^2 with 1 / 4, W = 3 188 / 125 us, W = 5
+        // 222 / 163; at W = 7 with 1 / 2, 16.8M 453 / 460 us, 3.0M of one density 138 / 145 (4 spills, and above W = 8
+        // leaves one wave per SIMD). Direct weights with 1 / 2 / 4: FP64, 8.4M, W = 5 772 / 702 / 705 us, W = 8 2165 /
+        // 1928 / 2321; FP32, 4.2M, W = 6 2 / 4 434 / 636 us.
+        constexpr int kB = kTab == kTabDirect ? 2 : sizeof(R) == 8 && W >= 6 ? 1 : 4;
         const int np = it.w & 0xffff, fturns = it.w >> 16;  // pieces; turns of full pieces only
         const int turns = (np + 63) >> 6;
         // the lane's piece of turn j: turns count from the shortest tails (a ragged last run of 64) to the full pieces
@@ -361,8 +361,13 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<Acc, W, kTab>()))) void k_grid
             }
         }
         __syncthreads();
-        Cell* out = reinterpret_cast<Cell*>(a.patches) + static_cast<size_t>(a.by_entry ? it.y : item) * P2;
-        const int nout = a.by_entry && it.z == 0 ? 0 : P2;
+        Cell* out = reinterpret_cast<Cell*>(a.patches) + static_cast<size_t>(item) * P2;
+        int nout = P2;
+        if (a.by_entry) {
+            const int4 q = a.items[item];                   // read again: held over the turns it costs registers
+            out = reinterpret_cast<Cell*>(a.patches) + static_cast<size_t>(q.y) * P2;
+            if (q.z == 0) nout = 0;
+        }
         for (int i = threadIdx.x; i < nout; i += blockDim.x) {
             const int row = __umulhi(static_cast<unsigned>(i), inv_p);
             const int from = a.transpose ? (i - row * P) * P + row : i;
