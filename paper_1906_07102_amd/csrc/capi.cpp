@@ -147,17 +147,22 @@ int fit_patches(int T, int lsub, lmg_precision prec, int W, int Ms) {
 }
 // Waves per gridding workgroup, a multiple of its patches: four, as an item has about four turns (16.8M visibilities:
 // 4.1) and the waves beyond an item's turns only wait (4.2M, W = 10, compensated: 234 us with four, 344 with six).
-// A launch of few items gets six, since it does not fill the chip and an item's latency is what counts: 202K
-// visibilities on 1024^2 58 us with four, 45 with six; 1.0M on 2048^2, W = 5, 54 and 47; but 3.0M of one density on
-// 2048^2, 84 and 129. The estimate takes a quarter of the tiles as occupied, as an image's data are. (env
-// LMG_GRID_WAVES overrides, 1 .. kMaxGridWaves, to the next multiple of the patches)
+// A launch of few items, which does not fill the chip, so that an item's latency is what counts, gets eight, two to each
+// SIMD (six leave two SIMDs with twice the work of the others): in FP32 with four / six / eight, tracks of 202K on 1024^2
+// 45 / 38 / 37 us at W = 7, of 300K on 2048^2 at W = 6 38 / 41 / 33, of 1.0M on 2048^2 51 / 62 / 48, at W = 5 38 / 32 /
+// 30; but data of one density, whose items have few turns, 300K on 1024^2 at W = 7 26 / 39 / 31. More items than five to
+// a compute unit do better with four where the flush of W^2 cells takes longer than the sums before it (1.0M in 24
+// channels of 512^2, W = 6 53 / 67 / 66 us; W = 5 41 / 38 / 37; FP64, W = 8 300 / 238 / 235). The estimate takes a
+// quarter of the tiles as occupied, as an image's data are. (env LMG_GRID_WAVES overrides, 1 .. kMaxGridWaves, to the
+// next multiple of the patches)
 int fit_waves(int T, int N, int nchan, int64_t nvis, int cap, lmg_precision prec, int W, int npatch) {
     const int forced = env_int("LMG_GRID_WAVES", 0);
     if (forced >= 1 && forced <= kMaxGridWaves)
         return std::min((forced + npatch - 1) / npatch, kMaxGridWaves / npatch) * npatch;
     if (npatch == 3) return 6;
     const int64_t tiles = static_cast<int64_t>(N / T) * (N / T) * nchan;
-    if (nvis <= (int64_t{1} << 20) && std::min((tiles + 3) / 4, nvis) + nvis / cap <= 2048) return npatch == 4 ? 8 : 6;
+    const int64_t few = prec != LMG_F64 && W >= 6 ? 1280 : 2048;
+    if (nvis <= (int64_t{1} << 20) && std::min((tiles + 3) / 4, nvis) + nvis / cap <= few) return 8;
     return 4;
 }
 
