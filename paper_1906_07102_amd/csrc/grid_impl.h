@@ -288,7 +288,13 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<Acc, W, kTab>()))) void k_grid
         // 222 / 163; at W = 7 with 1 / 2, 16.8M 453 / 460 us, 3.0M of one density 138 / 145 (4 spills, and above W = 8
         // leaves one wave per SIMD). Direct weights with 1 / 2 / 4: FP64, 8.4M, W = 5 772 / 702 / 705 us, W = 8 2165 /
         // 1928 / 2321; FP32, 4.2M, W = 6 2 / 4 434 / 636 us.
-        constexpr int kB = kTab == kTabDirect ? 2 : sizeof(R) == 8 && W >= 6 ? 1 : 4;
+        // In the FP32 forms the code for four entries in every pass outgrows the instruction cache from W = 14 on (13 in
+        // the compensated form, whose flush is longer; there two do from W = 15): 4.2M with 4 / 2 / 1, FP32 W = 13 294 /
+        // 306 / 323 us, 14 428 / 336 / 351, 16 1150 / 741 / 781; compensated 12 330 / 335 / 343, 13 464 / 372 / 386, 15 580
+        // / 603 / 509, 16 1273 / 1300 / 895.
+        constexpr bool kComp = std::is_same<Acc, AccKahan>::value;
+        constexpr int kWide = kComp && W >= 15 ? 1 : W >= (kComp ? 13 : 14) ? 2 : 4;
+        constexpr int kB = kTab == kTabDirect ? 2 : sizeof(R) == 8 && W >= 6 ? 1 : kWide;
         const int np = it.w & 0xffff, fturns = it.w >> 16;  // pieces; turns of full pieces only
         const int turns = (np + 63) >> 6;
         // the lane's piece of turn j: turns count from the shortest tails (a ragged last run of 64) to the full pieces
