@@ -558,11 +558,11 @@ lmg_status run_grid(const lmg_plan* p, const void* vis, const float* w, void* gr
 
 // Degridding by the quadrants of a plan that grids by quadrants: dense FP64 data at W = 6 .. 8. The fill of four small
 // patches costs more than that of a large one, so sparse data go by whole tiles: 8192^2 in FP64, whole / quadrants, 1.0M
-// visibilities at W = 7 70 / 119 us, 3.0M 113 / 132 (W = 8 240 / 226), 6.0M 234 / 219, 16.8M 348 / 317 (W = 5 267 / 250,
+// visibilities at W = 7 70 / 119 us, 3.0M 113 / 132 (but W = 8 240 / 226), 6.0M 234 / 219, 16.8M 348 / 317 (W = 5 267 / 250,
 // but 6.0M 187 / 215; W = 3 151 / 199, 9 488 / 547). FP32 grids' patches are half as large (16.8M 195 / 223). Each visibility's sum is its own, so
 // the results are the same bits.
 bool degrid_by_quadrants(const lmg_plan* p) {
-    return p->prec == LMG_F64 && p->g.W >= 6 && p->g.W <= 8 && p->nvis >= 6000000;
+    return p->prec == LMG_F64 && p->g.W >= 6 && p->g.W <= 8 && p->nvis >= (p->g.W == 8 ? 3000000 : 6000000);
 }
 
 // Degridding into entry order.
