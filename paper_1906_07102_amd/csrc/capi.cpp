@@ -174,6 +174,12 @@ size_t real_size(lmg_precision p) { return p == LMG_F64 ? 8 : 4; }
 size_t cplx_size(lmg_precision p) { return 2 * real_size(p); }
 size_t patch_cell_size(lmg_precision p) { return p == LMG_F32 ? 8 : 16; }
 
+// Gridding work items are the quadrants of 64-cell tiles (1 = log2 2) on 8192^2 grids, where 128 x 128 tiles cannot be
+// smaller, in the modes with 16-byte patch cells: a 64-cell patch leaves a compute unit one workgroup (gridding 16.8M
+// visibilities, compensated, W = 7: 694 us whole, 578 as quadrants; 4.2M, FP64, W = 6: 283 and 229; FP32's 8-byte cells
+// leave three, 154 and 156).
+int tile_lsub(int N, int T, lmg_precision prec) { return N == 8192 && T == 64 && prec != LMG_F32 ? 1 : 0; }
+
 struct Layout {
     size_t flags, tile_count, tile_start, item_start, blockhist, blocks, chan_blocks, items, sub, inv0, off0, off, pos2, inv, pieces, coef,
         twiddle, hpix, total;
@@ -205,7 +211,7 @@ Layout plan_layout(int N, int64_t nvis, lmg_precision prec, int cap, int nchan =
     L.blocks = take(static_cast<size_t>(L.max_blocks) * sizeof(int4));
     L.chan_blocks = take((static_cast<size_t>(nchan) + 1) * sizeof(int));
     L.items = take(static_cast<size_t>(L.max_items) * sizeof(int4));
-    L.sub = take(N == 8192 ? static_cast<size_t>(L.max_items) * 4 * sizeof(int4) : 0);
+    L.sub = take(tile_lsub(N, 64, prec) ? static_cast<size_t>(L.max_items) * 4 * sizeof(int4) : 0);
     L.inv0 = take(static_cast<size_t>(nvis) * sizeof(int));
     L.off0 = take(static_cast<size_t>(nvis) * packed_offset_bytes(prec == LMG_F64));
     L.off = take(static_cast<size_t>(nvis + kRunPad) * packed_offset_bytes(prec == LMG_F64));
@@ -252,12 +258,6 @@ Scratch scratch_layout(int N, int W, int T, int lsub, int M, int64_t items, int6
     s.total = o;
     return s;
 }
-
-// Gridding work items are the quadrants of 64-cell tiles (1 = log2 2) on 8192^2 grids, where 128 x 128 tiles cannot be
-// smaller, in the modes with 16-byte patch cells: a 64-cell patch leaves a compute unit one workgroup (gridding 16.8M
-// visibilities, compensated, W = 7: 694 us whole, 578 as quadrants; 4.2M, FP64, W = 6: 283 and 229; FP32's 8-byte cells
-// leave three, 154 and 156).
-int tile_lsub(int N, int T, lmg_precision prec) { return N == 8192 && T == 64 && prec != LMG_F32 ? 1 : 0; }
 
 size_t scratch_for(int N, int W, int T, int M, int items, int64_t nvis, lmg_precision prec, int op) {
     size_t b = 0;
