@@ -387,8 +387,8 @@ __global__ __launch_bounds__((FftShape<N, ROWS>::kThreads)) void k_fft_pass(FftA
             emit(dst + static_cast<size_t>(row) * a.dst_pitch + o, x, h_out ? h_out[r] : R(1));
     };
     stockham_stages<R, N, ROWS, 3, kStraight>(buf, tw, w, outer_out, store);
-    if constexpr (kStraight && N > 8) return;
-    // Transposed (or a row of one stage): from LDS, the rows of the workgroup side by side. out_count * ROWS <=
+    if constexpr (kStraight) return;
+    // Transposed: from LDS, the rows of the workgroup side by side. out_count * ROWS <=
     // kPer * NT outputs; the factors' loads issued first.
     constexpr int kPer = ROWS * N / NT;
     const int nout = a.out_count * ROWS;
@@ -406,9 +406,7 @@ __global__ __launch_bounds__((FftShape<N, ROWS>::kThreads)) void k_fft_pass(FftA
         const int row = row0 + rr;
         if (idx >= nout || row >= a.nrows) continue;
         const VT x = buf[rr * L::kPitch + row_slot<L::kRowPad>((a.out_pos + o + N / 2) & (N - 1))];
-        const size_t at = kStraight       ? static_cast<size_t>(row) * a.dst_pitch + o
-                          : a.dst_blocked ? blocked(o, row + a.dst_col, a.dst_pitch)
-                                          : static_cast<size_t>(o) * a.dst_pitch + row;
+        const size_t at = a.dst_blocked ? blocked(o, row + a.dst_col, a.dst_pitch) : static_cast<size_t>(o) * a.dst_pitch + row;
         emit(dst + at, x, hout[q]);
     }
 }
@@ -433,8 +431,11 @@ hipError_t launch_fft_n(const FftArgs& a, hipStream_t s) {
     constexpr size_t row_bytes = static_cast<size_t>(N) * 2 * sizeof(R);
     // two rows per workgroup: two workgroups share a compute unit, one loading while the other transforms
     constexpr int rows = (2 * row_bytes <= 131072) ? 2 : 1;
-    if (a.straight)
-        return a.sign > 0 ? launch_fft_sign<R, N, rows, 1, true>(a, s) : launch_fft_sign<R, N, rows, -1, true>(a, s);
+    if (a.straight) {
+        // the image calls' last passes, on grids of at least 64 cells (the straight store takes the last of several stages)
+        if constexpr (N < 64) return hipErrorInvalidValue;
+        else return a.sign > 0 ? launch_fft_sign<R, N, rows, 1, true>(a, s) : launch_fft_sign<R, N, rows, -1, true>(a, s);
+    }
     return a.sign > 0 ? launch_fft_sign<R, N, rows, 1, false>(a, s) : launch_fft_sign<R, N, rows, -1, false>(a, s);
 }
 template <typename R>
