@@ -1077,8 +1077,9 @@ lmg_status lmg_workspace_size(int N, int W, double x0, int64_t nvis, lmg_precisi
 namespace {
 // Largest grid on which a one-shot image call transforms the whole grid rather than wait for the band its
 // visibilities occupy: that wait, in the middle of the call, drains the queue; the wait for the plan at the call's end
-// finds the rest queued (dirty image and prediction, waiting against whole: 2,000 visibilities on 128^2 114 and 103 us,
-// 201,600 on 1024^2 214 and 210; 1.0M on 2048^2 273 and 283, in FP64 390 and 421).
+// finds the rest queued (dirty image and prediction, waiting against whole: 2,000 visibilities on 128^2 123 and 108 us,
+// 201,600 on 512^2 203 and 194; on 1024^2 2,000 130 and 124, in FP64 136 and 131, 201,600 210 and 208, in FP64 263 and
+// 265, 1.0M 259 and 255, in FP64 323 and 323; on 2048^2 2,000 174 and 180, 1.0M 298 and 310, in FP64 383 and 416).
 constexpr int kWholeImageN = 1024;
 
 template <typename F>

@@ -23,8 +23,11 @@ inline int plan_block_vis(int N, int64_t nvis) {
     const int64_t v = (std::max(least, (nvis + 255) / 256) + 1023) / 1024 * 1024;
     return static_cast<int>(std::min<int64_t>(v, kPlanBlockVis));
 }
-// Plans of at most this many visibilities scatter directly (k_plan_scatter).
-constexpr int64_t kDirectPlanVis = 1 << 18;
+// Plans of at most this many visibilities scatter directly (k_plan_scatter): the scattered stores cost less than the two
+// passes that order them while the arrays stay in L2 (whole plans, two more passes / directly, W = 7: 200,000 visibilities
+// on 1024^2 78 and 72 us, 1.0M 92 and 86, 2.0M 109 and 115; on 4096^2 1.0M 134 and 122, in FP64 145 and 132, 2.0M 165 and
+// 172; one density on 1024^2 1.0M 91 and 89, 2.0M 116 and 133; 1.0M in 24 channels of 512^2 107 and 100).
+constexpr int64_t kDirectPlanVis = 1 << 20;
 // Plans of one channel and at most this many visibilities take one launch up to the scatter (k_plan_small): up to there
 // one workgroup is no slower than the general passes' four launches (2,000 visibilities 43 us, general 50; 8,000 52 and
 // 52; 16,000 74 and 57; the whole plan with its item sort).
