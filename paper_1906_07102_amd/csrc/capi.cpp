@@ -130,8 +130,8 @@ int fit_tile(int T, int N, lmg_precision prec, int W, int Ms) {
 // compute unit (tiles of 32 cells), else one (64-cell tiles: 4.2M visibilities on 8192^2 in FP32 154 us with one, 207
 // with two). With one patch the flushes of a workgroup's waves wait for each other: four waves on one / two patches, W = 7 kernel times, 16.8M
 // visibilities FP32 206 / 187 us, compensated 293 / 274, FP64 474 / 450; 3.0M of one density on 2048^2 FP32 114 / 84,
-// compensated 176 / 122, FP64 188 / 147. (256 sparse channels at W = 5, compensated, are the exception: 458 with one
-// patch and three waves, 510 with two and four.) A function of the grid, mode, support, table and tile: the
+// compensated 176 / 122, FP64 188 / 147. (256 sparse channels, compensated, are the exception: W = 5 438 with one
+// patch and three waves, 507 with two and four.) A function of the grid, mode, support, table and tile: the
 // number of patches fixes the order of the sums, which a batch and a single channel share.
 //
 // Wide plain FP32 and FP64 sums take more, as many more flushes reach a cell: from W = 9 on four in FP32 where two
@@ -153,7 +153,9 @@ int fit_patches(int T, int lsub, lmg_precision prec, int W, int Ms) {
 // 30; but data of one density, whose items have few turns, 300K on 1024^2 at W = 7 26 / 39 / 31. More items than five to
 // a compute unit do better with four where the flush of W^2 cells takes longer than the sums before it (1.0M in 24
 // channels of 512^2, W = 6 53 / 67 / 66 us; W = 5 41 / 38 / 37; FP64, W = 8 300 / 238 / 235). The estimate takes a
-// quarter of the tiles as occupied, as an image's data are. (env LMG_GRID_WAVES overrides, 1 .. kMaxGridWaves, to the
+// quarter of the tiles as occupied, as an image's data are. Plain FP32 at W = 8, where registers hold a compute unit to
+// eight waves, works on four items at a time with two waves each rather than on two (15.8M in 256 channels of 1024^2 662
+// us, with four waves 834; 4.0M 390 and 507; 4.0M of one density on 4096^2 178 and 207; 4.2M of tracks 131 and 126). (env LMG_GRID_WAVES overrides, 1 .. kMaxGridWaves, to the
 // next multiple of the patches)
 int fit_waves(int T, int N, int nchan, int64_t nvis, int cap, lmg_precision prec, int W, int npatch) {
     const int forced = env_int("LMG_GRID_WAVES", 0);
@@ -163,7 +165,7 @@ int fit_waves(int T, int N, int nchan, int64_t nvis, int cap, lmg_precision prec
     const int64_t tiles = static_cast<int64_t>(N / T) * (N / T) * nchan;
     const int64_t few = prec != LMG_F64 && W >= 6 ? 1280 : 2048;
     if (nvis <= (int64_t{1} << 20) && std::min((tiles + 3) / 4, nvis) + nvis / cap <= few) return 8;
-    return 4;
+    return prec == LMG_F32 && W == 8 && npatch == 2 && nvis > (int64_t{1} << 20) ? 2 : 4;
 }
 
 int choose_cap() { return std::min(env_int("LMG_CAP", 8192), kMaxCap); }
