@@ -128,9 +128,9 @@ int fit_tile(int T, int N, lmg_precision prec, int W, int Ms) {
 }
 // LDS patches of a gridding workgroup, among which it divides each sum: two where two workgroups of two patches share a
 // compute unit (tiles of 32 cells), else one (64-cell tiles: 4.2M visibilities on 8192^2 in FP32 154 us with one, 207
-// with two). With one patch the flushes of a workgroup's waves wait for each other: four waves on one / two patches, W = 7 kernel times, 16.8M
-// visibilities FP32 206 / 187 us, compensated 293 / 274, FP64 474 / 450; 3.0M of one density on 2048^2 FP32 114 / 84,
-// compensated 176 / 122, FP64 188 / 147. (256 sparse channels, compensated, are the exception: W = 5 438 with one
+// with two). With one patch the flushes of a workgroup's waves wait for each other: four waves on one / two patches,
+// W = 7 kernel times, 16.8M visibilities FP32 206 / 187 us, compensated 293 / 274, FP64 474 / 450; 3.0M of one density
+// on 2048^2 FP32 114 / 84, compensated 176 / 122, FP64 188 / 147. (256 sparse channels, compensated, are the exception: W = 5 438 with one
 // patch and three waves, 507 with two and four.) A function of the grid, mode, support, table and tile: the
 // number of patches fixes the order of the sums, which a batch and a single channel share.
 //
@@ -155,8 +155,8 @@ int fit_patches(int T, int lsub, lmg_precision prec, int W, int Ms) {
 // channels of 512^2, W = 6 53 / 67 / 66 us; W = 5 41 / 38 / 37; FP64, W = 8 300 / 238 / 235). The estimate takes a
 // quarter of the tiles as occupied, as an image's data are. Plain FP32 at W = 8, where registers hold a compute unit to
 // eight waves, works on four items at a time with two waves each rather than on two (15.8M in 256 channels of 1024^2 662
-// us, with four waves 834; 4.0M 390 and 507; 4.0M of one density on 4096^2 178 and 207; 4.2M of tracks 131 and 126). (env LMG_GRID_WAVES overrides, 1 .. kMaxGridWaves, to the
-// next multiple of the patches)
+// us, with four waves 834; 4.0M 390 and 507; 4.0M of one density on 4096^2 178 and 207; 4.2M of tracks 131 and 126).
+// (env LMG_GRID_WAVES overrides, 1 .. kMaxGridWaves, to the next multiple of the patches)
 int fit_waves(int T, int N, int nchan, int64_t nvis, int cap, lmg_precision prec, int W, int npatch) {
     const int forced = env_int("LMG_GRID_WAVES", 0);
     if (forced >= 1 && forced <= kMaxGridWaves)
@@ -523,7 +523,8 @@ lmg_status run_grid_entries(const lmg_plan* p, const void* vs, void* grid, void*
     a.tab_global = table_global(t, p->prec) ? 1 : 0;
     a.n_items = p->flags + 1; a.max_items = p->max_items << (2 * p->g.lsub); a.npatch = p->npatch; a.waves = p->waves; a.Ft = p->Ft; a.kb = p->kb;
     a.items = p->sub; a.pieces = p->pieces; a.off = p->off; a.coef = p->coef;
-    a.vis = vs; a.patches = patches; a.by_entry = p->by_entry ? 1 : 0; a.counter = counters; a.counter_zero = counter_zero ? 1 : 0;
+    a.vis = vs; a.patches = patches; a.by_entry = p->by_entry ? 1 : 0;
+    a.counter = counters; a.counter_zero = counter_zero ? 1 : 0;
     a.transpose = band_only ? 1 : 0;
     {
         TraceScope ts("grid_items", s);
@@ -560,9 +561,9 @@ lmg_status run_grid(const lmg_plan* p, const void* vis, const float* w, void* gr
 
 // Degridding by the quadrants of a plan that grids by quadrants: dense FP64 data at W = 6 .. 8. The fill of four small
 // patches costs more than that of a large one, so sparse data go by whole tiles: 8192^2 in FP64, whole / quadrants, 1.0M
-// visibilities at W = 7 70 / 119 us, 3.0M 113 / 132 (but W = 8 240 / 226), 6.0M 234 / 219, 16.8M 348 / 317 (W = 5 267 / 250,
-// but 6.0M 187 / 215; W = 3 151 / 199, 9 488 / 547). FP32 grids' patches are half as large (16.8M 195 / 223). Each visibility's sum is its own, so
-// the results are the same bits.
+// visibilities at W = 7 70 / 119 us, 3.0M 113 / 132 (but W = 8 240 / 226), 6.0M 234 / 219, 16.8M 348 / 317 (W = 5
+// 267 / 250, but 6.0M 187 / 215; W = 3 151 / 199, 9 488 / 547). FP32 grids' patches are half as large (16.8M 195 / 223).
+// Each visibility's sum is its own, so the results are the same bits.
 bool degrid_by_quadrants(const lmg_plan* p) {
     return p->prec == LMG_F64 && p->g.W >= 6 && p->g.W <= 8 && p->nvis >= (p->g.W == 8 ? 3000000 : 6000000);
 }

@@ -266,8 +266,8 @@ __device__ __forceinline__ void scan_staged(const PlanGeom& g, int* s_start, int
     for (int i = threadIdx.x; i < nitems; i += blockDim.x) {
         int a = 0, b = tot;          // s_items[a] <= i < s_items[b]
         while (b - a > 1) {
-        const int m = (a + b) >> 1;
-        if (s_items[m] <= i) a = m; else b = m;
+            const int m = (a + b) >> 1;
+            if (s_items[m] <= i) a = m; else b = m;
         }
         const int c = s_start[a + 1] - s_start[a];
         const int ni = slot_items(c, cap);
