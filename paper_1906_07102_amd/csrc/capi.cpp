@@ -130,9 +130,9 @@ int fit_tile(int T, int N, lmg_precision prec, int W, int Ms) {
 // compute unit (tiles of 32 cells), else one (64-cell tiles: 4.2M visibilities on 8192^2 in FP32 154 us with one, 207
 // with two). With one patch the flushes of a workgroup's waves wait for each other: four waves on one / two patches,
 // W = 7 kernel times, 16.8M visibilities FP32 206 / 187 us, compensated 293 / 274, FP64 474 / 450; 3.0M of one density
-// on 2048^2 FP32 114 / 84, compensated 176 / 122, FP64 188 / 147. (256 sparse channels, compensated, are the exception: W = 5 438 with one
-// patch and three waves, 507 with two and four.) A function of the grid, mode, support, table and tile: the
-// number of patches fixes the order of the sums, which a batch and a single channel share.
+// on 2048^2 FP32 114 / 84, compensated 176 / 122, FP64 188 / 147. (256 sparse channels, compensated, are the exception:
+// W = 5 438 with one patch and three waves, 507 with two and four.) A function of the grid, mode, support, table and
+// tile: the number of patches fixes the order of the sums, which a batch and a single channel share.
 //
 // Wide plain FP32 and FP64 sums take more, as many more flushes reach a cell: from W = 9 on four in FP32 where two
 // workgroups of four fit (1.0M visibilities on 2048^2, W = 14: two 8.8e-8 against FP64, four 6.6e-8), three on 64-cell
