@@ -137,10 +137,13 @@ int fit_tile(int T, int N, lmg_precision prec, int W, int Ms) {
 // Wide plain FP32 and FP64 sums take more, as many more flushes reach a cell: from W = 9 on four in FP32 where two
 // workgroups of four fit (1.0M visibilities on 2048^2, W = 14: two 8.8e-8 against FP64, four 6.6e-8), three on 64-cell
 // tiles (1.0M on 8192^2, W = 12: one 1.05e-7, three 7.2e-8; with six waves also the faster, 283 and 230 us); in FP64 two
-// where only one workgroup of two fits (W = 15 and 16).
-int fit_patches(int T, int lsub, lmg_precision prec, int W, int Ms) {
+// where only one workgroup of two fits (W = 15 and 16). Four also at W = 5 and 6 on grids of up to 128^2, whose few tiles
+// hold an array's whole centre (4,500 crowded visibilities with a strong source, relative RMS against FP64 at W = 6: two
+// 5.71e-8, four 4.84e-8; 13.7 and 15.1 us at W = 5, 15.1 and 17.7 at W = 6 with 2,162 of tracks).
+int fit_patches(int N, int T, int lsub, lmg_precision prec, int W, int Ms) {
     auto groups = [&](int s) { return static_cast<int>(kMaxLds / (grid_lds_bytes(prec, W, T, Ms, s) + 256)); };
     const int two = groups(2) >= 2 ? 2 : 1;
+    if (prec == LMG_F32 && N <= 128 && (W == 5 || W == 6) && groups(4) >= 2) return 4;
     if (prec == LMG_F32 && W >= 9) return groups(4) >= 2 ? 4 : T > 32 && groups(3) >= 1 ? 3 : two;
     if (prec == LMG_F64 && T <= 32 && lsub == 0 && groups(2) >= 1) return 2;
     return two;
@@ -510,6 +513,14 @@ lmg_status wait_plan(const lmg_plan* p, hipStream_t s) {
     return LMG_OK;
 }
 
+// Plain FP32 grids of up to 1024^2, whose items have few turns: an item without a turn of full pieces deals its pieces one
+// by one to the turns, and with them the patches, of a group. Taken 64 neighbours at a time, the flushes of a few dense
+// cells fall to one patch and round against a large sum (relative RMS against FP64 with a strong source at the centre, 64
+// at a time / dealt: W = 6, 12,000 visibilities on 256^2 6.9e-8 / 5.7e-8; W = 7, 60,000 on 512^2 8.0e-8 / 5.9e-8). A turn
+// then takes as long as the longest of more pieces: 201,600 on 1024^2, W = 7 36.7 / 37.9 us, 3.0M in 48 channels 125 /
+// 127; on larger grids, whose items have enough turns without it, 8.4M on 4096^2, W = 7 112 / 116.
+bool deal_pieces(const lmg_plan* p) { return p->prec == LMG_F32 && p->g.N <= 1024; }
+
 // Gridding of visibilities already in entry order (weights applied) through
 // the plan: overwrite the grid (every cell of the window written), or add to
 // it (accumulate: only tiles that receive patches are read and written).
@@ -521,7 +532,8 @@ lmg_status run_grid_entries(const lmg_plan* p, const void* vs, void* grid, void*
     a.N = p->g.N; a.W = p->g.W; a.T = p->g.T >> p->g.lsub; a.ntx = p->g.ntx << p->g.lsub; a.lsub = p->g.lsub;
     a.Ms = table_ms(t); a.degree = kernel_degree(t);
     a.tab_global = table_global(t, p->prec) ? 1 : 0;
-    a.n_items = p->flags + 1; a.max_items = p->max_items << (2 * p->g.lsub); a.npatch = p->npatch; a.waves = p->waves; a.Ft = p->Ft; a.kb = p->kb;
+    a.n_items = p->flags + 1; a.max_items = p->max_items << (2 * p->g.lsub); a.npatch = p->npatch; a.waves = p->waves;
+    a.deal = deal_pieces(p) ? 1 : 0; a.Ft = p->Ft; a.kb = p->kb;
     a.items = p->sub; a.pieces = p->pieces; a.off = p->off; a.coef = p->coef;
     a.vis = vs; a.patches = patches; a.by_entry = p->by_entry ? 1 : 0;
     a.counter = counters; a.counter_zero = counter_zero ? 1 : 0;
@@ -645,7 +657,7 @@ lmg_status create_plan(const lmg_table* table, int N, lmg_precision prec, int nc
     const int64_t items = most_items(N, T, nchan, nvis, cap);
     const int lsub = items <= INT32_MAX / 4 ? tile_lsub(N, T, prec) : 0;
     const int Tq = T >> lsub;
-    const int npatch = fit_patches(Tq, lsub, prec, table->W, Ms);
+    const int npatch = fit_patches(N, Tq, lsub, prec, table->W, Ms);
     const int waves = fit_waves(Tq, N, nchan, nvis, cap, prec, table->W, npatch);
     if (grid_lds_bytes(prec, table->W, Tq, Ms, npatch) > kMaxDynLds) return LMG_ENOTSUP;
     const Layout L = plan_layout(N, nvis, prec, cap, nchan);

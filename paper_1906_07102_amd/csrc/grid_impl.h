@@ -299,10 +299,15 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<Acc, W, kTab>()))) void k_grid
         constexpr int kB = kTab == kTabDirect ? 2 : sizeof(R) == 8 && W >= 6 ? 1 : kWide;
         const int np = it.w & 0xffff, fturns = it.w >> 16;  // pieces; turns of full pieces only
         const int turns = (np + 63) >> 6;
-        // the lane's piece of turn j: turns count from the shortest tails (a ragged last run of 64) to the full pieces
+        // the lane's piece of turn j: turns count from the shortest tails (a ragged last run of 64) to the full pieces.
+        // Dealt: S runs, each of another patch, take 64 S pieces by turns (such groups count from the longest pieces).
+        const bool deal = std::is_same<Acc, AccF32>::value && a.deal && fturns == 0;
+        const int nth = deal ? (turns - 1 + S - wave % S) % S : 0;      // of the wave's runs in their groups
         auto piece_of = [&](int j) {
             const int run = turns - 1 - j;
-            return run < 0 ? np : run < fturns ? lane * fturns + run : run * 64 + lane;
+            if (run < 0) return np;
+            if (deal) return (run - nth) * 64 + lane * min(S, turns - run + nth) + nth;
+            return run < fturns ? lane * fturns + run : run * 64 + lane;
         };
 #pragma unroll
         for (int pass = 0; pass < NPASS; ++pass) {

@@ -67,6 +67,7 @@ struct GridArgs {
     const int* n_items;    // device: number of work items (written by the plan)
     int max_items;         // most work items the plan can have (sizes the launch), quadrants counted
     int npatch, waves;     // LDS patches per workgroup; waves per workgroup, a multiple of it up to kMaxGridWaves
+    int deal;              // 1: the pieces of npatch consecutive turns are dealt to them one by one (plain FP32)
     int Ft, kb;            // packed offsets: bits of the in-interval fraction t and of the interval k
     const int4* items;     // (tile, first position, count, pieces)
     const int2* pieces;    // (first entry, length | cell << 16)
