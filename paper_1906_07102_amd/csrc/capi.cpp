@@ -156,7 +156,10 @@ int fit_patches(int N, int T, int lsub, lmg_precision prec, int W, int Ms) {
 // 30; but data of one density, whose items have few turns, 300K on 1024^2 at W = 7 26 / 39 / 31. More items than five to
 // a compute unit do better with four where the flush of W^2 cells takes longer than the sums before it (1.0M in 24
 // channels of 512^2, W = 6 53 / 67 / 66 us; W = 5 41 / 38 / 37; FP64, W = 8 300 / 238 / 235). The estimate takes a
-// quarter of the tiles as occupied, as an image's data are. Plain FP32 at W = 8, where registers hold a compute unit to
+// quarter of the tiles as occupied, as an image's data are. On grids of up to four tiles an edge that quarter's items are
+// alike and all take their time at once: from two to a compute unit on (in FP64 from W = 8 four) they do better with four
+// waves (eight / four, 500,000 visibilities in 128 channels of 128^2, W = 6 compensated 52 / 42 us, W = 8 FP64 189 / 243;
+// 1.0M in 256, W = 7 FP32 86 / 55, compensated 98 / 75, FP64 127 / 98). Plain FP32 at W = 8, where registers hold a compute unit to
 // eight waves, works on four items at a time with two waves each rather than on two (15.8M in 256 channels of 1024^2 662
 // us, with four waves 834; 4.0M 390 and 507; 4.0M of one density on 4096^2 178 and 207; 4.2M of tracks 131 and 126).
 // (env LMG_GRID_WAVES overrides, 1 .. kMaxGridWaves, to the next multiple of the patches)
@@ -166,7 +169,8 @@ int fit_waves(int T, int N, int nchan, int64_t nvis, int cap, lmg_precision prec
         return std::min((forced + npatch - 1) / npatch, kMaxGridWaves / npatch) * npatch;
     if (npatch == 3) return 6;
     const int64_t tiles = static_cast<int64_t>(N / T) * (N / T) * nchan;
-    const int64_t few = prec != LMG_F64 && W >= 6 ? 1280 : 2048;
+    const int64_t even = prec == LMG_F64 && W >= 8 ? 1024 : 512;
+    const int64_t few = N / T <= 4 && (prec == LMG_F64 || W >= 6) ? even : prec != LMG_F64 && W >= 6 ? 1280 : 2048;
     if (nvis <= (int64_t{1} << 20) && std::min((tiles + 3) / 4, nvis) + nvis / cap <= few) return 8;
     return prec == LMG_F32 && W == 8 && npatch == 2 && nvis > (int64_t{1} << 20) ? 2 : 4;
 }
