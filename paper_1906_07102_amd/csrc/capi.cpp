@@ -159,9 +159,10 @@ int fit_patches(int N, int T, int lsub, lmg_precision prec, int W, int Ms) {
 // quarter of the tiles as occupied, as an image's data are. On grids of up to four tiles an edge that quarter's items are
 // alike and all take their time at once: from two to a compute unit on (in FP64 from W = 8 four) they do better with four
 // waves (eight / four, 500,000 visibilities in 128 channels of 128^2, W = 6 compensated 52 / 42 us, W = 8 FP64 189 / 243;
-// 1.0M in 256, W = 7 FP32 86 / 55, compensated 98 / 75, FP64 127 / 98). Plain FP32 at W = 8, where registers hold a compute unit to
-// eight waves, works on four items at a time with two waves each rather than on two (15.8M in 256 channels of 1024^2 662
-// us, with four waves 834; 4.0M 390 and 507; 4.0M of one density on 4096^2 178 and 207; 4.2M of tracks 131 and 126).
+// 1.0M in 256, W = 7 FP32 86 / 55, compensated 98 / 75, FP64 127 / 98). Plain FP32 at W = 8, where registers hold a
+// compute unit to eight waves, works on four items at a time with two waves each rather than on two (15.8M in 256
+// channels of 1024^2 662 us, with four waves 834; 4.0M 390 and 507; 4.0M of one density on 4096^2 178 and 207; 4.2M of
+// tracks 131 and 126).
 // (env LMG_GRID_WAVES overrides, 1 .. kMaxGridWaves, to the next multiple of the patches)
 int fit_waves(int T, int N, int nchan, int64_t nvis, int cap, lmg_precision prec, int W, int npatch) {
     const int forced = env_int("LMG_GRID_WAVES", 0);

@@ -236,7 +236,9 @@ __device__ __forceinline__ void flush_rows(typename Acc::Cell* patch, unsigned c
 // then rounds while it is small, which halves the error that the flushes add
 // (relative RMS of the grid against FP64, W = 7, longest first / shortest first
 // with the FP64 merges: 201,600 visibilities on 1024^2 8.19e-8 / 6.37e-8, 16.8M on
-// 4096^2 6.82e-8 / 5.47e-8; the time does not change by more than 2 %). A workgroup has S = a.npatch patches and
+// 4096^2 6.82e-8 / 5.47e-8), and the waves of a patch flush one after another
+// while the longer pieces are still summed (compensated, W = 7, 201,600 on
+// 1024^2 55 / 46 us, 1.0M on 2048^2 79 / 66). A workgroup has S = a.npatch patches and
 // `waves` waves, a multiple of S; turn j is accumulated in registers by wave
 // j mod waves and flushed into patch j mod S, after the turns before it on
 // that patch (s_turn counts them). So the order of every sum is that of the
@@ -299,12 +301,15 @@ __attribute__((amdgpu_waves_per_eu(waves_per_simd<Acc, W, kTab>()))) void k_grid
         constexpr int kB = kTab == kTabDirect ? 2 : sizeof(R) == 8 && W >= 6 ? 1 : kWide;
         const int np = it.w & 0xffff, fturns = it.w >> 16;  // pieces; turns of full pieces only
         const int turns = (np + 63) >> 6;
-        // the lane's piece of turn j: turns count from the shortest tails (a ragged last run of 64) to the full pieces.
+        // the lane's piece of turn j: turns count from the shortest tails (a ragged last run of 64) to the full pieces; from
+        // the full pieces where direct weights make a long last turn the item's time and sums are not plain FP32 (8.4M on
+        // 4096^2, shortest / longest first: compensated W = 2 374 / 330 us, 6 846 / 713; FP64 W = 1 310 / 279, 4 559 / 520).
         // Dealt: S runs, each of another patch, take 64 S pieces by turns (such groups count from the longest pieces).
-        const bool deal = std::is_same<Acc, AccF32>::value && a.deal && fturns == 0;
+        constexpr bool kPlain = std::is_same<Acc, AccF32>::value, kLongFirst = kTab == kTabDirect && !kPlain;
+        const bool deal = kPlain && a.deal && fturns == 0;
         const int nth = deal ? (turns - 1 + S - wave % S) % S : 0;      // of the wave's runs in their groups
         auto piece_of = [&](int j) {
-            const int run = turns - 1 - j;
+            const int run = kLongFirst ? (j < turns ? j : -1) : turns - 1 - j;
             if (run < 0) return np;
             if (deal) return (run - nth) * 64 + lane * min(S, turns - run + nth) + nth;
             return run < fturns ? lane * fturns + run : run * 64 + lane;
