@@ -148,6 +148,11 @@ int fit_patches(int N, int T, int lsub, lmg_precision prec, int W, int Ms) {
     if (prec == LMG_F64 && T <= 32 && lsub == 0 && groups(2) >= 1) return 2;
     return two;
 }
+// Work items to be expected of a plan: a quarter of the tiles, as an image's data occupy, and one for every cap visibilities.
+int64_t expected_items(int T, int N, int nchan, int64_t nvis, int cap) {
+    const int64_t tiles = static_cast<int64_t>(N / T) * (N / T) * nchan;
+    return std::min((tiles + 3) / 4, nvis) + nvis / cap;
+}
 // Waves per gridding workgroup, a multiple of its patches: four, as an item has about four turns (16.8M visibilities:
 // 4.1) and the waves beyond an item's turns only wait (4.2M, W = 10, compensated: 234 us with four, 344 with six).
 // A launch of few items, which does not fill the chip, so that an item's latency is what counts, gets eight, two to each
@@ -169,10 +174,9 @@ int fit_waves(int T, int N, int nchan, int64_t nvis, int cap, lmg_precision prec
     if (forced >= 1 && forced <= kMaxGridWaves)
         return std::min((forced + npatch - 1) / npatch, kMaxGridWaves / npatch) * npatch;
     if (npatch == 3) return 6;
-    const int64_t tiles = static_cast<int64_t>(N / T) * (N / T) * nchan;
     const int64_t even = prec == LMG_F64 && W >= 8 ? 1024 : 512;
     const int64_t few = N / T <= 4 && (prec == LMG_F64 || W >= 6) ? even : prec != LMG_F64 && W >= 6 ? 1280 : 2048;
-    if (nvis <= (int64_t{1} << 20) && std::min((tiles + 3) / 4, nvis) + nvis / cap <= few) return 8;
+    if (nvis <= (int64_t{1} << 20) && expected_items(T, N, nchan, nvis, cap) <= few) return 8;
     return prec == LMG_F32 && W == 8 && npatch == 2 && nvis > (int64_t{1} << 20) ? 2 : 4;
 }
 
@@ -585,6 +589,19 @@ bool degrid_by_quadrants(const lmg_plan* p) {
     return p->prec == LMG_F64 && p->g.W >= 6 && p->g.W <= 8 && p->nvis >= (p->g.W == 8 ? 3000000 : 6000000);
 }
 
+// One degridding workgroup per compute unit, where registers and LDS would hold two (of 1,024 threads, whose reads of W^2
+// cells per visibility compete): launches of one to seven items to a compute unit, which then balance over twice the
+// rounds (one / two, 500,000 visibilities in 128 channels of 128^2, FP32 W = 10 52 / 77 us, FP64 W = 7 44 / 57; 1.0M in
+// 24 channels of 512^2, FP32 W = 8 69 / 89, W = 14 96 / 130). With more items the second workgroup fills its patch while
+// the first sums (3.0M in 48 channels of 1024^2, W = 10 174 / 153), with fewer or sparse ones nothing competes. Below
+// W = 8 FP32 gains on few of these and loses on others (1.0M on 1024^2 of one density, W = 7 0.79 of two's time; 4.0M on
+// 2048^2 1.04); FP64 above W = 8 has registers for one only.
+bool one_degrid_group(const lmg_plan* p) {
+    const int64_t items = expected_items(p->g.T, p->g.N, p->nchan, p->nvis, p->cap);
+    const bool two = p->prec == LMG_F64 ? p->g.W <= 8 : p->g.W >= 8;
+    return two && items > 340 && items <= (p->g.W >= 14 ? 4096 : 1700) && p->nvis >= 128 * items;
+}
+
 // Degridding into entry order.
 lmg_status run_degrid_entries(const lmg_plan* p, const void* grid, bool transposed, void* vs, int* counters,
                               bool counter_zero, hipStream_t s) {
@@ -598,7 +615,7 @@ lmg_status run_degrid_entries(const lmg_plan* p, const void* grid, bool transpos
     a.n_items = p->flags + 1; a.max_items = p->max_items << (2 * lsub); a.Ft = p->Ft; a.kb = p->kb;
     a.items = lsub ? p->sub : p->items; a.pieces = p->pieces; a.off = p->off; a.coef = p->coef;
     a.grid = grid; a.transpose = transposed ? 1 : 0; a.vis_out = vs; a.counter = counters + 1;
-    a.counter_zero = counter_zero ? 1 : 0;
+    a.counter_zero = counter_zero ? 1 : 0; a.one_group = one_degrid_group(p) ? 1 : 0;
     TraceScope ts("degrid_items", s);
     LMG_HIP(launch_degrid(p->prec, a, s));
     return LMG_OK;

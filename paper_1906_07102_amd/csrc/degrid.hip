@@ -102,12 +102,9 @@ hipError_t launch_degrid_w(const DegridArgs& a, hipStream_t s) {
     const int P = a.T + W - 1;
     const size_t tab = kTab == kTabLds ? ((static_cast<size_t>(a.Ms + 1) * W * 4 * sizeof(R)) + 15) & ~size_t(15) : 0;
     const size_t need = tab + static_cast<size_t>(P) * P * sizeof(typename dev::C2<R>::T);
-    // FP32 at W >= 14: one workgroup per compute unit, by asking for more than half of its LDS. Two of 1,024 threads, for
-    // which the registers suffice there, read patches of W^2 cells per visibility against each other (one / two, 1.0M in 24
-    // channels of 512^2, W = 14 96 / 130 us, 16 182 / 251; 1.0M on 2048^2 86 / 96, 167 / 187; 3.0M in 48 channels of
-    // 1024^2 261 / 250, 435 / 436).
+    // one workgroup per compute unit, by asking for more than half of its LDS
     constexpr size_t kMoreThanHalf = kMaxLds / 2 + 1024;
-    const size_t shm = sizeof(R) == 4 && W >= 14 ? std::max(need, kMoreThanHalf) : need;
+    const size_t shm = a.one_group ? std::max(need, kMoreThanHalf) : need;
     const void* fn = reinterpret_cast<const void*>(&dev::k_degrid_items<R, W, kTab>);
     static const hipError_t attr = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxDynLds);
     if (attr != hipSuccess) return attr;

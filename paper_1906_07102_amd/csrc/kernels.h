@@ -115,6 +115,7 @@ struct DegridArgs {
     void* vis_out;         // entry order
     int* counter;          // work-item counter
     int counter_zero;      // 1: an earlier launch zeroed it; 0: the launcher does, where it is read at all
+    int one_group;         // 1: one workgroup per compute unit
 };
 
 struct FftArgs {
